@@ -442,8 +442,10 @@ int lm_head_gemv_q4(const specee_dims *dm, int N, const specee_half *hidden, con
     if ((rc = check_q4(dm, qweight, scales, zeros, group))) return rc;
     if (!hidden || !gamma || !out) return SPECEE_EINVAL;
     if (misaligned(hidden) || misaligned(gamma)) return SPECEE_EALIGN;
-    return launch_lm_head_q4(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), qweight, H(scales), H(zeros), group, out,
-                             static_cast<hipStream_t>(stream)) == hipSuccess
+    // one hidden state (or a format whose chunks cross groups): vector units; more: one pass per 16 on the matrix cores
+    const auto launch = lm_head_q4_mfma_supported(dm->d, N, group, qweight) ? launch_lm_head_q4_mfma : launch_lm_head_q4;
+    return launch(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), qweight, H(scales), H(zeros), group, out,
+                  static_cast<hipStream_t>(stream)) == hipSuccess
                ? SPECEE_OK
                : SPECEE_EHIP;
 }
@@ -460,14 +462,17 @@ int specee_verify_q4(const specee_dims *dm, int N, const specee_half *hidden, co
     if ((rc = check_q4(dm, qweight, scales, zeros, group))) return rc;
     if (!hidden || !gamma || !ids || !token || !max_logit || !hit) return SPECEE_EINVAL;
     if (misaligned(hidden) || misaligned(gamma) || misaligned(workspace)) return SPECEE_EALIGN;
-    const int P = lm_head_q4_workgroups(dm->V);
-    const size_t half_ws = align256((size_t)N * P * sizeof(float));
+    // the workspace is sized for the vector kernel's candidates; the matrix-core kernel leaves at most as many
+    const size_t half_ws = align256((size_t)N * lm_head_q4_workgroups(dm->V) * sizeof(float));
     if (!workspace || workspace_bytes < 2 * half_ws) return SPECEE_EWORKSPACE;
     float *best_val = static_cast<float *>(workspace);
     int32_t *best_idx = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + half_ws);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (launch_lm_head_q4_argmax(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), qweight, H(scales), H(zeros), group,
-                                 best_val, best_idx, gate, done, st) != hipSuccess)
+    const bool mfma = lm_head_q4_mfma_supported(dm->d, N, group, qweight);
+    const int P = mfma ? lm_head_q4_mfma_workgroups(dm->V) : lm_head_q4_workgroups(dm->V);
+    const auto launch = mfma ? launch_lm_head_q4_mfma_argmax : launch_lm_head_q4_argmax;
+    if (launch(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), qweight, H(scales), H(zeros), group, best_val, best_idx,
+               gate, done, st) != hipSuccess)
         return SPECEE_EHIP;
     return launch_verify_finish(best_val, best_idx, P, N, ids, dm->K, gate, done, token, max_logit, hit, st) ==
                    hipSuccess

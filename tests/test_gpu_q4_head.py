@@ -160,3 +160,49 @@ def test_q4_head_argument_errors(sp):
     with pytest.raises(sp.SpeceeError) as ei:
         sp.verify_q4(*a, 16, dev(t["ids"]), workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
     assert ei.value.code == -3
+
+
+@pytest.mark.parametrize("d,V,N,group,hscale,misalign", [
+    (4096, 257, 16, 128, 1.0, 0),      # whole stages, one row past two blocks of 128
+    (640, 128, 2, 128, 1.0, 0),        # ragged last stage; the fewest states
+    (512, 127, 17, 64, 1.0, 0),        # two words per chunk; a second tile of states holding one
+    (96, 33, 3, 32, 1.0, 0),           # one word per chunk, less than a share of a stage
+    (1024, 130, 5, 256, 1.0, 2),       # several chunks per group; codes and scales off 16-byte alignment
+    (64, 65665, 4, 64, 1.0, 0),        # two row blocks per workgroup, ragged end
+    (512, 129, 8, 128, 2.0 ** -13, 0), # hidden states near the smallest normal halves
+    (512, 129, 8, 128, 16000.0, 0),    # products with the norm weight beyond the range of halves
+])
+def test_lm_head_q4_several_states(sp, oracle, d, V, N, group, hscale, misalign):
+    """Matrix-core pass (two or more states).  Every product enters whole, so the error is that of fp32 sums: a term
+    passes at most 3 * 4 * 32 additions of a chunk, d / 512 folds and a handful of combining steps, each off by
+    2^-24 of what it has summed, which sum |x| scale (code + zero) bounds."""
+    t = case(d + V + N, d, V, 2, 8, N, group, False)
+    t["hidden"] = (t["hidden"].astype(np.float32).clip(-4, 4) * hscale).astype(np.float16)
+    if hscale > 1:
+        t["gamma"] = (t["gamma"] * 2).astype(np.float16)
+    ref = oracle.lm_head_gemv_q4(t["hidden"], t["gamma"], t["q"], t["scales"], t["zeros"], group)
+    h, g = t["hidden"].astype(np.float64), t["gamma"].astype(np.float64)
+    r = 1.0 / np.sqrt((h * h).mean(axis=1) + 1e-5)
+    codes = (t["q"][:, :, None] >> (4 * np.arange(8, dtype=np.uint32))) & 15
+    s, z = (np.repeat(a.astype(np.float64), group, axis=1) for a in (t["scales"], t["zeros"]))
+    bound = np.abs(h * g) * r[:, None] @ (s * (codes.reshape(V, d) + z)).T
+    qd, sd, zd = qdev(t)
+    if misalign:  # views that start 8 bytes past a 16-byte boundary
+        qb = torch.zeros(qd.numel() + 2, dtype=torch.int32, device="cuda")
+        qb[2:] = qd.flatten()
+        qd = qb[2:].view(qd.shape)
+        sb = torch.zeros(sd.numel() + 4, dtype=torch.float16, device="cuda")
+        sb[4:] = sd.flatten()
+        sd = sb[4:].view(sd.shape)
+    out = torch.full((N, V), float("nan"), device="cuda")
+    got = host(sp.lm_head_gemv_q4(dev(t["hidden"]), dev(t["gamma"]), qd, sd, zd, group, out=out))
+    assert np.isfinite(got).all()
+    assert np.all(np.abs(got - ref) <= (3 * 4 * 32 + d / 512 + 8) * 2.0 ** -24 * bound)
+    ids = t["ids"].copy()
+    ids[:, 0] = ref.argmax(axis=1)
+    v = sp.verify_q4(dev(t["hidden"]), dev(t["gamma"]), qd, sd, zd, group, dev(ids))
+    torch.cuda.synchronize()
+    v = {k: host(a) for k, a in v.items()}
+    rows = np.arange(N)
+    # the same sums decide: the token is the arg-max of the logits this library returns, bit for bit
+    assert np.array_equal(v["token"], got.argmax(axis=1)) and np.array_equal(v["max_logit"], got[rows, v["token"]])
