@@ -10,6 +10,13 @@ namespace specee {
 
 typedef _Float16 half_t;
 
+// Trees whose nodes are the tokens of a predictor launch: what the merge needs beside PredictParams
+struct TreeMergeParams {
+    int G, n, Mcap;      // trees, ids per tree, capacity of a tree's merged set
+    const int32_t *ids;  // [G][n]
+    int32_t *merged, *M_out, *cols;
+};
+
 struct PredictParams {
     int d, V, K, H;
     float eps, threshold;
@@ -29,7 +36,12 @@ struct PredictParams {
     int group;
     float *logits, *probs, *scores;
     int32_t *exit_flags;
+    TreeMergeParams tree;  // launch_tree_nodes only
 };
+
+// Trees scored node by node (B = G * N tokens): predictor and merge in one launch, then overflow and path rule
+bool tree_nodes_preferred(int total_nodes, int n_ids, int K, int H, bool q4);
+hipError_t launch_tree_nodes(const PredictParams &p, int N, const int32_t *parent, int32_t *path_exit, hipStream_t s);
 
 hipError_t launch_predict(const PredictParams &p, hipStream_t s);
 hipError_t launch_predict_q4(const PredictParams &p, hipStream_t s);

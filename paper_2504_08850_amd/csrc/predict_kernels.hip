@@ -13,11 +13,30 @@
 // fixed-order LDS exchange across the eight wavefronts.
 #include "device_utils.h"
 #include "kernels.h"
+#include "merge_block.h"
 #include "predictor_tail.h"
+#include "tree_finish.h"
 
 namespace specee {
 
 constexpr int kPredictThreads = 512;
+
+// The merge of one tree's ids, by a workgroup of its own of the launch that scores the trees' nodes (TREE below):
+// the nodes read their rows by id and need nothing of it, so it is off their path.
+template <int T>
+__device__ __forceinline__ void merge_one_tree(const TreeMergeParams &m, int g) {
+    extern __shared__ __attribute__((aligned(16))) int32_t tree_merge_lds[];
+    int32_t *uniq;
+    int col_of[kMergePerThread];
+    const int M = merge_block<T>(m.ids + (size_t)g * m.n, m.n, tree_merge_lds, uniq, col_of);
+    if (threadIdx.x == 0) m.M_out[g] = M;
+    for (int i = threadIdx.x; i < m.Mcap; i += T) m.merged[(size_t)g * m.Mcap + i] = i < M ? uniq[i] : -1;
+#pragma unroll
+    for (int e = 0; e < kMergePerThread; ++e) {
+        const int i = threadIdx.x + e * T;
+        if (i < m.n) m.cols[(size_t)g * m.n + i] = col_of[e];
+    }
+}
 
 // KC: speculative rows held in flight (K <= KC).  VPT: 16-byte vectors per
 // thread per row (d/8 <= VPT * 512 * tiles).  SWEEP: the previous layer's local
@@ -31,8 +50,13 @@ constexpr int kPredictThreads = 512;
 // workgroups fit on a CU, so more independent chains of the two memory trips are in flight, and the
 // redundant feature arithmetic and the barriers halve; a thread then owns MU = 2 hidden units, both
 // requested up front.
-template <int KC, int VPT, bool SWEEP, bool EXACT, int T = kPredictThreads, int MU = 1>
+// TREE: the tokens are the nodes of p.tree.G trees; the first p.tree.G workgroups merge the trees' ids.
+template <int KC, int VPT, bool SWEEP, bool EXACT, int T = kPredictThreads, int MU = 1, bool TREE = false>
 __global__ __launch_bounds__(T) void predict_kernel(PredictParams p) {
+    if (TREE && (int)blockIdx.x < p.tree.G) {
+        merge_one_tree<T>(p.tree, blockIdx.x);
+        return;
+    }
     constexpr int kWaves = T / kWave;
     // throughput shape: hidden states pass through once, so they are read with the non-temporal hint; the
     // LM-head rows are not -- tokens of a batch share rows, and the hint costs those re-reads their cache
@@ -45,7 +69,7 @@ __global__ __launch_bounds__(T) void predict_kernel(PredictParams p) {
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = tid >> 6;
-    const int b = blockIdx.x;
+    const int b = TREE ? (int)blockIdx.x - p.tree.G : (int)blockIdx.x;
     const int l = blockIdx.y;
     const int K = EXACT ? KC : p.K, H = p.H, d = p.d;
     const int nv = d >> 3;
@@ -327,13 +351,17 @@ __device__ __forceinline__ void q4_tail(const PredictParams &p, int b, int K, fl
 // EXACT: K == KC at compile time (see predict_kernel).  Every load is unconditional on a clamped, valid
 // address -- a load under a branch would make the compiler wait for all outstanding loads at the join
 // and turn the K rows into K serial trips to memory; unused data is zeroed by selects instead.
-template <int KC, int VPT, bool EXACT, int T = kPredictThreads, int MU = 1>
+template <int KC, int VPT, bool EXACT, int T = kPredictThreads, int MU = 1, bool TREE = false>
 __global__ __launch_bounds__(T) void predict_q4_kernel(PredictParams p) {
+    if (TREE && (int)blockIdx.x < p.tree.G) {
+        merge_one_tree<T>(p.tree, blockIdx.x);
+        return;
+    }
     constexpr int kWaves = T / kWave;
     __shared__ float red[kWaves][KC + 1];
     __shared__ float red_u[kWaves];
     const int tid = threadIdx.x;
-    const int b = blockIdx.x;
+    const int b = TREE ? (int)blockIdx.x - p.tree.G : (int)blockIdx.x;
     const int K = EXACT ? KC : p.K, H = p.H, d = p.d;
     const int nv = d >> 3, ng = d / p.group;
 
@@ -456,14 +484,18 @@ __global__ __launch_bounds__(T) void predict_q4_kernel(PredictParams p) {
 // row serve all 32 elements.  Per token that is a third of the load instructions of the word-per-thread
 // layout (the small scale / zero-point loads dominate there), and the vector memory path, not HBM, is
 // what a CU runs out of first with rows this short.  CPT: chunks per thread (d <= 32 * T * CPT).
-template <int KC, int T, int CPT, int MU>
+template <int KC, int T, int CPT, int MU, bool TREE = false>
 __global__ __launch_bounds__(T) void predict_q4_wide_kernel(PredictParams p) {
+    if (TREE && (int)blockIdx.x < p.tree.G) {
+        merge_one_tree<T>(p.tree, blockIdx.x);
+        return;
+    }
     constexpr int kWaves = T / kWave;
     constexpr int K = KC;
     __shared__ float red[kWaves][KC + 1];
     __shared__ float red_u[kWaves];
     const int tid = threadIdx.x;
-    const int b = blockIdx.x;
+    const int b = TREE ? (int)blockIdx.x - p.tree.G : (int)blockIdx.x;
     const int H = p.H, d = p.d;
     const int nc = d >> 5, nv = d >> 3, ng = d / p.group;
 
@@ -585,9 +617,10 @@ __global__ void first_exit_kernel(const int32_t *exit_flags, int L, int B, int32
 
 constexpr int kBatchMinTokens = 1024;  // tokens per launch from which the throughput shapes are used
 
-template <int KC, bool SWEEP, bool EXACT>
+template <int KC, bool SWEEP, bool EXACT, bool TREE>
 static hipError_t launch_vpt(const PredictParams &p, hipStream_t s) {
-    dim3 grid(p.B, p.L), block(kPredictThreads);
+    dim3 grid(p.B + (TREE ? p.tree.G : 0), p.L), block(kPredictThreads);
+    const size_t lds = TREE ? (size_t)merge_lds_ints(p.tree.n) * sizeof(int32_t) : 0;
     const int nv = p.d >> 3;
     if constexpr (!SWEEP && EXACT && KC <= 8) {
         // throughput shape: K in {4, 8}, many tokens, rows of at most 4 * 256 vectors (d <= 8192)
@@ -598,38 +631,39 @@ static hipError_t launch_vpt(const PredictParams &p, hipStream_t s) {
         if ((p.B >= kBatchMinTokens || small_fit) && nv <= 2 * 256 * (KC == 4 ? 2 : 1)) {
             const dim3 blk(256);
             if (nv <= 2 * 256)
-                hipLaunchKernelGGL((predict_kernel<KC, 2, false, true, 256, 2>), grid, blk, 0, s, p);
+                hipLaunchKernelGGL((predict_kernel<KC, 2, false, true, 256, 2, TREE>), grid, blk, lds, s, p);
             else
-                hipLaunchKernelGGL((predict_kernel<KC, 4, false, true, 256, 2>), grid, blk, 0, s, p);
+                hipLaunchKernelGGL((predict_kernel<KC, 4, false, true, 256, 2, TREE>), grid, blk, lds, s, p);
             return hipGetLastError();
         }
     }
     const int vpt = (nv + kPredictThreads - 1) / kPredictThreads;
     if (vpt <= 1)
-        hipLaunchKernelGGL((predict_kernel<KC, 1, SWEEP, EXACT>), grid, block, 0, s, p);
+        hipLaunchKernelGGL((predict_kernel<KC, 1, SWEEP, EXACT, kPredictThreads, 1, TREE>), grid, block, lds, s, p);
     else if (vpt <= 2 || KC > 8)
-        hipLaunchKernelGGL((predict_kernel<KC, 2, SWEEP, EXACT>), grid, block, 0, s, p);
+        hipLaunchKernelGGL((predict_kernel<KC, 2, SWEEP, EXACT, kPredictThreads, 1, TREE>), grid, block, lds, s, p);
     else if constexpr (KC <= 8)
-        hipLaunchKernelGGL((predict_kernel<KC, 4, SWEEP, EXACT>), grid, block, 0, s, p);
+        hipLaunchKernelGGL((predict_kernel<KC, 4, SWEEP, EXACT, kPredictThreads, 1, TREE>), grid, block, lds, s, p);
     return hipGetLastError();
 }
 
-template <bool SWEEP>
+template <bool SWEEP, bool TREE>
 static hipError_t launch_kc(const PredictParams &p, hipStream_t s) {
-    if (p.K == 4) return launch_vpt<4, SWEEP, true>(p, s);
-    if (p.K == 8) return launch_vpt<8, SWEEP, true>(p, s);
-    if (p.K < 4) return launch_vpt<4, SWEEP, false>(p, s);
-    if (p.K < 8) return launch_vpt<8, SWEEP, false>(p, s);
-    return launch_vpt<16, SWEEP, false>(p, s);
+    if (p.K == 4) return launch_vpt<4, SWEEP, true, TREE>(p, s);
+    if (p.K == 8) return launch_vpt<8, SWEEP, true, TREE>(p, s);
+    if (p.K < 4) return launch_vpt<4, SWEEP, false, TREE>(p, s);
+    if (p.K < 8) return launch_vpt<8, SWEEP, false, TREE>(p, s);
+    return launch_vpt<16, SWEEP, false, TREE>(p, s);
 }
 
 hipError_t launch_predict(const PredictParams &p, hipStream_t s) {
-    return launch_kc<false>(p, s);
+    return launch_kc<false, false>(p, s);
 }
 
-template <int KC, bool EXACT>
+template <int KC, bool EXACT, bool TREE>
 static hipError_t launch_q4_kc(const PredictParams &p, hipStream_t s) {
-    const dim3 grid(p.B), block(kPredictThreads);
+    const dim3 grid(p.B + (TREE ? p.tree.G : 0)), block(kPredictThreads);
+    const size_t lds = TREE ? (size_t)merge_lds_ints(p.tree.n) * sizeof(int32_t) : 0;
     const int nv = p.d >> 3;
     if constexpr (EXACT && KC == 4) {
         // throughput shape (see predict_kernel): a quantised row is a quarter of the bytes, so the fixed
@@ -639,40 +673,102 @@ static hipError_t launch_q4_kc(const PredictParams &p, hipStream_t s) {
         // B=8000 at d=4096: 37 -> 29 us, at d=8192: 71 -> 58 us
         const bool wide_ok = p.group % 32 == 0 && p.d % 32 == 0 && (reinterpret_cast<uintptr_t>(p.qweight) & 15) == 0;
         if (wide_ok && p.B >= kBatchMinTokens && p.d <= 32 * 128) {
-            hipLaunchKernelGGL((predict_q4_wide_kernel<4, 128, 1, 4>), grid, dim3(128), 0, s, p);
+            hipLaunchKernelGGL((predict_q4_wide_kernel<4, 128, 1, 4, TREE>), grid, dim3(128), lds, s, p);
             return hipGetLastError();
         }
         if (wide_ok && p.B >= kBatchMinTokens && p.d <= 32 * 256) {
-            hipLaunchKernelGGL((predict_q4_wide_kernel<4, 256, 1, 2>), grid, dim3(256), 0, s, p);
+            hipLaunchKernelGGL((predict_q4_wide_kernel<4, 256, 1, 2, TREE>), grid, dim3(256), lds, s, p);
             return hipGetLastError();
         }
         if (p.B >= kBatchMinTokens && nv <= 4 * 128) {
-            hipLaunchKernelGGL((predict_q4_kernel<4, 4, true, 128, 4>), grid, dim3(128), 0, s, p);
+            hipLaunchKernelGGL((predict_q4_kernel<4, 4, true, 128, 4, TREE>), grid, dim3(128), lds, s, p);
             return hipGetLastError();
         }
         if (p.B >= kBatchMinTokens && nv <= 4 * 256) {
-            hipLaunchKernelGGL((predict_q4_kernel<4, 4, true, 256, 2>), grid, dim3(256), 0, s, p);
+            hipLaunchKernelGGL((predict_q4_kernel<4, 4, true, 256, 2, TREE>), grid, dim3(256), lds, s, p);
             return hipGetLastError();
         }
     }
     if (nv <= kPredictThreads)
-        hipLaunchKernelGGL((predict_q4_kernel<KC, 1, EXACT>), grid, block, 0, s, p);
+        hipLaunchKernelGGL((predict_q4_kernel<KC, 1, EXACT, kPredictThreads, 1, TREE>), grid, block, lds, s, p);
     else
-        hipLaunchKernelGGL((predict_q4_kernel<KC, 2, EXACT>), grid, block, 0, s, p);
+        hipLaunchKernelGGL((predict_q4_kernel<KC, 2, EXACT, kPredictThreads, 1, TREE>), grid, block, lds, s, p);
     return hipGetLastError();
 }
 
+template <bool TREE>
+static hipError_t launch_q4_any(const PredictParams &p, hipStream_t s) {
+    if (p.K == 4) return launch_q4_kc<4, true, TREE>(p, s);
+    if (p.K == 8) return launch_q4_kc<8, true, TREE>(p, s);
+    if (p.K < 4) return launch_q4_kc<4, false, TREE>(p, s);
+    if (p.K < 8) return launch_q4_kc<8, false, TREE>(p, s);
+    return launch_q4_kc<16, false, TREE>(p, s);
+}
+
 hipError_t launch_predict_q4(const PredictParams &p, hipStream_t s) {
-    if (p.K == 4) return launch_q4_kc<4, true>(p, s);
-    if (p.K == 8) return launch_q4_kc<8, true>(p, s);
-    if (p.K < 4) return launch_q4_kc<4, false>(p, s);
-    if (p.K < 8) return launch_q4_kc<8, false>(p, s);
-    return launch_q4_kc<16, false>(p, s);
+    return launch_q4_any<false>(p, s);
+}
+
+// Second half of the node-by-node tree call: a tree whose merged set did not fit is refused as a whole (NaN, no
+// exit), otherwise the path rule on the exit flags.  One workgroup per tree.
+constexpr int kTreeTailThreads = 256;
+__global__ __launch_bounds__(kTreeTailThreads) void tree_tail_kernel(PredictParams p, int N, const int32_t *parent,
+                                                                     int32_t *path_exit) {
+    extern __shared__ __attribute__((aligned(16))) int32_t tree_tail_lds[];  // exit flags [N], parents [N]
+    int32_t *ex = tree_tail_lds, *par = tree_tail_lds + N;
+    const int g = blockIdx.x, tid = threadIdx.x;
+    const size_t base = (size_t)g * N;
+    for (int n = tid; n < N; n += kTreeTailThreads) {
+        ex[n] = p.exit_flags[base + n];
+        par[n] = path_exit ? parent[base + n] : -1;
+    }
+    if (p.tree.M_out[g] > p.tree.Mcap) {  // uniform over the workgroup
+        for (int n = tid; n < N; n += kTreeTailThreads) {
+            ex[n] = 0;  // (each thread its own entries)
+            p.exit_flags[base + n] = 0;
+            p.scores[base + n] = quiet_nan();
+        }
+        for (int i = tid; i < N * p.K; i += kTreeTailThreads) {
+            p.logits[base * p.K + i] = quiet_nan();
+            p.probs[base * p.K + i] = quiet_nan();
+        }
+    }
+    if (!path_exit) return;
+    __syncthreads();
+    finish_paths(ex, par, N, tid, kTreeTailThreads, path_exit + base);
+}
+
+// Trees scored node by node: every node is a token of its own that gathers its K rows, while one workgroup per tree
+// merges the ids beside them.  Against one workgroup per tree (or the split contraction of a few trees) this gives up
+// reading a shared row once per tree -- the caches serve the repeats -- and gains a chain of two memory trips per
+// node on every CU instead of merge -> contraction -> scoring in series.
+// Where the line lies (60-node trees, d = 4096, K = 4 unless given, node by node without the tail kernel's 2 us
+// against the tree kernels): fp16 1 tree 3.8 / 15.2 us, 16 trees 6.9 / 20.5, 64 trees 18.9 / 23.6, 96 trees
+// 26.9 / 27.8, 128 trees 33.7 / 31.0; d = 8192, K = 8, 64 nodes: 32 trees 30.4 / 48.2, 64 trees 56.1 / 63.2;
+// K = 5, d = 5120 (no matrix-core MLP in the tree kernel), 50 nodes: 64 trees 50 / 108, 128 trees 92 / 115.
+// Quantised rows: 16 trees 8.6 / 44.4 us, 128 trees 25.6 / 46.1, 256 trees 45.7 / 50.3; K = 8, d = 5120, 50 nodes:
+// 64 trees 46.3 / 54.3, 128 trees 82.6 / 54.9; K = 3, d = 4608, 40 nodes: 128 trees 56.9 / 84.4.
+// n ids of a tree: at most four per thread of the workgroup that merges them (256 threads; the 128-thread shape is
+// only taken by K = 4 on quantised rows, where a tree has at most 64 nodes).
+bool tree_nodes_preferred(int total_nodes, int n_ids, int K, int H, bool q4) {
+    if (n_ids > 4 * 256) return false;
+    const bool mfma = mlp_mfma_ok(K, H);
+    if (q4) return total_nodes <= (K == 4 && mfma ? 12288 : mfma ? 3072 : 6144);
+    return total_nodes <= (mfma ? 4096 : 8192);
+}
+
+hipError_t launch_tree_nodes(const PredictParams &p, int N, const int32_t *parent, int32_t *path_exit, hipStream_t s) {
+    const hipError_t e = p.qweight ? launch_q4_any<true>(p, s) : launch_kc<false, true>(p, s);
+    if (e != hipSuccess) return e;
+    if (!path_exit && p.tree.n <= p.tree.Mcap) return hipSuccess;  // no path rule, and the set always fits
+    hipLaunchKernelGGL(tree_tail_kernel, dim3(p.tree.G), dim3(kTreeTailThreads), (size_t)2 * N * sizeof(int32_t), s, p,
+                       N, parent, path_exit);
+    return hipGetLastError();
 }
 
 hipError_t launch_predict_sweep(const PredictParams &p, int32_t *first_exit, hipStream_t s) {
     if (p.L > 0) {
-        hipError_t e = launch_kc<true>(p, s);
+        hipError_t e = launch_kc<true, false>(p, s);
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(first_exit_kernel, dim3((p.B + 255) / 256), dim3(256), 0, s, p.exit_flags, p.L, p.B,

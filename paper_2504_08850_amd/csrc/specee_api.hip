@@ -59,11 +59,10 @@ TreeSplit tree_split(int d, int n_total, int N, int Mcap) {
 
 // Trees per launch from which one workgroup (or a few, see below) per tree beats spreading every
 // tree over the whole GPU, and the workgroups per launch the ticketed d-slices aim for (one
-// 512-thread workgroup per CU).  With more slices than kWholeMaxSlices the serial hand-off to the
-// last workgroup costs more than the slices save.  Measured on MI355X with 60-node trees.
+// 512-thread workgroup per CU).  Calls of up to a few thousand nodes take neither shape: their nodes
+// are scored one by one (tree_nodes_preferred).  Measured on MI355X with 60-node trees.
 constexpr int kWholeTreeMinTrees = 20;
 constexpr int kWholeTargetWgs = 256;
-constexpr int kWholeMaxSlices = 8;
 
 inline size_t align256(size_t b) {
     return (b + 255) & ~(size_t)255;
@@ -293,6 +292,22 @@ int lm_head_gemv(const specee_dims *dm, int N, const specee_half *hidden, const 
     return e == hipSuccess ? SPECEE_OK : SPECEE_EHIP;
 }
 
+// The nodes of G trees as the tokens of a predictor launch (the head is filled in by the caller)
+static PredictParams tree_nodes_params(const specee_dims *dm, int G, int N, int Mcap, const specee_half *hidden,
+                                       const specee_half *gamma, const int32_t *ids, const float *prev_probs,
+                                       const specee_mlp *mlp, int32_t *merged_ids, int32_t *M_out, int32_t *cols,
+                                       float *logits, float *probs, float *scores, int32_t *exit_flags) {
+    PredictParams p{};
+    p.d = dm->d; p.V = dm->V; p.K = dm->K; p.H = dm->H; p.eps = dm->eps; p.threshold = dm->threshold;
+    p.B = G * N; p.L = 1;
+    p.hidden = H(hidden); p.gamma = H(gamma); p.ids = ids; p.prev = prev_probs;
+    p.W1 = H(mlp->W1); p.b1 = H(mlp->b1); p.w2 = H(mlp->w2); p.b2 = H(mlp->b2);
+    p.logits = logits; p.probs = probs; p.scores = scores; p.exit_flags = exit_flags;
+    p.tree.G = G; p.tree.n = N * dm->K; p.tree.Mcap = Mcap; p.tree.ids = ids;
+    p.tree.merged = merged_ids; p.tree.M_out = M_out; p.tree.cols = cols;
+    return p;
+}
+
 // Host-side checks shared by the tree entry points; nothing is dereferenced.
 static int check_tree_args(const specee_dims *dm, int G, int N, int Mcap, const specee_half *hidden,
                            const specee_half *gamma, const specee_half *lm_head, const int32_t *ids,
@@ -357,14 +372,25 @@ static int predict_tree_common(const specee_dims *dm, int G, int N, int Mcap, co
     fp.logits = logits; fp.probs = probs; fp.scores = scores; fp.exit_flags = exit_flags;
     fp.parent = parent; fp.path_exit = path_exit;
 
+    const bool whole = G >= kWholeTreeMinTrees && tree_whole_supported(N, dm->K, Mcap);
+    if (!whole && exact_fit && (!workspace || workspace_bytes < lay.total)) return SPECEE_EWORKSPACE;
+
+    // up to a few thousand nodes: every node on its own, which needs no workspace
+    if (tree_nodes_preferred(G * N, N * dm->K, dm->K, dm->H, false)) {
+        PredictParams pp = tree_nodes_params(dm, G, N, Mcap, hidden, gamma, ids, prev_probs, mlp, merged_ids, M_out,
+                                             cols, logits, probs, scores, exit_flags);
+        pp.lm_head = H(lm_head);
+        return launch_tree_nodes(pp, N, parent, path_exit, st) == hipSuccess ? SPECEE_OK : SPECEE_EHIP;
+    }
+
     // enough small trees to occupy the GPU with one workgroup each: a single launch does merge,
     // contraction over all of d, scoring and the path rule, and no partial sums touch memory
-    if (G >= kWholeTreeMinTrees && tree_whole_supported(N, dm->K, Mcap)) {
+    if (whole) {
         gp.ids = ids;
         // fewer trees than the GPU holds workgroups: S workgroups per tree, one d-slice each, and the
-        // last to finish adds the slices up and scores the tree
+        // last to finish adds the slices up and scores the tree (at most three: trees of up to 64 nodes
+        // only come here when there are more than 64 of them)
         int S = kWholeTargetWgs / G;
-        if (S > kWholeMaxSlices) S = kWholeMaxSlices;
         if (S < 1) S = 1;
         int dslice = (((dm->d + S - 1) / S + 127) / 128) * 128;
         S = (dm->d + dslice - 1) / dslice;
@@ -381,7 +407,6 @@ static int predict_tree_common(const specee_dims *dm, int G, int N, int Mcap, co
         return launch_tree_whole(gp, fp, G, st) == hipSuccess ? SPECEE_OK : SPECEE_EHIP;
     }
 
-    if (exact_fit && (!workspace || workspace_bytes < lay.total)) return SPECEE_EWORKSPACE;
     // few trees: split d over many workgroups; merge inside the contraction kernel (one launch less on the
     // latency path) unless that would repeat it too often
     const bool fuse = tree_gemm_can_fuse_merge(N * dm->K) && (long long)G * ts.S <= 64;
@@ -495,6 +520,14 @@ int specee_predict_tree_q4(const specee_dims *dm, int G, int N, int Mcap, const 
     if ((rc = check_q4(dm, qweight, scales, zeros, group))) return rc;
     if ((reinterpret_cast<uintptr_t>(qweight) & 7) != 0) return SPECEE_EALIGN;
     if (!tree_q4_supported(dm->d, N, dm->K, Mcap, group)) return SPECEE_EINVAL;
+    if (tree_nodes_preferred(G * N, N * dm->K, dm->K, dm->H, true)) {
+        PredictParams pp = tree_nodes_params(dm, G, N, Mcap, hidden, gamma, ids, prev_probs, mlp, merged_ids, M_out,
+                                             cols, logits, probs, scores, exit_flags);
+        pp.qweight = qweight; pp.qscales = H(scales); pp.qzeros = H(zeros); pp.group = group;
+        return launch_tree_nodes(pp, N, parent, path_exit, static_cast<hipStream_t>(stream)) == hipSuccess
+                   ? SPECEE_OK
+                   : SPECEE_EHIP;
+    }
     TreeQ4Params tp{};
     tp.d = dm->d; tp.V = dm->V; tp.N = N; tp.K = dm->K; tp.Mcap = Mcap; tp.group = group; tp.eps = dm->eps;
     tp.hidden = H(hidden); tp.gamma = H(gamma); tp.qweight = qweight; tp.qscales = H(scales); tp.qzeros = H(zeros);

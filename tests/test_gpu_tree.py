@@ -553,3 +553,44 @@ def test_c5_large_vocab_tree_and_full_head(sp, oracle):
             u = np.unique(ts[gi]["ids"])
             assert gotb["M"][gi] == len(u) and np.array_equal(gotb["merged"][gi][:len(u)], u)
     oracle.set_threads(1)
+
+
+@pytest.mark.parametrize("d,V,K,H,N,G,Mcap", [
+    (256, 700, 4, 64, 64, 64, 64),     # the most nodes that are scored node by node
+    (256, 700, 4, 64, 64, 65, 64),     # one tree more: two d-slices per tree by ticket
+    (264, 700, 4, 64, 61, 260, 64),    # more trees than CUs, ragged d and N
+    (520, 777, 8, 64, 64, 66, 256),    # wide merged sets, d-slices
+    (256, 777, 8, 64, 64, 130, 256),   # ... one d-slice
+    (200, 300, 3, 100, 64, 128, 64),   # no matrix-core MLP: node by node up to twice as many
+    (200, 300, 3, 100, 64, 129, 64),   # one tree more
+    (384, 900, 1, 64, 1024, 9, 64),    # trees of more than 64 nodes: split contraction with the merge in its prologue
+    (136, 3000, 4, 64, 256, 3, 40),    # four ids per merging thread; one tree overflows its capacity
+    (136, 3000, 4, 64, 257, 3, 40),    # more ids than that: merge kernel and split contraction
+])
+def test_tree_both_sides_of_the_node_by_node_line(sp, oracle, d, V, K, H, N, G, Mcap):
+    rng = np.random.default_rng(d + V + K + N + G)
+    ids = np.empty((G, N, K), np.int32)
+    for g in range(G):
+        width = 50 if (Mcap, g) == (40, 1) else [Mcap, max(K, Mcap - 9), max(K, Mcap // 2), K][g % 4]
+        pool = rng.permutation(V)[:width]
+        ids[g] = pool[rng.integers(0, width, size=(N, K))]
+    parent = np.tile(np.array([-1] + [int(rng.integers(0, n)) for n in range(1, N)], np.int32), (G, 1))
+    t = dict(hidden=rng.standard_normal((G, N, d)).astype(np.float16),
+             gamma=(1 + 0.05 * rng.standard_normal(d)).astype(np.float16),
+             lm_head=(0.05 * rng.standard_normal((V, d))).astype(np.float16), ids=ids, parent=parent,
+             prev_probs=rng.dirichlet(np.ones(K), size=(G, N)).astype(np.float32),
+             W1=(0.1 * rng.standard_normal((H, 3 * K))).astype(np.float16),
+             w2=(0.1 * rng.standard_normal(H)).astype(np.float16), b1=None, b2=None)
+    over = [1] if Mcap == 40 else []
+    got = run_tree(sp, t, dev(t["lm_head"]), Mcap)
+    for g in over:                     # a set that does not fit is reported and refuses the whole tree
+        assert got["M"][g] == 50 and np.array_equal(got["merged"][g], np.unique(ids[g])[:Mcap])
+        assert all(np.isnan(got[k][g]).all() for k in ("logits", "probs", "scores"))
+        assert not got["exit"][g].any() and not got["path_exit"][g].any()
+    keep = [g for g in range(G) if g not in over]
+    t = {k: v[keep] if k in ("hidden", "ids", "parent", "prev_probs") else v for k, v in t.items()}
+    got = {k: v[keep] for k, v in got.items()}
+    oracle.set_threads(8)
+    ref = ref_tree(oracle, t, Mcap)
+    oracle.set_threads(1)
+    check_tree(got, ref, 0.5, f"{G} trees d={d} K={K} N={N} Mcap={Mcap}", min_compared=0.3)

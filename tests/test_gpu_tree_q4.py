@@ -147,3 +147,19 @@ def test_tree_q4_argument_errors(sp):
     with pytest.raises(sp.SpeceeError) as ei:
         run(sp, big, 64)
     assert ei.value.code == -1
+
+
+@pytest.mark.parametrize("d,V,K,H,N,G,Mcap", [
+    (128, 300, 4, 64, 64, 192, 64),   # the most nodes that are scored node by node
+    (128, 300, 4, 64, 64, 193, 64),   # one tree more: one workgroup per tree
+    (128, 300, 8, 64, 64, 48, 128),   # K = 8: fewer
+    (128, 300, 8, 64, 64, 49, 128),
+    (128, 300, 3, 100, 64, 96, 64),   # no matrix-core MLP
+    (160, 300, 3, 100, 64, 97, 64),
+])
+def test_tree_q4_both_sides_of_the_node_by_node_line(sp, oracle, d, V, K, H, N, G, Mcap):
+    t = make(d + N + K + G, d, V, K, H, N, G, 32, Mcap)
+    oracle.set_threads(8)
+    r = ref(oracle, t, Mcap)
+    oracle.set_threads(1)
+    check_tree(run(sp, t, Mcap), r, 0.5, f"tree_q4 d={d} K={K} N={N} G={G}", min_compared=0.3)
