@@ -16,6 +16,7 @@ from pathlib import Path
 PKG = Path(__file__).resolve().parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libspecee.so"
+BINDING = PKG / "_binding.so"
 OBJ = PKG / "_build"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -53,7 +54,29 @@ def build(verbose: bool = True) -> Path:
     os.replace(tmp, LIB)
     if verbose:
         print(f"built {LIB} from {len(srcs)} sources")
+    build_binding()
     return LIB
+
+
+def build_binding() -> Path:
+    """The Python entry points (csrc/python/binding.cpp), linked against the library beside them."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    tmp = BINDING.with_suffix(f".tmp{os.getpid()}.so")
+    inc = [sysconfig.get_paths()["include"], *cpp_extension.include_paths(), "/opt/rocm/include"]
+    torch_lib = str(Path(torch.__file__).parent / "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[f"-isystem{d}" for d in inc], str(CSRC / "python" / "binding.cpp"), "-o", str(tmp),
+           f"-L{PKG}", "-l:libspecee.so", f"-L{torch_lib}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"the compiler failed on binding.cpp:\n{r.stderr}")
+    os.replace(tmp, BINDING)
+    return BINDING
 
 
 if __name__ == "__main__":

@@ -1,4 +1,5 @@
-"""Python binding of libspecee.so (include/specee.h): argument marshalling only.
+"""Python binding of libspecee.so (include/specee.h): argument marshalling only, the decode loop's calls natively
+(_binding.so, csrc/python/binding.cpp) and the rest through ctypes.
 
 Tensors are torch tensors on the GPU (PyTorch supplies device memory and
 streams, nothing else); every computation happens inside the HIP library.  A
@@ -14,6 +15,7 @@ import torch
 _PKG = Path(__file__).resolve().parent
 LIB_PATH = _PKG / "libspecee.so"
 _lib = None
+_binding = None
 
 OP_PREDICT, OP_PREDICT_SWEEP, OP_PREDICT_TREE, OP_LM_HEAD, OP_VERIFY, OP_LAYER_LOOP, OP_VERIFY_Q4, \
     OP_PREDICT_TREE_Q4 = range(8)
@@ -56,6 +58,20 @@ def lib():
     return _lib
 
 
+def _call():
+    """The calls of a decode loop, marshalled natively (built beside the library, the same C entry points): a
+    specee_predict through ctypes took the host 11.4 us, which is what an eager call cost; it is 4.6 us now."""
+    global _binding
+    if _binding is None:
+        lib()
+        path = _PKG / "_binding.so"
+        if not path.exists():
+            raise FileNotFoundError(f"{path} is missing: build it with `python -m paper_2504_08850_amd.build`")
+        from . import _binding as native
+        _binding = native
+    return _binding
+
+
 def _ptr(t, dtype=None):
     if t is None:
         return C.c_void_p(None)
@@ -70,13 +86,8 @@ def _stream(stream):
     return C.c_void_p(s.cuda_stream)
 
 
-def _mlp(W1, w2, b1, b2):
-    f16 = torch.float16
-    return Mlp(_ptr(W1, f16).value, _ptr(b1, f16).value, _ptr(w2, f16).value, _ptr(b2, f16).value)
-
-
-def _dims(d, V, K, H, eps, threshold):
-    return Dims(int(d), int(V), int(K), int(H), float(eps), float(threshold))
+def _handle(stream):
+    return None if stream is None else stream.cuda_stream
 
 
 def workspace_bytes(op, dims: Dims, n, Mcap=0) -> int:
@@ -87,10 +98,10 @@ def workspace_bytes(op, dims: Dims, n, Mcap=0) -> int:
 
 
 def _workspace(op, dims, n, Mcap, workspace, device):
-    need = workspace_bytes(op, dims, n, Mcap)
     if workspace is None:
+        need = workspace_bytes(op, Dims(*dims), n, Mcap)
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=device)
-    return workspace, C.c_size_t(workspace.numel() * workspace.element_size())
+    return workspace, workspace.numel() * workspace.element_size()
 
 
 def predict(hidden, gamma, lm_head, ids, prev_probs, W1, w2, b1=None, b2=None, eps=1e-5, threshold=0.5,
@@ -107,13 +118,10 @@ def predict(hidden, gamma, lm_head, ids, prev_probs, W1, w2, b1=None, b2=None, e
                    probs=torch.empty((B, K), dtype=torch.float32, device=dev),
                    scores=torch.empty((B,), dtype=torch.float32, device=dev),
                    exit=torch.empty((B,), dtype=torch.int32, device=dev))
-    dims = _dims(d, V, K, H, eps, threshold)
-    mlp = _mlp(W1, w2, b1, b2)
-    f16 = torch.float16
-    rc = lib().specee_predict(C.byref(dims), C.c_int(B), _ptr(hidden, f16), _ptr(gamma, f16), _ptr(lm_head, f16),
-                              _ptr(ids, torch.int32), _ptr(prev_probs, torch.float32), C.byref(mlp),
-                              _ptr(done, torch.int32), _ptr(out["logits"]), _ptr(out["probs"]), _ptr(out["scores"]), _ptr(out["exit"]),
-                              _stream(stream))
+    dims = (d, V, K, H, eps, threshold)
+    mlp = (W1, b1, w2, b2)
+    rc = _call().specee_predict(dims, B, hidden, gamma, lm_head, ids, prev_probs, mlp, done, out["logits"],
+                                out["probs"], out["scores"], out["exit"], _handle(stream))
     if rc:
         raise SpeceeError("specee_predict", rc)
     return out
@@ -135,14 +143,10 @@ def predict_q4(hidden, gamma, qweight, scales, zeros, group, ids, prev_probs, W1
                    probs=torch.empty((B, K), dtype=torch.float32, device=dev),
                    scores=torch.empty((B,), dtype=torch.float32, device=dev),
                    exit=torch.empty((B,), dtype=torch.int32, device=dev))
-    dims = _dims(d, V, K, H, eps, threshold)
-    mlp = _mlp(W1, w2, b1, b2)
-    f16 = torch.float16
-    rc = lib().specee_predict_q4(C.byref(dims), C.c_int(B), _ptr(hidden, f16), _ptr(gamma, f16),
-                                 _ptr(qweight, torch.int32), _ptr(scales, f16), _ptr(zeros, f16), C.c_int(group),
-                                 _ptr(ids, torch.int32), _ptr(prev_probs, torch.float32), C.byref(mlp),
-                                 _ptr(done, torch.int32), _ptr(out["logits"]), _ptr(out["probs"]),
-                                 _ptr(out["scores"]), _ptr(out["exit"]), _stream(stream))
+    dims = (d, V, K, H, eps, threshold)
+    mlp = (W1, b1, w2, b2)
+    rc = _call().specee_predict_q4(dims, B, hidden, gamma, qweight, scales, zeros, group, ids, prev_probs, mlp, done,
+                                   out["logits"], out["probs"], out["scores"], out["exit"], _handle(stream))
     if rc:
         raise SpeceeError("specee_predict_q4", rc)
     return out
@@ -162,14 +166,10 @@ def predict_sweep(hidden, gamma, lm_head, ids, W1, w2, b1=None, b2=None, prev0=N
                    scores=torch.empty((L, B), dtype=torch.float32, device=dev),
                    exit=torch.empty((L, B), dtype=torch.int32, device=dev),
                    first_exit=torch.empty((B,), dtype=torch.int32, device=dev))
-    dims = _dims(d, V, K, H, eps, threshold)
-    mlp = _mlp(W1, w2, b1, b2)
-    f16 = torch.float16
-    rc = lib().specee_predict_sweep(C.byref(dims), C.c_int(L), C.c_int(B), _ptr(hidden, f16), _ptr(gamma, f16),
-                                    _ptr(lm_head, f16), _ptr(ids, torch.int32), _ptr(prev0, torch.float32),
-                                    C.byref(mlp), _ptr(active, torch.int32), _ptr(out["logits"]),
-                                    _ptr(out["probs"]), _ptr(out["scores"]), _ptr(out["exit"]),
-                                    _ptr(out["first_exit"]), _stream(stream))
+    dims = (d, V, K, H, eps, threshold)
+    mlp = (W1, b1, w2, b2)
+    rc = _call().specee_predict_sweep(dims, L, B, hidden, gamma, lm_head, ids, prev0, mlp, active, out["logits"],
+                                      out["probs"], out["scores"], out["exit"], out["first_exit"], _handle(stream))
     if rc:
         raise SpeceeError("specee_predict_sweep", rc)
     return out
@@ -190,16 +190,13 @@ def layer_loop(hidden, gamma, lm_head, ids, W1, w2, b1=None, b2=None, prev0=None
                    ver_token=torch.empty((L, B), dtype=i32, device=dev), hit=torch.empty((L, B), dtype=i32, device=dev),
                    exit_layer=torch.empty((B,), dtype=i32, device=dev), token=torch.empty((B,), dtype=i32, device=dev),
                    status=torch.empty((B,), dtype=i32, device=dev))
-    dims = _dims(d, V, K, H, eps, threshold)
-    mlp = _mlp(W1, w2, b1, b2)
+    dims = (d, V, K, H, eps, threshold)
     workspace, wbytes = _workspace(OP_LAYER_LOOP, dims, B, 0, workspace, dev)
-    f16 = torch.float16
-    rc = lib().specee_layer_loop(C.byref(dims), C.c_int(L), C.c_int(B), _ptr(hidden, f16), _ptr(gamma, f16),
-                                 _ptr(lm_head, f16), _ptr(ids, torch.int32), _ptr(prev0, torch.float32), C.byref(mlp),
-                                 _ptr(active, torch.int32), _ptr(out["logits"]), _ptr(out["probs"]),
-                                 _ptr(out["scores"]), _ptr(out["exit"]), _ptr(out["ver_token"]), _ptr(out["hit"]),
-                                 _ptr(out["exit_layer"]), _ptr(out["token"]), _ptr(out["status"]),
-                                 C.c_longlong(int(spin_limit)), _ptr(workspace), wbytes, _stream(stream))
+    mlp = (W1, b1, w2, b2)
+    rc = _call().specee_layer_loop(dims, L, B, hidden, gamma, lm_head, ids, prev0, mlp, active, out["logits"],
+                                   out["probs"], out["scores"], out["exit"], out["ver_token"], out["hit"],
+                                   out["exit_layer"], out["token"], out["status"], int(spin_limit), workspace, wbytes,
+                                   _handle(stream))
     if rc:
         raise SpeceeError("specee_layer_loop", rc)
     out["_workspace"] = workspace
@@ -222,17 +219,13 @@ def layer_loop_q4(hidden, gamma, qweight, scales, zeros, group, ids, W1, w2, b1=
                    ver_token=torch.empty((L, B), dtype=i32, device=dev), hit=torch.empty((L, B), dtype=i32, device=dev),
                    exit_layer=torch.empty((B,), dtype=i32, device=dev), token=torch.empty((B,), dtype=i32, device=dev),
                    status=torch.empty((B,), dtype=i32, device=dev))
-    dims = _dims(d, V, K, H, eps, threshold)
-    mlp = _mlp(W1, w2, b1, b2)
+    dims = (d, V, K, H, eps, threshold)
     workspace, wbytes = _workspace(OP_LAYER_LOOP, dims, B, 0, workspace, dev)
-    f16 = torch.float16
-    rc = lib().specee_layer_loop_q4(C.byref(dims), C.c_int(L), C.c_int(B), _ptr(hidden, f16), _ptr(gamma, f16),
-                                    _ptr(qweight, torch.int32), _ptr(scales, f16), _ptr(zeros, f16), C.c_int(group),
-                                    _ptr(ids, torch.int32), _ptr(prev0, torch.float32), C.byref(mlp),
-                                    _ptr(active, torch.int32), _ptr(out["logits"]), _ptr(out["probs"]),
-                                    _ptr(out["scores"]), _ptr(out["exit"]), _ptr(out["ver_token"]), _ptr(out["hit"]),
-                                    _ptr(out["exit_layer"]), _ptr(out["token"]), _ptr(out["status"]),
-                                    C.c_longlong(int(spin_limit)), _ptr(workspace), wbytes, _stream(stream))
+    mlp = (W1, b1, w2, b2)
+    rc = _call().specee_layer_loop_q4(dims, L, B, hidden, gamma, qweight, scales, zeros, group, ids, prev0, mlp,
+                                      active, out["logits"], out["probs"], out["scores"], out["exit"],
+                                      out["ver_token"], out["hit"], out["exit_layer"], out["token"], out["status"],
+                                      int(spin_limit), workspace, wbytes, _handle(stream))
     if rc:
         raise SpeceeError("specee_layer_loop_q4", rc)
     out["_workspace"] = workspace
@@ -262,16 +255,12 @@ def predict_tree(hidden, gamma, lm_head, ids, prev_probs, W1, w2, b1=None, b2=No
                    scores=torch.empty((G, N), dtype=f32, device=dev),
                    exit=torch.empty((G, N), dtype=i32, device=dev),
                    path_exit=torch.empty((G, N), dtype=i32, device=dev) if want_path else None)
-    dims = _dims(d, V, K, H, eps, threshold)
-    mlp = _mlp(W1, w2, b1, b2)
+    dims = (d, V, K, H, eps, threshold)
     workspace, wbytes = _workspace(OP_PREDICT_TREE, dims, G * N, Mcap, workspace, dev)
-    f16 = torch.float16
-    rc = lib().specee_predict_tree(C.byref(dims), C.c_int(G), C.c_int(N), C.c_int(Mcap), _ptr(hidden, f16),
-                                   _ptr(gamma, f16), _ptr(lm_head, f16), _ptr(ids, torch.int32),
-                                   _ptr(parent, torch.int32), _ptr(prev_probs, torch.float32), C.byref(mlp),
-                                   _ptr(out["merged"]), _ptr(out["M"]), _ptr(out["cols"]), _ptr(out["logits"]),
-                                   _ptr(out["probs"]), _ptr(out["scores"]), _ptr(out["exit"]),
-                                   _ptr(out.get("path_exit")), _ptr(workspace), wbytes, _stream(stream))
+    mlp = (W1, b1, w2, b2)
+    rc = _call().specee_predict_tree(dims, G, N, Mcap, hidden, gamma, lm_head, ids, parent, prev_probs, mlp,
+                                     out["merged"], out["M"], out["cols"], out["logits"], out["probs"], out["scores"],
+                                     out["exit"], out.get("path_exit"), workspace, wbytes, _handle(stream))
     if rc:
         raise SpeceeError("specee_predict_tree", rc)
     out["_workspace"] = workspace
@@ -289,15 +278,11 @@ def predict_tree_static(hidden, gamma, lm_head, ids, prev_probs, W1, w2, b1=None
     V = lm_head.shape[0]
     K = ids.shape[2]
     H = w2.shape[0]
-    dims = _dims(d, V, K, H, eps, threshold)
-    mlp = _mlp(W1, w2, b1, b2)
-    f16 = torch.float16
-    rc = lib().specee_predict_tree_static(C.byref(dims), C.c_int(G), C.c_int(N), C.c_int(Mcap), _ptr(hidden, f16),
-                                          _ptr(gamma, f16), _ptr(lm_head, f16), _ptr(ids, torch.int32),
-                                          _ptr(parent, torch.int32), _ptr(prev_probs, torch.float32), C.byref(mlp),
-                                          _ptr(out["merged"]), _ptr(out["M"]), _ptr(out["cols"]),
-                                          _ptr(out["logits"]), _ptr(out["probs"]), _ptr(out["scores"]),
-                                          _ptr(out["exit"]), _ptr(out.get("path_exit")), _stream(stream))
+    dims = (d, V, K, H, eps, threshold)
+    mlp = (W1, b1, w2, b2)
+    rc = _call().specee_predict_tree_static(dims, G, N, Mcap, hidden, gamma, lm_head, ids, parent, prev_probs, mlp,
+                                            out["merged"], out["M"], out["cols"], out["logits"], out["probs"],
+                                            out["scores"], out["exit"], out.get("path_exit"), _handle(stream))
     if rc:
         raise SpeceeError("specee_predict_tree_static", rc)
     return out
@@ -310,11 +295,10 @@ def lm_head_gemv(hidden, gamma, lm_head, eps=1e-5, out=None, workspace=None, str
     dev = hidden.device
     if out is None:
         out = torch.empty((N, V), dtype=torch.float32, device=dev)
-    dims = _dims(d, V, 1, 1, eps, 0.5)
+    dims = (d, V, 1, 1, eps, 0.5)
     workspace, wbytes = _workspace(OP_LM_HEAD, dims, N, 0, workspace, dev)
-    f16 = torch.float16
-    rc = lib().lm_head_gemv(C.byref(dims), C.c_int(N), _ptr(hidden, f16), _ptr(gamma, f16), _ptr(lm_head, f16),
-                            _ptr(out, torch.float32), _ptr(workspace), wbytes, _stream(stream))
+    assert out.dtype == torch.float32, out.dtype
+    rc = _call().lm_head_gemv(dims, N, hidden, gamma, lm_head, out, workspace, wbytes, _handle(stream))
     if rc:
         raise SpeceeError("lm_head_gemv", rc)
     return out
@@ -332,14 +316,11 @@ def verify(hidden, gamma, lm_head, ids, gate=None, eps=1e-5, out=None, workspace
         out = dict(token=torch.empty((N,), dtype=torch.int32, device=dev),
                    max_logit=torch.empty((N,), dtype=torch.float32, device=dev),
                    hit=torch.empty((N,), dtype=torch.int32, device=dev))
-    dims = _dims(d, V, K, 1, eps, 0.5)
+    dims = (d, V, K, 1, eps, 0.5)
     workspace, wbytes = _workspace(OP_VERIFY, dims, N, 0, workspace, dev)
-    f16 = torch.float16
-    rc = lib().specee_verify(C.byref(dims), C.c_int(N), _ptr(hidden, f16), _ptr(gamma, f16), _ptr(lm_head, f16),
-                             _ptr(ids, torch.int32), _ptr(gate, torch.int32), _ptr(done, torch.int32),
-                             _ptr(out["token"]),
-                             _ptr(out["max_logit"]), _ptr(out["hit"]),
-                             _ptr(workspace), wbytes, _stream(stream))
+    assert done is None or done.dtype == torch.int32, done.dtype
+    rc = _call().specee_verify(dims, N, hidden, gamma, lm_head, ids, gate, done, out["token"], out["max_logit"],
+                               out["hit"], workspace, wbytes, _handle(stream))
     if rc:
         raise SpeceeError("specee_verify", rc)
     return out
@@ -349,20 +330,18 @@ def _q4_args(qweight, scales, zeros, group, d):
     V = qweight.shape[0]
     assert qweight.shape == (V, d // 8) and qweight.dtype == torch.int32, "codes travel as int32 words"
     assert scales.shape == (V, d // group) and zeros.shape == scales.shape
-    f16 = torch.float16
-    return V, (_ptr(qweight, torch.int32), _ptr(scales, f16), _ptr(zeros, f16), C.c_int(group))
+    return V, (qweight, scales, zeros, group)
 
 
 def lm_head_gemv_q4(hidden, gamma, qweight, scales, zeros, group, eps=1e-5, out=None, stream=None):
     """lm_head_gemv_q4: out [N][V] against the 4-bit group-quantised head."""
     N, d = hidden.shape
-    V, q = _q4_args(qweight, scales, zeros, group, d)
+    V, head = _q4_args(qweight, scales, zeros, group, d)
     if out is None:
         out = torch.empty((N, V), dtype=torch.float32, device=hidden.device)
-    dims = _dims(d, V, 1, 1, eps, 0.5)
-    f16 = torch.float16
-    rc = lib().lm_head_gemv_q4(C.byref(dims), C.c_int(N), _ptr(hidden, f16), _ptr(gamma, f16), *q,
-                               _ptr(out, torch.float32), _stream(stream))
+    dims = (d, V, 1, 1, eps, 0.5)
+    assert out.dtype == torch.float32, out.dtype
+    rc = _call().lm_head_gemv_q4(dims, N, hidden, gamma, *head, out, _handle(stream))
     if rc:
         raise SpeceeError("lm_head_gemv_q4", rc)
     return out
@@ -372,20 +351,18 @@ def verify_q4(hidden, gamma, qweight, scales, zeros, group, ids, gate=None, eps=
               stream=None, done=None):
     """specee_verify_q4: specee_verify against the 4-bit group-quantised head."""
     N, d = hidden.shape
-    V, q = _q4_args(qweight, scales, zeros, group, d)
+    V, head = _q4_args(qweight, scales, zeros, group, d)
     K = ids.shape[1]
     dev = hidden.device
     if out is None:
         out = dict(token=torch.empty((N,), dtype=torch.int32, device=dev),
                    max_logit=torch.empty((N,), dtype=torch.float32, device=dev),
                    hit=torch.empty((N,), dtype=torch.int32, device=dev))
-    dims = _dims(d, V, K, 1, eps, 0.5)
+    dims = (d, V, K, 1, eps, 0.5)
     workspace, wbytes = _workspace(OP_VERIFY_Q4, dims, N, 0, workspace, dev)
-    f16 = torch.float16
-    rc = lib().specee_verify_q4(C.byref(dims), C.c_int(N), _ptr(hidden, f16), _ptr(gamma, f16), *q,
-                                _ptr(ids, torch.int32), _ptr(gate, torch.int32), _ptr(done, torch.int32),
-                                _ptr(out["token"]), _ptr(out["max_logit"]), _ptr(out["hit"]), _ptr(workspace), wbytes,
-                                _stream(stream))
+    assert done is None or done.dtype == torch.int32, done.dtype
+    rc = _call().specee_verify_q4(dims, N, hidden, gamma, *head, ids, gate, done, out["token"], out["max_logit"],
+                                  out["hit"], workspace, wbytes, _handle(stream))
     if rc:
         raise SpeceeError("specee_verify_q4", rc)
     return out
@@ -399,7 +376,7 @@ def predict_tree_q4(hidden, gamma, qweight, scales, zeros, group, ids, prev_prob
         hidden, ids, prev_probs = hidden[None], ids[None], prev_probs[None]
         parent = None if parent is None else parent[None]
     G, N, d = hidden.shape
-    V, q = _q4_args(qweight, scales, zeros, group, d)
+    V, head = _q4_args(qweight, scales, zeros, group, d)
     K = ids.shape[2]
     H = w2.shape[0]
     dev = hidden.device
@@ -412,15 +389,11 @@ def predict_tree_q4(hidden, gamma, qweight, scales, zeros, group, ids, prev_prob
                    scores=torch.empty((G, N), dtype=f32, device=dev),
                    exit=torch.empty((G, N), dtype=i32, device=dev),
                    path_exit=torch.empty((G, N), dtype=i32, device=dev) if parent is not None else None)
-    dims = _dims(d, V, K, H, eps, threshold)
-    mlp = _mlp(W1, w2, b1, b2)
-    f16 = torch.float16
-    rc = lib().specee_predict_tree_q4(C.byref(dims), C.c_int(G), C.c_int(N), C.c_int(Mcap), _ptr(hidden, f16),
-                                      _ptr(gamma, f16), *q, _ptr(ids, torch.int32), _ptr(parent, torch.int32),
-                                      _ptr(prev_probs, torch.float32), C.byref(mlp), _ptr(out["merged"]),
-                                      _ptr(out["M"]), _ptr(out["cols"]), _ptr(out["logits"]), _ptr(out["probs"]),
-                                      _ptr(out["scores"]), _ptr(out["exit"]), _ptr(out.get("path_exit")),
-                                      _stream(stream))
+    dims = (d, V, K, H, eps, threshold)
+    mlp = (W1, b1, w2, b2)
+    rc = _call().specee_predict_tree_q4(dims, G, N, Mcap, hidden, gamma, *head, ids, parent, prev_probs, mlp,
+                                        out["merged"], out["M"], out["cols"], out["logits"], out["probs"],
+                                        out["scores"], out["exit"], out.get("path_exit"), _handle(stream))
     if rc:
         raise SpeceeError("specee_predict_tree_q4", rc)
     if single:

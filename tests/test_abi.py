@@ -148,3 +148,21 @@ def test_scheduler_matches_oracle(sp, oracle):
         s.push(L)
     with pytest.raises(sp.SpeceeError):
         sp.Scheduler(1000)
+
+
+def test_native_marshalling_refuses_what_the_library_must_not_see(sp):
+    import torch
+    call = sp._call()
+    none = (None, None, None, None)
+    empty = ((8, 1, 1, 1, 0.0, 0.0), 0, None, None, None, None, None, none, None, None, None, None, None)
+    assert call.specee_predict(*empty, 0) == 0                       # an empty batch reads nothing
+    assert call.specee_predict((7, 1, 1, 1, 0.0, 0.0), *empty[1:], 0) == -1
+    host = torch.zeros((1, 8), dtype=torch.float16)
+    with pytest.raises(AssertionError):                              # not on the GPU
+        call.specee_predict(empty[0], 1, host, *empty[3:], 0)
+    with pytest.raises(TypeError):                                   # not a tensor
+        call.specee_predict(empty[0], 1, 5, *empty[3:], 0)
+    with pytest.raises(TypeError):                                   # a missing argument
+        call.specee_predict(*empty)
+    with pytest.raises(TypeError):                                   # dimensions that are no tuple of six
+        call.specee_predict((8, 1), *empty[1:], 0)
