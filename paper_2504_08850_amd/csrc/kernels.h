@@ -40,7 +40,7 @@ struct PredictParams {
 };
 
 // Trees scored node by node (B = G * N tokens): predictor and merge in one launch, then overflow and path rule
-bool tree_nodes_preferred(int total_nodes, int n_ids, int K, int H, bool q4);
+bool tree_nodes_preferred(int total_nodes, int n_ids, int d, int K, int H, int Mcap, bool q4);
 hipError_t launch_tree_nodes(const PredictParams &p, int N, const int32_t *parent, int32_t *path_exit, hipStream_t s);
 
 hipError_t launch_predict(const PredictParams &p, hipStream_t s);

@@ -616,6 +616,23 @@ __global__ void first_exit_kernel(const int32_t *exit_flags, int L, int B, int32
 }
 
 constexpr int kBatchMinTokens = 1024;  // tokens per launch from which the throughput shapes are used
+// The same on quantised rows, whose workgroups of 128 threads pay earlier (d = 4096, K = 4: 128 tokens 4.2 us either
+// way, 512 tokens 5.9 -> 5.5, 900 tokens 8.4 -> 5.8 us; d = 5120: 128 tokens 5.0 -> 4.5, 900 tokens 10.8 -> 8.2 us).
+constexpr int kQ4BatchMinTokens = 128;
+
+// A tree's ids are merged by one workgroup of the launch, at most kMergePerThread of them per thread.
+template <bool TREE>
+static bool merge_fits(const PredictParams &p, int threads) {
+    return !TREE || p.tree.n <= kMergePerThread * threads;
+}
+
+// K values that are compiled in.  Against the generic form (rows of W1 read where they are used, tests of k < K):
+// K = 3, 8000 tokens 51.2 -> 38.3 us, one token 4.3 -> 3.3 us; K = 5, 8000 tokens 103 -> 55 us, one token 5.9 -> 3.8 us;
+// quantised rows, 8000 tokens: K = 3 59.5 -> 27.3, K = 5 124 -> 35.4, K = 8 (now with the throughput shapes of K = 4)
+// 77.5 -> 41.5 us.
+static bool predict_exact(int K) {
+    return K == 3 || K == 4 || K == 5 || K == 8;
+}
 
 template <int KC, bool SWEEP, bool EXACT, bool TREE>
 static hipError_t launch_vpt(const PredictParams &p, hipStream_t s) {
@@ -623,12 +640,19 @@ static hipError_t launch_vpt(const PredictParams &p, hipStream_t s) {
     const size_t lds = TREE ? (size_t)merge_lds_ints(p.tree.n) * sizeof(int32_t) : 0;
     const int nv = p.d >> 3;
     if constexpr (!SWEEP && EXACT && KC <= 8) {
-        // throughput shape: K in {4, 8}, many tokens, rows of at most 4 * 256 vectors (d <= 8192)
+        // throughput shape: K known at compile time, many tokens, rows of at most 4 * 256 vectors (d <= 8192)
         // (also for a few tokens when a row is exactly two vectors per thread, d = 4096: four wavefronts
         // instead of eight start and meet sooner -- 3.36 -> 3.32 us per call, 3.89 -> 3.47 us with the rows in HBM;
         // at d = 5120, where the last vectors are masked, the 512-thread shape stays ahead)
+        if constexpr (KC <= 5) {
+            // rows of at most two vectors per thread of 128 (d = 2048, K = 4: B=2000 9.9 -> 8.2 us, B=8000 29.3 -> 26.6)
+            if (p.B >= kBatchMinTokens && nv <= 2 * 128 && merge_fits<TREE>(p, 128)) {
+                hipLaunchKernelGGL((predict_kernel<KC, 2, false, true, 128, 4, TREE>), grid, dim3(128), lds, s, p);
+                return hipGetLastError();
+            }
+        }
         const bool small_fit = KC == 4 && nv == 2 * 256;
-        if ((p.B >= kBatchMinTokens || small_fit) && nv <= 2 * 256 * (KC == 4 ? 2 : 1)) {
+        if ((p.B >= kBatchMinTokens || small_fit) && nv <= 2 * 256 * (KC <= 4 ? 2 : 1)) {
             const dim3 blk(256);
             if (nv <= 2 * 256)
                 hipLaunchKernelGGL((predict_kernel<KC, 2, false, true, 256, 2, TREE>), grid, blk, lds, s, p);
@@ -651,6 +675,8 @@ template <bool SWEEP, bool TREE>
 static hipError_t launch_kc(const PredictParams &p, hipStream_t s) {
     if (p.K == 4) return launch_vpt<4, SWEEP, true, TREE>(p, s);
     if (p.K == 8) return launch_vpt<8, SWEEP, true, TREE>(p, s);
+    if (!SWEEP && p.K == 3) return launch_vpt<3, false, true, TREE>(p, s);
+    if (!SWEEP && p.K == 5) return launch_vpt<5, false, true, TREE>(p, s);
     if (p.K < 4) return launch_vpt<4, SWEEP, false, TREE>(p, s);
     if (p.K < 8) return launch_vpt<8, SWEEP, false, TREE>(p, s);
     return launch_vpt<16, SWEEP, false, TREE>(p, s);
@@ -665,27 +691,27 @@ static hipError_t launch_q4_kc(const PredictParams &p, hipStream_t s) {
     const dim3 grid(p.B + (TREE ? p.tree.G : 0)), block(kPredictThreads);
     const size_t lds = TREE ? (size_t)merge_lds_ints(p.tree.n) * sizeof(int32_t) : 0;
     const int nv = p.d >> 3;
-    if constexpr (EXACT && KC == 4) {
+    if constexpr (EXACT && KC <= 8) {
         // throughput shape (see predict_kernel): a quantised row is a quarter of the bytes, so the fixed
         // cost per workgroup weighs more and small workgroups pay: 128 threads per token, four words per
         // row and thread, four hidden units per thread (B=8000 at d=4096: 51 -> 37 us)
         // chunks of 32 elements per thread when the format allows it (group % 32 == 0, rows 16-byte aligned):
         // B=8000 at d=4096: 37 -> 29 us, at d=8192: 71 -> 58 us
         const bool wide_ok = p.group % 32 == 0 && p.d % 32 == 0 && (reinterpret_cast<uintptr_t>(p.qweight) & 15) == 0;
-        if (wide_ok && p.B >= kBatchMinTokens && p.d <= 32 * 128) {
-            hipLaunchKernelGGL((predict_q4_wide_kernel<4, 128, 1, 4, TREE>), grid, dim3(128), lds, s, p);
+        if (wide_ok && p.B >= kQ4BatchMinTokens && p.d <= 32 * 128 && merge_fits<TREE>(p, 128)) {
+            hipLaunchKernelGGL((predict_q4_wide_kernel<KC, 128, 1, 4, TREE>), grid, dim3(128), lds, s, p);
             return hipGetLastError();
         }
-        if (wide_ok && p.B >= kBatchMinTokens && p.d <= 32 * 256) {
-            hipLaunchKernelGGL((predict_q4_wide_kernel<4, 256, 1, 2, TREE>), grid, dim3(256), lds, s, p);
+        if (wide_ok && p.B >= kQ4BatchMinTokens && p.d <= 32 * 256) {
+            hipLaunchKernelGGL((predict_q4_wide_kernel<KC, 256, 1, 2, TREE>), grid, dim3(256), lds, s, p);
             return hipGetLastError();
         }
-        if (p.B >= kBatchMinTokens && nv <= 4 * 128) {
-            hipLaunchKernelGGL((predict_q4_kernel<4, 4, true, 128, 4, TREE>), grid, dim3(128), lds, s, p);
+        if (p.B >= kQ4BatchMinTokens && nv <= 4 * 128 && merge_fits<TREE>(p, 128)) {
+            hipLaunchKernelGGL((predict_q4_kernel<KC, 4, true, 128, 4, TREE>), grid, dim3(128), lds, s, p);
             return hipGetLastError();
         }
-        if (p.B >= kBatchMinTokens && nv <= 4 * 256) {
-            hipLaunchKernelGGL((predict_q4_kernel<4, 4, true, 256, 2, TREE>), grid, dim3(256), lds, s, p);
+        if (p.B >= kQ4BatchMinTokens && nv <= 4 * 256) {
+            hipLaunchKernelGGL((predict_q4_kernel<KC, 4, true, 256, 2, TREE>), grid, dim3(256), lds, s, p);
             return hipGetLastError();
         }
     }
@@ -700,6 +726,8 @@ template <bool TREE>
 static hipError_t launch_q4_any(const PredictParams &p, hipStream_t s) {
     if (p.K == 4) return launch_q4_kc<4, true, TREE>(p, s);
     if (p.K == 8) return launch_q4_kc<8, true, TREE>(p, s);
+    if (p.K == 3) return launch_q4_kc<3, true, TREE>(p, s);
+    if (p.K == 5) return launch_q4_kc<5, true, TREE>(p, s);
     if (p.K < 4) return launch_q4_kc<4, false, TREE>(p, s);
     if (p.K < 8) return launch_q4_kc<8, false, TREE>(p, s);
     return launch_q4_kc<16, false, TREE>(p, s);
@@ -742,19 +770,20 @@ __global__ __launch_bounds__(kTreeTailThreads) void tree_tail_kernel(PredictPara
 // merges the ids beside them.  Against one workgroup per tree (or the split contraction of a few trees) this gives up
 // reading a shared row once per tree -- the caches serve the repeats -- and gains a chain of two memory trips per
 // node on every CU instead of merge -> contraction -> scoring in series.
-// Where the line lies (60-node trees, d = 4096, K = 4 unless given, node by node without the tail kernel's 2 us
-// against the tree kernels): fp16 1 tree 3.8 / 15.2 us, 16 trees 6.9 / 20.5, 64 trees 18.9 / 23.6, 96 trees
-// 26.9 / 27.8, 128 trees 33.7 / 31.0; d = 8192, K = 8, 64 nodes: 32 trees 30.4 / 48.2, 64 trees 56.1 / 63.2;
-// K = 5, d = 5120 (no matrix-core MLP in the tree kernel), 50 nodes: 64 trees 50 / 108, 128 trees 92 / 115.
-// Quantised rows: 16 trees 8.6 / 44.4 us, 128 trees 25.6 / 46.1, 256 trees 45.7 / 50.3; K = 8, d = 5120, 50 nodes:
-// 64 trees 46.3 / 54.3, 128 trees 82.6 / 54.9; K = 3, d = 4608, 40 nodes: 128 trees 56.9 / 84.4.
-// n ids of a tree: at most four per thread of the workgroup that merges them (256 threads; the 128-thread shape is
-// only taken by K = 4 on quantised rows, where a tree has at most 64 nodes).
-bool tree_nodes_preferred(int total_nodes, int n_ids, int K, int H, bool q4) {
-    if (n_ids > 4 * 256) return false;
-    const bool mfma = mlp_mfma_ok(K, H);
-    if (q4) return total_nodes <= (K == 4 && mfma ? 12288 : mfma ? 3072 : 6144);
-    return total_nodes <= (mfma ? 4096 : 8192);
+// Where the line lies (whole call against the tree kernels, 60 or 64 nodes, d = 4096, K = 4 unless given):
+// fp16, 1 tree 5.8 / 15.2 us, 16 trees 9.4 / 20.5, 48 trees 19.2 / 23.0, 64 trees 24.4 / 24.0; d = 5120, 48 trees
+// 23.4 / 24.1, 64 trees 28.3 / 26.2; K = 8, 48 trees 26.8 / 27.7, 64 trees 33.3 / 28.7 -- the bytes gathered
+// decide, nodes * (K + 1) * d.  Sets wider than 128 rows cost the tree kernel twice as much (d = 8192, K = 8:
+// 64 trees 60.1 / 63.2), and K = 3 and 5, which it scores without the matrix cores, four times (K = 5, d = 5120:
+// 190 trees 87.5 / 145).  Quantised rows: 1 tree 6.2 / 44.2, 16 trees 7.1 / 43.2, 192 trees 40.7 / 47.3; K = 8,
+// d = 5120, 80 trees 47.8 / 55.1; K = 3, 256 trees 54.2 / 102.  K that is not compiled in: the generic predictor is
+// two to three times slower per node.
+bool tree_nodes_preferred(int total_nodes, int n_ids, int d, int K, int H, int Mcap, bool q4) {
+    if (n_ids > kMergePerThread * 256) return false;  // one workgroup of 256 threads merges a tree's ids
+    const bool exact = predict_exact(K), mfma = mlp_mfma_ok(K, H);
+    if (q4) return total_nodes <= (!exact ? 6144 : !mfma ? 16384 : K == 4 ? 12288 : 5120);
+    if (!mfma) return total_nodes <= (exact ? 12288 : 8192);
+    return total_nodes <= 4096 && (Mcap > 128 || (long long)total_nodes * (K + 1) * d <= 80000000);
 }
 
 hipError_t launch_tree_nodes(const PredictParams &p, int N, const int32_t *parent, int32_t *path_exit, hipStream_t s) {

@@ -37,13 +37,16 @@ __device__ __forceinline__ void local_softmax(const float (&z)[KC], int K, float
 
 template <int KC>
 struct MlpRow {
-    uint2 w1[(3 * KC + 3) / 4];  // 3*KC halves of W1[j][:], valid when K == KC
+    // 3*KC halves of W1[j][:], valid when K == KC: 8-byte pieces, or single halves where a row is not whole pieces
+    static constexpr bool kPieces = (3 * KC) % 4 == 0;
+    uint2 w1[(3 * KC + 3) / 4];
+    half_t w1s[kPieces ? 1 : 3 * KC];
     half_t w2, b1;               // as loaded; widened where they are used, so that requesting a row never waits
     bool has_b1;
 };
 
-// Request hidden unit `j`'s weights.  Vector loads need K == KC (row length
-// 3*KC halves is then a multiple of 8 bytes and feature indices are static).
+// Request hidden unit `j`'s weights.  Needs K == KC for the row of W1 (feature indices are then static);
+// otherwise the row is read where it is used, one more trip to memory.
 template <int KC>
 __device__ __forceinline__ void mlp_row_load(MlpRow<KC> &r, const half_t *W1, const half_t *b1, const half_t *w2,
                                              int K, int H, int j) {
@@ -51,9 +54,15 @@ __device__ __forceinline__ void mlp_row_load(MlpRow<KC> &r, const half_t *W1, co
     // clamped (callers ignore units j >= H) and an absent bias reads w2 instead, masked at use.
     const int jj = min(j, H - 1);
     if (K == KC) {
-        const uint2 *src = reinterpret_cast<const uint2 *>(W1 + (size_t)jj * 3 * KC);
+        if constexpr (MlpRow<KC>::kPieces) {
+            const uint2 *src = reinterpret_cast<const uint2 *>(W1 + (size_t)jj * 3 * KC);
 #pragma unroll
-        for (int q = 0; q < (3 * KC) / 4; ++q) r.w1[q] = src[q];
+            for (int q = 0; q < (3 * KC) / 4; ++q) r.w1[q] = src[q];
+        } else {
+            const half_t *src = W1 + (size_t)jj * 3 * KC;
+#pragma unroll
+            for (int t = 0; t < 3 * KC; ++t) r.w1s[t] = src[t];
+        }
     }
     r.w2 = w2[jj];
     r.b1 = (b1 ? b1 : w2)[jj];
@@ -73,11 +82,16 @@ __device__ __forceinline__ float mlp_unit(const MlpRow<KC> &r, const half_t *W1,
             f[KC + k] = pr[k];
             f[2 * KC + k] = pr[k] - prev[k];
         }
+        if constexpr (MlpRow<KC>::kPieces) {
 #pragma unroll
-        for (int q = 0; q < (3 * KC) / 4; ++q) {
-            half4 w4 = __builtin_bit_cast(half4, r.w1[q]);
+            for (int q = 0; q < (3 * KC) / 4; ++q) {
+                half4 w4 = __builtin_bit_cast(half4, r.w1[q]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) a += (float)w4[e] * f[q * 4 + e];
+                for (int e = 0; e < 4; ++e) a += (float)w4[e] * f[q * 4 + e];
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < 3 * KC; ++t) a += (float)r.w1s[t] * f[t];
         }
     } else {
         const half_t *src = W1 + (size_t)j * 3 * K;

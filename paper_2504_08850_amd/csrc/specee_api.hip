@@ -63,6 +63,7 @@ TreeSplit tree_split(int d, int n_total, int N, int Mcap) {
 // are scored one by one (tree_nodes_preferred).  Measured on MI355X with 60-node trees.
 constexpr int kWholeTreeMinTrees = 20;
 constexpr int kWholeTargetWgs = 256;
+constexpr int kWholeMaxSlices = 8;  // more lose to the serial hand-off to the last workgroup
 
 inline size_t align256(size_t b) {
     return (b + 255) & ~(size_t)255;
@@ -376,7 +377,7 @@ static int predict_tree_common(const specee_dims *dm, int G, int N, int Mcap, co
     if (!whole && exact_fit && (!workspace || workspace_bytes < lay.total)) return SPECEE_EWORKSPACE;
 
     // up to a few thousand nodes: every node on its own, which needs no workspace
-    if (tree_nodes_preferred(G * N, N * dm->K, dm->K, dm->H, false)) {
+    if (tree_nodes_preferred(G * N, N * dm->K, dm->d, dm->K, dm->H, Mcap, false)) {
         PredictParams pp = tree_nodes_params(dm, G, N, Mcap, hidden, gamma, ids, prev_probs, mlp, merged_ids, M_out,
                                              cols, logits, probs, scores, exit_flags);
         pp.lm_head = H(lm_head);
@@ -388,9 +389,9 @@ static int predict_tree_common(const specee_dims *dm, int G, int N, int Mcap, co
     if (whole) {
         gp.ids = ids;
         // fewer trees than the GPU holds workgroups: S workgroups per tree, one d-slice each, and the
-        // last to finish adds the slices up and scores the tree (at most three: trees of up to 64 nodes
-        // only come here when there are more than 64 of them)
+        // last to finish adds the slices up and scores the tree
         int S = kWholeTargetWgs / G;
+        if (S > kWholeMaxSlices) S = kWholeMaxSlices;
         if (S < 1) S = 1;
         int dslice = (((dm->d + S - 1) / S + 127) / 128) * 128;
         S = (dm->d + dslice - 1) / dslice;
@@ -520,7 +521,7 @@ int specee_predict_tree_q4(const specee_dims *dm, int G, int N, int Mcap, const 
     if ((rc = check_q4(dm, qweight, scales, zeros, group))) return rc;
     if ((reinterpret_cast<uintptr_t>(qweight) & 7) != 0) return SPECEE_EALIGN;
     if (!tree_q4_supported(dm->d, N, dm->K, Mcap, group)) return SPECEE_EINVAL;
-    if (tree_nodes_preferred(G * N, N * dm->K, dm->K, dm->H, true)) {
+    if (tree_nodes_preferred(G * N, N * dm->K, dm->d, dm->K, dm->H, Mcap, true)) {
         PredictParams pp = tree_nodes_params(dm, G, N, Mcap, hidden, gamma, ids, prev_probs, mlp, merged_ids, M_out,
                                              cols, logits, probs, scores, exit_flags);
         pp.qweight = qweight; pp.qscales = H(scales); pp.qzeros = H(zeros); pp.group = group;

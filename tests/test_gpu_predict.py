@@ -385,3 +385,25 @@ def test_status_word_reports_invalid_ids_and_merge_overflow(sp):
     w = sp.status_word(o["scores"])
     torch.cuda.synchronize()
     assert int(host(w)[0]) == 1
+
+
+@pytest.mark.parametrize("q4", [False, True])
+@pytest.mark.parametrize("K", [3, 5, 8])
+@pytest.mark.parametrize("d,B", [(1056, 127), (1056, 128), (2048, 1023), (2048, 1024), (2080, 1024), (5120, 130)])
+def test_predict_compiled_in_widths(sp, oracle, q4, K, d, B):
+    """K = 3, 5, 8 on both sides of the lines between launch shapes (128 tokens on quantised rows, 1024 on fp16 rows;
+    rows of up to 2 * 128 and 2 * 256 vectors), H not a multiple of the workgroup, biases present."""
+    from test_gpu_q4 import case, ref, run
+    t = case(d + B + K, d, 301, K, 516, B, 32, True)
+    oracle.set_threads(8)
+    if q4:
+        got, want = run(sp, t), ref(oracle, t)
+    else:
+        t["lm_head"] = (0.05 * np.random.default_rng(K).standard_normal((301, d))).astype(np.float16)
+        a = [t[k] for k in ("hidden", "gamma", "lm_head", "ids", "prev_probs", "W1", "w2", "b1", "b2")]
+        want = oracle.predict(*a)
+        out = sp.predict(*[dev(x) for x in a])
+        torch.cuda.synchronize()
+        got = {k: host(v) for k, v in out.items()}
+    oracle.set_threads(1)
+    check_scored(got, want, 0.5, f"K={K} d={d} B={B} q4={q4}")

@@ -561,8 +561,11 @@ def test_c5_large_vocab_tree_and_full_head(sp, oracle):
     (264, 700, 4, 64, 61, 260, 64),    # more trees than CUs, ragged d and N
     (520, 777, 8, 64, 64, 66, 256),    # wide merged sets, d-slices
     (256, 777, 8, 64, 64, 130, 256),   # ... one d-slice
-    (200, 300, 3, 100, 64, 128, 64),   # no matrix-core MLP: node by node up to twice as many
-    (200, 300, 3, 100, 64, 129, 64),   # one tree more
+    (136, 300, 3, 100, 64, 192, 64),   # no matrix-core MLP: node by node up to three times as many
+    (136, 300, 3, 100, 64, 193, 64),   # one tree more
+    (136, 300, 6, 100, 64, 128, 64),   # K not compiled in: twice as many
+    (136, 300, 6, 100, 64, 129, 64),   # one tree more
+    (136, 3000, 4, 64, 256, 5, 64),    # narrow rows, many nodes: more ids than 128 threads can merge
     (384, 900, 1, 64, 1024, 9, 64),    # trees of more than 64 nodes: split contraction with the merge in its prologue
     (136, 3000, 4, 64, 256, 3, 40),    # four ids per merging thread; one tree overflows its capacity
     (136, 3000, 4, 64, 257, 3, 40),    # more ids than that: merge kernel and split contraction

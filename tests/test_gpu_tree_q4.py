@@ -152,10 +152,12 @@ def test_tree_q4_argument_errors(sp):
 @pytest.mark.parametrize("d,V,K,H,N,G,Mcap", [
     (128, 300, 4, 64, 64, 192, 64),   # the most nodes that are scored node by node
     (128, 300, 4, 64, 64, 193, 64),   # one tree more: one workgroup per tree
-    (128, 300, 8, 64, 64, 48, 128),   # K = 8: fewer
-    (128, 300, 8, 64, 64, 49, 128),
-    (128, 300, 3, 100, 64, 96, 64),   # no matrix-core MLP
-    (160, 300, 3, 100, 64, 97, 64),
+    (128, 300, 8, 64, 64, 80, 128),   # K = 8: fewer
+    (128, 300, 8, 64, 64, 81, 128),
+    (64, 300, 3, 100, 64, 256, 64),   # no matrix-core MLP in the tree kernel: more
+    (64, 300, 3, 100, 64, 257, 64),
+    (64, 300, 6, 100, 64, 96, 64),    # K not compiled in
+    (96, 300, 6, 100, 64, 97, 64),
 ])
 def test_tree_q4_both_sides_of_the_node_by_node_line(sp, oracle, d, V, K, H, N, G, Mcap):
     t = make(d + N + K + G, d, V, K, H, N, G, 32, Mcap)
