@@ -26,7 +26,7 @@ __device__ __forceinline__ float dot8(half8 w, floatx4 xa, floatx4 xb, float acc
 // xb: 4..7; every 16-byte LDS read is then free of bank conflicts).  Lane l takes vectors l, l+64, ...
 // The loads are unconditional (vector index clamped, contribution selected afterwards) so that the
 // compiler keeps them all in flight instead of draining the memory pipeline at a branch join.
-// STREAM: rows are read with the non-temporal hint (heads that no cache can keep).
+// STREAM: rows are read with the non-temporal hint (head_streams).
 template <bool STREAM>
 __device__ __forceinline__ void head_two_rows(const half_t *w0, const half_t *w1, int nv, int lane, const floatx4 *xa,
                                               const floatx4 *xb, float &acc0, float &acc1) {
@@ -78,9 +78,14 @@ __device__ __forceinline__ void head_argmax_rows(const half_t *lm_head, int d, i
     }
 }
 
-// A head beyond this size cannot stay in the 256 MB last-level cache between passes: stream it.
-inline bool head_streams(int d, int V) {
-    return (size_t)V * d * sizeof(half_t) > ((size_t)288 << 20);
+// Whether a pass reads the rows with the non-temporal hint.  A head beyond 288 MB cannot stay in the 256 MB last-level
+// cache: always.  A smaller one is read by a single state once per token, with a model's weights passing through that
+// cache in between, so it comes from HBM, and the hint is worth a tenth there (arg-max, heads alternating so that none
+// stays: 262 MB 52.5 -> 47.1 us, 206 MB 47.1 -> 41.4, 164 MB 40.6 -> 37.4; the same head back to back instead:
+// 41.9 -> 43.7, 35.3 -> 37.4, 30.9 -> 33.6 us).  Several states of one call re-read the head right behind each other
+// and keep the cache's help (layer loop, three tokens, 262 MB: 166 us against 177 with the hint; 197 MB: 133 / 162).
+inline bool head_streams(int d, int V, int states) {
+    return (size_t)V * d * sizeof(half_t) > ((size_t)(states == 1 ? 128 : 288) << 20);
 }
 
 }  // namespace specee

@@ -456,7 +456,7 @@ __global__ void layer_loop_empty_kernel(int32_t *exit_layer, int32_t *token, int
 
 template <int KC, int VPT, bool EXACT>
 static hipError_t launch_loop_one(LoopParams p, int max_wgs, hipStream_t s) {
-    const bool stream = head_streams(p.d, p.V);
+    const bool stream = head_streams(p.d, p.V, p.B);
     constexpr bool kCanQ4 = KC * VPT <= 16 && KC <= 8;
     void (*kern)(LoopParams) = stream ? layer_loop_kernel<KC, VPT, EXACT, true> : layer_loop_kernel<KC, VPT, EXACT, false>;
     size_t lds = (size_t)p.d * sizeof(float);
@@ -506,6 +506,8 @@ hipError_t launch_layer_loop(const LoopParams &p, int max_wgs, hipStream_t s) {
     }
     if (p.K == 4) return launch_loop_vpt<4, true>(p, max_wgs, s);
     if (p.K == 8) return launch_loop_vpt<8, true>(p, max_wgs, s);
+    if (p.K == 3) return launch_loop_vpt<3, true>(p, max_wgs, s);
+    if (p.K == 5) return launch_loop_vpt<5, true>(p, max_wgs, s);
     if (p.K < 4) return launch_loop_vpt<4, false>(p, max_wgs, s);
     if (p.K < 8) return launch_loop_vpt<8, false>(p, max_wgs, s);
     return launch_loop_vpt<16, false>(p, max_wgs, s);

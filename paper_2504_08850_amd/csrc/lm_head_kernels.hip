@@ -22,9 +22,7 @@ constexpr int kGemvRows = kHeadRows;  // rows in flight per wavefront
 // ARGMAX: instead of storing the V logits, keep the best (value, row) of this
 // workgroup's rows (lowest row on ties) and store one candidate per workgroup:
 // best_val / best_idx [N][gridDim.x].
-// STREAM: the head is larger than the last-level cache, so its rows are read with the non-temporal hint
-// (350 -> 310 us at 128256 x 8192); a head that fits is read normally and partly served by that cache from
-// one call to the next (262 MB at 32000 x 4096: 39.7 us against 41.1 us with the hint).
+// STREAM: rows read with the non-temporal hint (head_streams says when; 350 -> 310 us at 128256 x 8192).
 template <bool ARGMAX, bool STREAM>
 __global__ __launch_bounds__(kGemvThreads) void lm_head_gemv_kernel(int d, int V, float eps, const half_t *hidden,
                                                                     const half_t *gamma, const half_t *lm_head,
@@ -192,7 +190,7 @@ static void launch_gemv_one(int d, int V, float eps, int N, const half_t *hidden
 
 hipError_t launch_lm_head_gemv(int d, int V, float eps, int N, const half_t *hidden, const half_t *gamma,
                                const half_t *lm_head, float *out, hipStream_t s) {
-    if (head_streams(d, V))
+    if (head_streams(d, V, N))
         launch_gemv_one<false, true>(d, V, eps, N, hidden, gamma, lm_head, out, nullptr, nullptr, nullptr, nullptr, s);
     else
         launch_gemv_one<false, false>(d, V, eps, N, hidden, gamma, lm_head, out, nullptr, nullptr, nullptr, nullptr, s);
@@ -202,7 +200,7 @@ hipError_t launch_lm_head_gemv(int d, int V, float eps, int N, const half_t *hid
 hipError_t launch_lm_head_argmax_gemv(int d, int V, float eps, int N, const half_t *hidden, const half_t *gamma,
                                       const half_t *lm_head, float *best_val, int32_t *best_idx, const int32_t *gate,
                                       const int32_t *done, hipStream_t s) {
-    if (head_streams(d, V))
+    if (head_streams(d, V, N))
         launch_gemv_one<true, true>(d, V, eps, N, hidden, gamma, lm_head, nullptr, best_val, best_idx, gate, done, s);
     else
         launch_gemv_one<true, false>(d, V, eps, N, hidden, gamma, lm_head, nullptr, best_val, best_idx, gate, done, s);

@@ -314,3 +314,13 @@ def test_layer_loop_argument_errors(sp):
         sp.layer_loop(z((L, 2, d), f16), z((d,), f16), z((V, d), f16), z((2, K), i32), z((L, H, 3 * K), f16),
                       z((L, H), f16), workspace=torch.empty(64, dtype=torch.uint8, device="cuda"))
     assert ei.value.code == -3
+
+
+@pytest.mark.parametrize("seed,K,d,H", [(0, 3, 4104, 600), (0, 5, 520, 100), (2, 5, 4104, 512)])
+def test_layer_loop_compiled_in_widths(sp, oracle, seed, K, d, H):
+    """K = 3 and 5: one and two vectors per thread, fewer and more hidden units than threads."""
+    t, plant = loop_inputs(seed, d, 700, K, H, 5, 4, [2, None, 4, 0], True)
+    t = plant_hits(oracle, t, plant)
+    oracle.set_threads(8)
+    check_loop(oracle, sp, t, 0.45, what=f"loop K={K} d={d}")
+    oracle.set_threads(1)

@@ -168,3 +168,12 @@ def test_layer_loop_q4_empty_stack_and_argument_errors(sp):
     with pytest.raises(sp.SpeceeError) as ei:     # workspace too small
         sp.layer_loop_q4(*base(4, 32), workspace=torch.empty(64, dtype=torch.uint8, device="cuda"))
     assert ei.value.code == -3
+
+
+@pytest.mark.parametrize("K,d,group", [(3, 4160, 32), (5, 512, 64), (5, 4160, 32), (5, 4104, 24)])
+def test_layer_loop_q4_compiled_in_widths(sp, oracle, K, d, group):
+    """K = 3 and 5 on quantised rows: one and two vectors per thread, wide chunks and single words."""
+    t = plant_hits(oracle, loop_inputs_q4(0, d, 600, K, 512, 4, 3, group, True), [2, None, 1])
+    oracle.set_threads(8)
+    check_loop(oracle, sp, t, 0.45, what=f"q4 loop K={K} d={d}")
+    oracle.set_threads(1)
