@@ -31,15 +31,17 @@ namespace specee {
 constexpr int kGemmThreads = 256;
 constexpr int kGemmWaves = 4;
 constexpr int kKC = 64;           // k elements per LDS stage (128 bytes of every row)
-constexpr int kNB = 64;           // hidden states per workgroup (4 n-tiles of 16)
 constexpr int kLdsRow = kKC + 8;  // halves per LDS row: 144 bytes, keeps 16-byte reads spread over banks
 
 // PD: stages of global loads kept in flight per wavefront.  The stage loop is free of
 // branches (loads past the end are issued on clamped addresses and contribute zeros): a load
 // under a branch makes the compiler drain every outstanding load at the join.
-template <int TPW, int MODE, int PD>
+// NT: n-tiles of 16 hidden states per workgroup.
+template <int TPW, int MODE, int PD, int NT>
 // (two wavefronts per SIMD asked for: unbounded, the 256-row shape took 272 registers, i.e. one workgroup per CU)
 __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmParams p) {
+    constexpr int kNB = 16 * NT;                 // hidden states per workgroup
+    constexpr int HV = kNB > 32 ? kNB / 32 : 1;  // vectors of x per thread and stage (NT = 1: two threads per vector)
     __shared__ __attribute__((aligned(16))) half_t lds_hi[2][kNB][kLdsRow];
     __shared__ __attribute__((aligned(16))) half_t lds_lo[2][kNB][kLdsRow];
     __shared__ float lds_ssq[kNB];
@@ -66,18 +68,18 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
         const int m = min(m0 + (wave * TPW + tp) * 16 + c, M - 1);
         rowptr[tp] = p.lm_head + (size_t)m * d;
     }
-    // ---- B side: this thread stages vector column vc of hidden states r0 and r0+32
-    const int vc = tid & 7, r0 = tid >> 3;
-    const half_t *hptr[2];
-    bool hok[2];
+    // ---- B side: this thread stages vector column vc of hidden states r0 (and r0+32)
+    const int vc = tid & 7, r0 = (tid >> 3) & (kNB < 32 ? kNB - 1 : 31);
+    const half_t *hptr[HV];
+    bool hok[HV];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < HV; ++i) {
         const int n = n0 + r0 + 32 * i;
         hok[i] = n < p.N;
         hptr[i] = p.hidden + (size_t)(hok[i] ? n : 0) * d;
     }
 
-    half8 a_buf[PD][TPW][2], h_buf[PD][2], g_buf[PD];
+    half8 a_buf[PD][TPW][2], h_buf[PD][HV], g_buf[PD];
     auto issue = [&](int kc, int slot) {
         const int k0 = kc * kKC;
 #pragma unroll
@@ -87,17 +89,17 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
         const int ko = min(k0 + vc * 8, d - 8);
         g_buf[slot] = load_half8(p.gamma + ko);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) h_buf[slot][i] = load_half8(hptr[i] + ko);
+        for (int i = 0; i < HV; ++i) h_buf[slot][i] = load_half8(hptr[i] + ko);
     };
 #pragma unroll
     for (int u = 0; u < PD; ++u) issue(u, u);
 
-    floatx4 acc[TPW][4];
+    floatx4 acc[TPW][NT];
 #pragma unroll
     for (int tp = 0; tp < TPW; ++tp)
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) acc[tp][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float ssq[2] = {0.f, 0.f};
+        for (int nt = 0; nt < NT; ++nt) acc[tp][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float ssq[HV] = {};
 
     const int nstages = ((nchunks + PD - 1) / PD) * PD;
     int buf = 0;
@@ -107,7 +109,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
             const int kc = kc0 + u;
             const bool b_in = kc * kKC + vc * 8 < d;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
+            for (int i = 0; i < HV; ++i) {
                 const half8 hsel = (b_in && hok[i]) ? h_buf[u][i] : zero_half8();
                 half8 hi, lo;
 #pragma unroll
@@ -136,19 +138,19 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
             issue(kc + PD, u);
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                half8 bh[4], bl[4];
+                half8 bh[NT], bl[NT];
 #pragma unroll
-                for (int nt = 0; nt < 4; ++nt) {
+                for (int nt = 0; nt < NT; ++nt) {
                     bh[nt] = *reinterpret_cast<const half8 *>(&lds_hi[buf][nt * 16 + c][q * 16 + j * 8]);
                     bl[nt] = *reinterpret_cast<const half8 *>(&lds_lo[buf][nt * 16 + c][q * 16 + j * 8]);
                 }
 #pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
+                for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                     for (int tp = 0; tp < TPW; ++tp)
                         acc[tp][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_cur[tp][j], bh[nt], acc[tp][nt], 0, 0, 0);
 #pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
+                for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                     for (int tp = 0; tp < TPW; ++tp)
                         acc[tp][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_cur[tp][j], bl[nt], acc[tp][nt], 0, 0, 0);
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
 
     // ---- sum of squares of each hidden state: 8 consecutive lanes share a row
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < HV; ++i) {
         float v = ssq[i];
         v += dpp_f32<kDppXor1>(v);
         v += dpp_f32<kDppXor2>(v);
@@ -167,8 +169,8 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
         ssq[i] = v;
     }
     if (vc == 0) {
-        lds_ssq[r0] = ssq[0];
-        lds_ssq[r0 + 32] = ssq[1];
+#pragma unroll
+        for (int i = 0; i < HV; ++i) lds_ssq[r0 + 32 * i] = ssq[i];
     }
     __syncthreads();
 
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
         __shared__ float cand_v[kGemmWaves][kNB];
         __shared__ int cand_i[kGemmWaves][kNB];
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
             const float scale = 1.0f / sqrtf(lds_ssq[nt * 16 + c] / (float)d + p.eps);
             float bv = -INFINITY;
             int bi = 0x7fffffff;
@@ -222,7 +224,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
         return;
     }
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
         const int n = n0 + nt * 16 + c;
         if (n >= p.N) continue;
         const float scale = 1.0f / sqrtf(lds_ssq[nt * 16 + c] / (float)d + p.eps);
@@ -243,11 +245,11 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
     }
 }
 
-template <int MODE, int TPW, int PD>
+template <int MODE, int TPW, int PD, int NT>
 static void launch_one(const GemmParams &p, hipStream_t st) {
     const int rows_per_wg = 16 * TPW * kGemmWaves;
-    dim3 grid((p.V + rows_per_wg - 1) / rows_per_wg, 1, (p.N + kNB - 1) / kNB);
-    hipLaunchKernelGGL((full_head_gemm_kernel<TPW, MODE, PD>), grid, dim3(kGemmThreads), 0, st, p);
+    dim3 grid((p.V + rows_per_wg - 1) / rows_per_wg, 1, (p.N + 16 * NT - 1) / (16 * NT));
+    hipLaunchKernelGGL((full_head_gemm_kernel<TPW, MODE, PD, NT>), grid, dim3(kGemmThreads), 0, st, p);
 }
 
 // 256 rows per workgroup when that still gives >= 400 workgroups, otherwise 128
@@ -257,12 +259,19 @@ static int lm_head_tpw(int V) {
 
 // Measured on MI355X (N = 16..64): 256-row tiles with two stages in flight for large vocabularies
 // (4.9 TB/s at 128256 x 8192), 128-row tiles with four stages for 32000-row heads (4.3-4.4 TB/s).
+// Up to 32 hidden states the 128-row tiles carry one or two n-tiles instead of four: less of x to build, read back and
+// multiply per stage (head from HBM: 32000 x 4096, N = 16 68.3 -> 59.7 us, N = 32 71.0 -> 63.7 us; 50280 x 2048 60.5 ->
+// 58.4 us).  The 256-row tiles do not gain (128256 x 8192, N = 16: 409 -> 418 us) and keep four.
 template <int MODE>
 static hipError_t launch_stream(const GemmParams &p, hipStream_t st) {
     if (lm_head_tpw(p.V) == 4)
-        launch_one<MODE, 4, 2>(p, st);
+        launch_one<MODE, 4, 2, 4>(p, st);
+    else if (p.N <= 16)
+        launch_one<MODE, 2, 4, 1>(p, st);
+    else if (p.N <= 32)
+        launch_one<MODE, 2, 4, 2>(p, st);
     else
-        launch_one<MODE, 2, 4>(p, st);
+        launch_one<MODE, 2, 4, 4>(p, st);
     return hipGetLastError();
 }
 

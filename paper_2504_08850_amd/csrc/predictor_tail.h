@@ -5,6 +5,8 @@
 // A thread's first MLP row can be requested long before the logits exist, so
 // its latency hides behind the LM-head row traffic.
 #pragma once
+#include <type_traits>
+
 #include "device_utils.h"
 
 namespace specee {
@@ -39,8 +41,7 @@ template <int KC>
 struct MlpRow {
     // 3*KC halves of W1[j][:], valid when K == KC: 8-byte pieces, or single halves where a row is not whole pieces
     static constexpr bool kPieces = (3 * KC) % 4 == 0;
-    uint2 w1[(3 * KC + 3) / 4];
-    half_t w1s[kPieces ? 1 : 3 * KC];
+    std::conditional_t<kPieces, uint2, half_t> w1[kPieces ? (3 * KC + 3) / 4 : 3 * KC];
     half_t w2, b1;               // as loaded; widened where they are used, so that requesting a row never waits
     bool has_b1;
 };
@@ -61,7 +62,7 @@ __device__ __forceinline__ void mlp_row_load(MlpRow<KC> &r, const half_t *W1, co
         } else {
             const half_t *src = W1 + (size_t)jj * 3 * KC;
 #pragma unroll
-            for (int t = 0; t < 3 * KC; ++t) r.w1s[t] = src[t];
+            for (int t = 0; t < 3 * KC; ++t) r.w1[t] = src[t];
         }
     }
     r.w2 = w2[jj];
@@ -91,7 +92,7 @@ __device__ __forceinline__ float mlp_unit(const MlpRow<KC> &r, const half_t *W1,
             }
         } else {
 #pragma unroll
-            for (int t = 0; t < 3 * KC; ++t) a += (float)r.w1s[t] * f[t];
+            for (int t = 0; t < 3 * KC; ++t) a += (float)r.w1[t] * f[t];
         }
     } else {
         const half_t *src = W1 + (size_t)j * 3 * K;

@@ -155,3 +155,23 @@ def test_predict_then_gated_verify(sp, oracle):
                     assert abs(full[n, tok[n]] - full[n].max()) <= 4e-3 * max(1.0, abs(full[n].max()))
             else:
                 assert tok[n] == -1 and hit[n] == 0
+
+
+@pytest.mark.parametrize("N", [3, 15, 16, 17, 31, 32, 33])
+def test_multi_state_head_and_verify_by_tiles_of_states(sp, oracle, N):
+    """One, two and four tiles of 16 states per workgroup, each with its last state and one more."""
+    rng = np.random.default_rng(N)
+    d, V, K = 1032, 261, 4
+    h = rng.standard_normal((N, d)).astype(np.float16)
+    g = (1 + 0.05 * rng.standard_normal(d)).astype(np.float16)
+    w = (0.05 * rng.standard_normal((V, d))).astype(np.float16)
+    ref = oracle.lm_head_gemv(h, g, w)
+    got = sp.lm_head_gemv(dev(h), dev(g), dev(w)).cpu().numpy()
+    assert np.all(np.abs(got - ref) <= 2e-3 * np.maximum(np.abs(ref), 1.0))
+    ids = np.stack([rng.choice(V, K, replace=False) for _ in range(N)]).astype(np.int32)
+    out = sp.verify(dev(h), dev(g), dev(w), dev(ids))
+    torch.cuda.synchronize()
+    # the same sums decide: the arg-max of the logits this library returns, bit for bit
+    tok = out["token"].cpu().numpy()
+    assert np.array_equal(tok, got.argmax(axis=1))
+    assert np.array_equal(out["max_logit"].cpu().numpy(), got[np.arange(N), tok])
