@@ -258,11 +258,11 @@ int specee_verify_q4(const specee_dims *dims, int N, const specee_half *hidden, 
 /*
  * specee_predict_tree on the 4-bit group-quantised LM head (Sec. 6.2 in the
  * quantised setting of Sec. 7.1 / 7.3): arguments, outputs and conventions as
- * specee_predict_tree, the head given as for specee_predict_q4.  The merged
- * contraction runs on the codes themselves (exact), each quantisation group's
- * sums being scaled and shifted by that group's scale and zero-point.
- * One workgroup per tree, so the call is meant for batches of trees; a single
- * tree is correct but takes one CU's time.  Needs no workspace.
+ * specee_predict_tree, the head given as for specee_predict_q4.  Up to a few
+ * thousand nodes each is scored as specee_predict_q4 would; larger calls take one
+ * workgroup per tree, whose merged contraction runs on the codes themselves
+ * (exact), each quantisation group's sums being scaled and shifted by that
+ * group's scale and zero-point.  Needs no workspace.
  * Limits: N <= 64, N*K <= 1024, Mcap <= 128, group a multiple of 32 that divides
  * d, qweight 8-byte aligned; d and group such that the staged scales and
  * zero-points fit in LDS (d / group <= 128 at Mcap <= 64).  Other shapes return

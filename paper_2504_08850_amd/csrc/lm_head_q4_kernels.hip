@@ -1,4 +1,5 @@
-// Full-vocabulary LM head on a 4-bit group-quantised head, with the final RMSNorm fused in: the
+// Full-vocabulary LM head on a 4-bit group-quantised head for one hidden state (lm_head_q4_mfma.hip takes several,
+// unless the format keeps them here), with the final RMSNorm fused in: the
 // search space and the verification step (paper Sec. 4.1, Sec. 4.3.3) in the weight-quantised setting
 // of the cloud evaluation (Sec. 7.1 "Quantization", Sec. 7.3).  Format as for the quantised-rows
 // predictor: element i of row v is a code c in 0..15 in bits 4*(i%8).. of 32-bit word i/8 and stands for
