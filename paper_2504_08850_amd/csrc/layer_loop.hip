@@ -7,7 +7,7 @@
 // exit.  Here a group of Pg workgroups stays resident for a token and walks the layers:
 //   * the predictor of a layer is evaluated redundantly by every workgroup of the group (its reads hit
 //     in L2 after the first workgroup): all of them reach the same exit decision with no communication,
-//     so a layer that does not fire costs no synchronisation.  Such a layer measures 2.1 us at d = 4096:
+//     so a layer that does not fire costs no synchronisation.  Such a layer measures 1.7 us at d = 4096:
 //     about 600 instructions of one wavefront's stream (hidden state to float, sum of squares, K dot
 //     products, two workgroup-wide reductions, softmax and MLP), not memory, which is prefetched one
 //     active layer ahead;
@@ -335,7 +335,10 @@ __global__ __launch_bounds__(kLoopThreads) void layer_loop_kernel(LoopParams p) 
                                         }
                                     });
         } else {
-            head_argmax_rows<STREAM>(p.lm_head, d, row_begin, row_end, wave, kLoopWaves, lane, xa, xb, r, bv, bi);
+            if (STREAM && (meetings == 0 || p.stream_every))
+                head_argmax_rows<true>(p.lm_head, d, row_begin, row_end, wave, kLoopWaves, lane, xa, xb, r, bv, bi);
+            else
+                head_argmax_rows<false>(p.lm_head, d, row_begin, row_end, wave, kLoopWaves, lane, xa, xb, r, bv, bi);
         }
         if (lane == 0) {
             cv[wave] = bv;
@@ -457,6 +460,12 @@ __global__ void layer_loop_empty_kernel(int32_t *exit_layer, int32_t *token, int
 template <int KC, int VPT, bool EXACT>
 static hipError_t launch_loop_one(LoopParams p, int max_wgs, hipStream_t s) {
     const bool stream = head_streams(p.d, p.V, p.B);
+    // A token's later verifications re-read the head, as several states do.  Back to back, 32 verifications without the
+    // hint / with it always / for the first only: 262 MB 1416 / 1430 / 1416 us, 205 MB 1169 / 1234 / 1171, 164 MB
+    // 982 / 1011 / 983; one verification of a head from HBM: 60.4 / 54.9 / 54.6, 53.1 / 48.7 / 48.6, 46.0 / 42.2 /
+    // 41.9 us.  What the first pass leaves out of the cache the second has to fetch: two of them, from HBM, 105.3 / 100.4
+    // / 106.4, 90.4 / 87.0 / 92.2, 77.3 / 74.5 / 78.9 us.
+    p.stream_every = head_streams(p.d, p.V, 2);
     constexpr bool kCanQ4 = KC * VPT <= 16 && KC <= 8;
     void (*kern)(LoopParams) = stream ? layer_loop_kernel<KC, VPT, EXACT, true> : layer_loop_kernel<KC, VPT, EXACT, false>;
     size_t lds = (size_t)p.d * sizeof(float);
