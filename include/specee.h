@@ -241,8 +241,8 @@ int specee_verify(const specee_dims *dims, int N, const specee_half *hidden, con
  * the paper's cloud evaluation runs the whole predict -> verify loop on the
  * quantised model (Sec. 7.1 "Quantization", Sec. 7.3).  Every LM-head row is
  * scale * (code - zero) per group; nothing else changes, and the dequantised
- * weights are never formed or rounded.  One pass over the head per hidden state
- * (d/2 + 4*d/group bytes per row).
+ * weights are never formed or rounded.  A pass over the head is d/2 + 4*d/group
+ * bytes per row: one per hidden state, or one per 16 of them where that is faster.
  *   lm_head_gemv_q4: out [N][V] fp32.  Needs no workspace.
  *   specee_verify_q4: arguments and outputs as specee_verify (gate, done, token,
  *   max_logit, hit).  Workspace: SPECEE_OP_VERIFY_Q4 with n = N.

@@ -178,8 +178,8 @@ hipError_t launch_lm_head_q4_argmax(int d, int V, float eps, int N, const half_t
                                     float *best_val, int32_t *best_idx, const int32_t *gate, const int32_t *done,
                                     hipStream_t s);
 
-// The same for two or more hidden states on the matrix cores, 16 states per pass over the codes (lm_head_q4_mfma.hip)
-bool lm_head_q4_mfma_supported(int d, int N, int group, const uint32_t *qweight);
+// The same for several hidden states on the matrix cores, 16 states per pass over the codes (lm_head_q4_mfma.hip)
+bool lm_head_q4_mfma_preferred(int d, int V, int N, int group, const uint32_t *qweight);
 int lm_head_q4_mfma_workgroups(int V);  // never more than lm_head_q4_workgroups(V)
 hipError_t launch_lm_head_q4_mfma(int d, int V, float eps, int N, const half_t *hidden, const half_t *gamma,
                                   const uint32_t *qweight, const half_t *scales, const half_t *zeros, int group,

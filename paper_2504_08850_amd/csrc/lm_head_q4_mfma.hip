@@ -45,7 +45,6 @@ constexpr int kQmThreads = 256 * kQmKh;
 constexpr int kQmWaves = kQmThreads / kWave;
 constexpr int kQmSteps = kQmStage / 32;                               // k-steps per stage
 constexpr int kQmVec = kQmStates * (kQmStage / 8) / kQmThreads;       // vectors of x per thread and stage
-constexpr int kQmDepth = 2;                                           // stages of loads in flight
 constexpr size_t kQmFragBytes = (size_t)2 * kQmSteps * 3 * kWave * 16;
 constexpr size_t kQmSumBytes = (size_t)2 * kQmSteps * kQmStates * sizeof(float);
 constexpr size_t kQmLdsBudget = 156 * 1024;
@@ -88,6 +87,9 @@ __device__ __forceinline__ uint32_t pack_high(uint32_t a, uint32_t b) {
 template <int LW, bool ARGMAX>
 __global__ __launch_bounds__(kQmThreads) void lm_head_q4_mfma_kernel(Q4HeadParams p) {
     constexpr int CH = kQmShare / (32 * LW);  // chunks per share
+    // stages of loads in flight: with small groups the folds need the registers (two stages spilled 9 to 12 of them at
+    // LW = 1, and one stage is faster there: 50280 x 2048 in groups of 32, 16 states, 66 -> 55 us, of 64, 40 -> 37 us)
+    constexpr int kQmDepth = LW == 4 ? 2 : 1;
     extern __shared__ __attribute__((aligned(16))) unsigned char qm_smem[];
     typedef uintx4 (*frag_t)[kQmSteps][3][kWave];
     frag_t frag = reinterpret_cast<frag_t>(qm_smem);
@@ -341,18 +343,12 @@ __global__ __launch_bounds__(kQmThreads) void lm_head_q4_mfma_kernel(Q4HeadParam
     }
 }
 
-// From two hidden states on (32000 x 4096: 25.8 us against 32.1 us on the vector units, 50280 x 2048: 25.6 against
-// 31.0 us): one state is cheaper on the vector units (18.4 us), which build no B operand.  The format has to keep a
-// chunk inside a group, and the rows' scales have to fit in LDS beside the B operand.
+// Words per lane and chunk that the format allows (0: chunks would cross groups).
 static int qm_words(int d, int group, const uint32_t *qweight) {
     const uintptr_t a = reinterpret_cast<uintptr_t>(qweight);
     for (int lw = 4; lw >= 1; lw >>= 1)
         if (group % (32 * lw) == 0 && d % (32 * lw) == 0 && a % (4 * lw) == 0) return lw;
     return 0;
-}
-
-bool lm_head_q4_mfma_supported(int d, int N, int group, const uint32_t *qweight) {
-    return N >= 2 && qm_words(d, group, qweight) > 0 && qm_lds_bytes(d, group) <= kQmLdsBudget;
 }
 
 // At most 512 workgroups per 16 states: never more arg-max candidates than the vector kernel's launch leaves.
@@ -363,6 +359,35 @@ static int qm_blocks_per_wg(int V) {
 int lm_head_q4_mfma_workgroups(int V) {
     const int rows = kQmRows * qm_blocks_per_wg(V);
     return (V + rows - 1) / rows;
+}
+
+// Whether a call goes to the matrix cores.  The format has to keep a chunk inside a group, and the rows' scales have
+// to fit in LDS beside the B operand (at most 116 groups in a row: 14848 columns in groups of 128, 7424 in groups of 64,
+// 3712 in groups of 32).  One state is cheaper on the vector units (18.4 us at 32000 x 4096), which build no B operand.
+// Several states are compared by the time that each kernel takes, in nanoseconds, fitted to 1848 pairs of measurements
+// (d = 1024 ... 8192, V = 500 ... 128256, 2 ... 64 states, groups of 128, 64 and 32; where the slower kernel is chosen it
+// is so by 15 % at most, in 15 of the pairs by more than 6 %):
+//   here, whole rounds of one workgroup per CU and a fixed time per block of 128 rows -- building B, unpacking and
+//   folding, the folds of small groups costing more -- however few rows there are;
+//   vector kernel, rounds of 512 workgroups (the last one partly filled) of one state's rows each, whose time is a
+//   prologue plus the rows; above 64 rows per workgroup the re-reads of the larger head show.
+// Vector kernel against this one, 4096 columns in groups of 128: 32000 rows, 2 states 31 / 24 us, 16 states 193 / 27 us;
+// 8000 rows, 2 states 11 / 20 us, 4 states 20 / 21, 6 states 27 / 21; 2000 rows, 16 states 19 / 22, 32 states 33 / 22.
+// Groups of 64: 32000 rows, 2 states 31 / 31, 3 states 44 / 31; 8000 rows, 4 states 19 / 28, 8 states 33 / 29.  Groups
+// of 32, 2048 columns: 50280 rows, 3 states 40 / 50, 4 states 52 / 50.
+bool lm_head_q4_mfma_preferred(int d, int V, int N, int group, const uint32_t *qweight) {
+    const int lw = qm_words(d, group, qweight);
+    if (N < 2 || lw == 0 || qm_lds_bytes(d, group) > kQmLdsBudget) return false;
+    const long long wgs = (long long)lm_head_q4_mfma_workgroups(V) * ((N + kQmStates - 1) / kQmStates);
+    const float block_ns = lw == 4 ? 5500.f + 3.85f * d : lw == 2 ? 6600.f + 5.5f * d : 6500.f + 9.6f * d;
+    const float here = (float)((wgs + 255) / 256 * qm_blocks_per_wg(V)) * block_ns;
+
+    const long long vwgs = (long long)lm_head_q4_workgroups(V) * N;
+    const int rows = (V + lm_head_q4_workgroups(V) - 1) / lm_head_q4_workgroups(V);
+    const float rows32 = (float)((rows + 31) / 32) * (rows > 64 ? 1.25f : 1.f);
+    const float round_ns = 1600.f + 0.56f * d + (1000.f + 1550.f * ((d + 2047) / 2048)) * rows32;
+    const float vector = 2500.f + 0.5f * ((float)vwgs / 512 + (float)((vwgs + 511) / 512)) * round_ns;
+    return 1.04f * here < vector;
 }
 
 template <int LW, bool ARGMAX>

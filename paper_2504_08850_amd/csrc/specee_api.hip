@@ -468,8 +468,9 @@ int lm_head_gemv_q4(const specee_dims *dm, int N, const specee_half *hidden, con
     if ((rc = check_q4(dm, qweight, scales, zeros, group))) return rc;
     if (!hidden || !gamma || !out) return SPECEE_EINVAL;
     if (misaligned(hidden) || misaligned(gamma)) return SPECEE_EALIGN;
-    // one hidden state (or a format whose chunks cross groups): vector units; more: one pass per 16 on the matrix cores
-    const auto launch = lm_head_q4_mfma_supported(dm->d, N, group, qweight) ? launch_lm_head_q4_mfma : launch_lm_head_q4;
+    // vector units: a pass over the head per state; matrix cores: a pass per 16 states
+    const bool mfma = lm_head_q4_mfma_preferred(dm->d, dm->V, N, group, qweight);
+    const auto launch = mfma ? launch_lm_head_q4_mfma : launch_lm_head_q4;
     return launch(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), qweight, H(scales), H(zeros), group, out,
                   static_cast<hipStream_t>(stream)) == hipSuccess
                ? SPECEE_OK
@@ -494,7 +495,7 @@ int specee_verify_q4(const specee_dims *dm, int N, const specee_half *hidden, co
     float *best_val = static_cast<float *>(workspace);
     int32_t *best_idx = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + half_ws);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool mfma = lm_head_q4_mfma_supported(dm->d, N, group, qweight);
+    const bool mfma = lm_head_q4_mfma_preferred(dm->d, dm->V, N, group, qweight);
     const int P = mfma ? lm_head_q4_mfma_workgroups(dm->V) : lm_head_q4_workgroups(dm->V);
     const auto launch = mfma ? launch_lm_head_q4_mfma_argmax : launch_lm_head_q4_argmax;
     if (launch(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), qweight, H(scales), H(zeros), group, best_val, best_idx,

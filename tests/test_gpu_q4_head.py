@@ -162,18 +162,28 @@ def test_q4_head_argument_errors(sp):
     assert ei.value.code == -3
 
 
-@pytest.mark.parametrize("d,V,N,group,hscale,misalign", [
-    (4096, 257, 16, 128, 1.0, 0),      # whole stages, one row past two blocks of 128
-    (640, 128, 2, 128, 1.0, 0),        # ragged last stage; the fewest states
-    (512, 127, 17, 64, 1.0, 0),        # two words per chunk; a second tile of states holding one
-    (96, 33, 3, 32, 1.0, 0),           # one word per chunk, less than a share of a stage
-    (1024, 130, 5, 256, 1.0, 2),       # several chunks per group; codes and scales off 16-byte alignment
-    (64, 65665, 4, 64, 1.0, 0),        # two row blocks per workgroup, ragged end
-    (512, 129, 8, 128, 2.0 ** -13, 0), # hidden states near the smallest normal halves
-    (512, 129, 8, 128, 16000.0, 0),    # products with the norm weight beyond the range of halves
+@pytest.mark.parametrize("d,V,N,group,hscale,misalign,matrix", [
+    (4096, 257, 16, 128, 1.0, 0, False),
+    (640, 128, 2, 128, 1.0, 0, False),
+    (512, 127, 17, 64, 1.0, 0, False),
+    (96, 33, 3, 32, 1.0, 0, False),
+    (1024, 130, 5, 256, 1.0, 2, False),
+    (64, 65665, 4, 64, 1.0, 0, True),          # two row blocks per workgroup, ragged end
+    (512, 129, 8, 128, 2.0 ** -13, 0, False),
+    (512, 129, 8, 128, 16000.0, 0, False),
+    (4096, 2049, 32, 128, 1.0, 0, True),       # whole stages, one row past sixteen blocks of 128
+    (640, 12033, 2, 128, 1.0, 0, True),        # ragged last stage; the fewest states
+    (512, 2047, 17, 64, 1.0, 0, True),         # two words per chunk; a second tile of states holding one
+    (96, 4033, 3, 32, 1.0, 0, False),          # one word per chunk, less than a share of a stage: not enough rows
+    (96, 9033, 3, 32, 1.0, 0, True),           # ... enough
+    (1056, 1900, 33, 96, 1.0, 0, True),        # one word per chunk, three chunks per group, three tiles of states
+    (1024, 9002, 5, 256, 1.0, 2, True),        # several chunks per group; codes and scales off 16-byte alignment
+    (512, 3073, 8, 128, 2.0 ** -13, 0, True),  # hidden states near the smallest normal halves
+    (512, 3073, 8, 128, 16000.0, 0, True),     # products with the norm weight beyond the range of halves
+    (4096, 700, 48, 32, 1.0, 0, False),        # 128 groups in a row: their scales do not fit beside the operand
 ])
-def test_lm_head_q4_several_states(sp, oracle, d, V, N, group, hscale, misalign):
-    """Matrix-core pass (two or more states).  Every product enters whole, so the error is that of fp32 sums: a term
+def test_lm_head_q4_several_states(sp, oracle, d, V, N, group, hscale, misalign, matrix):
+    """Several states, on either kernel.  On the matrix cores every product enters whole, so the error is that of fp32 sums: a term
     passes at most 3 * 4 * 32 additions of a chunk, d / 512 folds and a handful of combining steps, each off by
     2^-24 of what it has summed, which sum |x| scale (code + zero) bounds."""
     t = case(d + V + N, d, V, 2, 8, N, group, False)
@@ -197,6 +207,9 @@ def test_lm_head_q4_several_states(sp, oracle, d, V, N, group, hscale, misalign)
     out = torch.full((N, V), float("nan"), device="cuda")
     got = host(sp.lm_head_gemv_q4(dev(t["hidden"]), dev(t["gamma"]), qd, sd, zd, group, out=out))
     assert np.isfinite(got).all()
+    # the vector kernel sums a state's logits the same way whether or not others come with it, the matrix cores do not
+    one = host(sp.lm_head_gemv_q4(dev(t["hidden"][:1]), dev(t["gamma"]), qd, sd, zd, group))
+    assert np.array_equal(one[0], got[0]) == (not matrix)
     assert np.all(np.abs(got - ref) <= (3 * 4 * 32 + d / 512 + 8) * 2.0 ** -24 * bound)
     ids = t["ids"].copy()
     ids[:, 0] = ref.argmax(axis=1)
@@ -206,3 +219,53 @@ def test_lm_head_q4_several_states(sp, oracle, d, V, N, group, hscale, misalign)
     rows = np.arange(N)
     # the same sums decide: the token is the arg-max of the logits this library returns, bit for bit
     assert np.array_equal(v["token"], got.argmax(axis=1)) and np.array_equal(v["max_logit"], got[rows, v["token"]])
+
+
+@pytest.mark.parametrize("d,V,group,N", [(512, 5003, 128, 6), (512, 1303, 128, 33), (512, 6003, 64, 6),
+                                         (512, 2303, 64, 33)])
+def test_verify_q4_gate_and_done_on_the_matrix_cores(sp, oracle, d, V, group, N):
+    """States of one tile of 16 share a pass: a tile with some states off, a tile with all of them off, and candidates
+    that were never written (the workspace is poisoned first with what would win)."""
+    t = case(d + V + N, d, V, 4, 8, N, group, False)
+    full = oracle.lm_head_gemv_q4(t["hidden"], t["gamma"], t["q"], t["scales"], t["zeros"], group)
+    ids = t["ids"].copy()
+    ids[:, 1] = full.argmax(axis=1)                  # every verified state hits
+    n = np.arange(N)
+    for gate, done in [(n % 3 != 1, n == 2), (n >= 16, n % 4 == 0), (n < 16, np.zeros(N, bool)),
+                       (np.zeros(N, bool), np.zeros(N, bool)), (np.ones(N, bool), np.ones(N, bool))]:
+        need = sp.workspace_bytes(sp.OP_VERIFY_Q4, sp.Dims(d, V, 4, 1, 1e-5, 0.5), N)
+        ws = torch.full((need // 4,), 1e30, dtype=torch.float32, device="cuda")
+        out = {"token": torch.full((N,), 123, dtype=torch.int32, device="cuda"),
+               "max_logit": torch.full((N,), 9.0, dtype=torch.float32, device="cuda"),
+               "hit": torch.full((N,), 5, dtype=torch.int32, device="cuda")}
+        done_d = dev(done.astype(np.int32))
+        got = run_verify(sp, t, ids, gate=dev(7 * gate.astype(np.int32)), done=done_d, workspace=ws, out=out)
+        live = gate & ~done
+        check_verify(got, full, ids, f"verify_q4 gated N={N} group={group}", live=live)
+        assert np.array_equal(host(done_d), (done | live).astype(np.int32))
+        if live.any():
+            free = run_verify(sp, t, ids)            # the sums of a live state do not depend on who else is on
+            assert all(np.array_equal(got[k][live], free[k][live]) for k in got)
+
+
+@pytest.mark.parametrize("group,V", [(128, 3073), (64, 3501), (32, 4500)])
+def test_q4_head_on_the_matrix_cores_keeps_a_bad_state_to_itself(sp, group, V):
+    """NaN and infinite hidden states: their own logits are NaN, as from the vector kernel, every other state of the tile
+    is the same bit for bit, and the verification reports them as it does for one state."""
+    d, N, bad = 512, 18, [3, 7, 16]
+    t = case(V, d, V, 4, 8, N, group, False)
+    args = (dev(t["gamma"]), *qdev(t), group)
+    good = host(sp.lm_head_gemv_q4(dev(t["hidden"]), *args))
+    h = t["hidden"].copy()
+    h[3, 100], h[7, 0], h[16, d - 1] = np.nan, np.inf, -np.inf
+    got = host(sp.lm_head_gemv_q4(dev(h), *args))
+    one = host(sp.lm_head_gemv_q4(dev(h[3:4]), *args))
+    assert not np.array_equal(good[0], host(sp.lm_head_gemv_q4(dev(h[:1]), *args))[0])   # the matrix cores took it
+    rest = np.setdiff1d(np.arange(N), bad)
+    assert np.array_equal(got[rest], good[rest])
+    assert np.isnan(one).all() and np.isnan(got[bad]).all()
+    v, w = (run_verify(sp, dict(t, hidden=x), t["ids"]) for x in (h, t["hidden"]))
+    assert all(np.array_equal(v[k][rest], w[k][rest]) for k in v)
+    for n in bad:
+        alone = run_verify(sp, dict(t, hidden=h[n:n + 1]), t["ids"][n:n + 1])
+        assert all(np.array_equal(v[k][n:n + 1], alone[k], equal_nan=k == "max_logit") for k in v), (n, v["token"][n], alone)
