@@ -70,7 +70,6 @@ struct LoopParams {
     float *cand_val;        // [2][B][workgroups per token] arg-max candidates
     int32_t *cand_idx;
     long long spin_limit;   // polls of the arrival counter before a meeting is given up
-    bool stream_every;      // non-temporal hint in every verification, not only in a token's first (set by the launcher)
 };
 hipError_t launch_layer_loop(const LoopParams &p, int max_wgs, hipStream_t s);
 

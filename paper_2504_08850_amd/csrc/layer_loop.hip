@@ -46,7 +46,8 @@ constexpr int kLoopMaskLds = 1024;  // layers of the active mask kept in LDS (de
 // 2 = quantised head read word by word.  On a quantised head the token's K rows are dequantised once, into
 // the float registers that hold them anyway (with the RMSNorm weight folded in), so the predictor of a layer is
 // the same code; the verification streams the codes (q4_head_rows).  Needs KEEP (K <= 8).
-template <int KC, int VPT, bool EXACT, bool STREAM, int HEAD = 0>
+// STREAM: verifications that read the head with the non-temporal hint -- 0 none, 1 all, 2 a token's first.
+template <int KC, int VPT, bool EXACT, int STREAM, int HEAD = 0>
 __global__ __launch_bounds__(kLoopThreads) void layer_loop_kernel(LoopParams p) {
     constexpr bool KEEP = KC * VPT <= 16 && KC <= 8;
     constexpr bool Q4 = HEAD != 0;
@@ -335,7 +336,7 @@ __global__ __launch_bounds__(kLoopThreads) void layer_loop_kernel(LoopParams p) 
                                         }
                                     });
         } else {
-            if (STREAM && (meetings == 0 || p.stream_every))
+            if (STREAM == 1 || (STREAM == 2 && meetings == 0))
                 head_argmax_rows<true>(p.lm_head, d, row_begin, row_end, wave, kLoopWaves, lane, xa, xb, r, bv, bi);
             else
                 head_argmax_rows<false>(p.lm_head, d, row_begin, row_end, wave, kLoopWaves, lane, xa, xb, r, bv, bi);
@@ -459,21 +460,25 @@ __global__ void layer_loop_empty_kernel(int32_t *exit_layer, int32_t *token, int
 
 template <int KC, int VPT, bool EXACT>
 static hipError_t launch_loop_one(LoopParams p, int max_wgs, hipStream_t s) {
-    const bool stream = head_streams(p.d, p.V, p.B);
+    constexpr bool kCanQ4 = KC * VPT <= 16 && KC <= 8;
     // A token's later verifications re-read the head, as several states do.  Back to back, 32 verifications without the
     // hint / with it always / for the first only: 262 MB 1416 / 1430 / 1416 us, 205 MB 1169 / 1234 / 1171, 164 MB
     // 982 / 1011 / 983; one verification of a head from HBM: 60.4 / 54.9 / 54.6, 53.1 / 48.7 / 48.6, 46.0 / 42.2 /
     // 41.9 us.  What the first pass leaves out of the cache the second has to fetch: two of them, from HBM, 105.3 / 100.4
-    // / 106.4, 90.4 / 87.0 / 92.2, 77.3 / 74.5 / 78.9 us.
-    p.stream_every = head_streams(p.d, p.V, 2);
-    constexpr bool kCanQ4 = KC * VPT <= 16 && KC <= 8;
-    void (*kern)(LoopParams) = stream ? layer_loop_kernel<KC, VPT, EXACT, true> : layer_loop_kernel<KC, VPT, EXACT, false>;
+    // / 106.4, 90.4 / 87.0 / 92.2, 77.3 / 74.5 / 78.9 us.  Wider shapes have no registers for a second copy of the
+    // streaming loop (K = 8, d > 4096: 25 -> 54 spilled) and read a head that the cache can keep without the hint.
+    void (*kern)(LoopParams) = layer_loop_kernel<KC, VPT, EXACT, 0>;
+    if (head_streams(p.d, p.V, 2)) {
+        kern = layer_loop_kernel<KC, VPT, EXACT, 1>;
+    } else if constexpr (KC * VPT <= 8) {
+        if (head_streams(p.d, p.V, p.B)) kern = layer_loop_kernel<KC, VPT, EXACT, 2>;
+    }
     size_t lds = (size_t)p.d * sizeof(float);
     int quantum = kLoopWaves * kHeadRows;
     if (p.qweight) {
         if constexpr (kCanQ4) {
             const bool wide = p.group % 32 == 0 && p.d % 32 == 0 && (reinterpret_cast<uintptr_t>(p.qweight) & 15) == 0;
-            kern = wide ? layer_loop_kernel<KC, VPT, EXACT, false, 1> : layer_loop_kernel<KC, VPT, EXACT, false, 2>;
+            kern = wide ? layer_loop_kernel<KC, VPT, EXACT, 0, 1> : layer_loop_kernel<KC, VPT, EXACT, 0, 2>;
             lds += (size_t)(p.d / p.group) * sizeof(float);
             quantum = kLoopWaves * kQ4HeadRows;
         } else {
