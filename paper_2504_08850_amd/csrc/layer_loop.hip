@@ -518,13 +518,17 @@ hipError_t launch_layer_loop(const LoopParams &p, int max_wgs, hipStream_t s) {
         hipLaunchKernelGGL(layer_loop_empty_kernel, dim3(1), dim3(64), 0, s, p.exit_layer, p.token, p.status, p.B);
         return hipGetLastError();
     }
-    if (p.K == 4) return launch_loop_vpt<4, true>(p, max_wgs, s);
-    if (p.K == 8) return launch_loop_vpt<8, true>(p, max_wgs, s);
-    if (p.K == 3) return launch_loop_vpt<3, true>(p, max_wgs, s);
-    if (p.K == 5) return launch_loop_vpt<5, true>(p, max_wgs, s);
-    if (p.K < 4) return launch_loop_vpt<4, false>(p, max_wgs, s);
-    if (p.K < 8) return launch_loop_vpt<8, false>(p, max_wgs, s);
-    return launch_loop_vpt<16, false>(p, max_wgs, s);
+    switch (p.K) {
+        case 1: return launch_loop_vpt<1, true>(p, max_wgs, s);
+        case 2: return launch_loop_vpt<2, true>(p, max_wgs, s);
+        case 3: return launch_loop_vpt<3, true>(p, max_wgs, s);
+        case 4: return launch_loop_vpt<4, true>(p, max_wgs, s);
+        case 5: return launch_loop_vpt<5, true>(p, max_wgs, s);
+        case 6: return launch_loop_vpt<6, true>(p, max_wgs, s);
+        case 7: return launch_loop_vpt<7, true>(p, max_wgs, s);
+        case 8: return launch_loop_vpt<8, true>(p, max_wgs, s);
+        default: return launch_loop_vpt<16, false>(p, max_wgs, s);
+    }
 }
 
 }  // namespace specee

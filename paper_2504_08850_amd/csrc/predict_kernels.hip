@@ -42,7 +42,7 @@ __device__ __forceinline__ void merge_one_tree(const TreeMergeParams &m, int g) 
 // thread per row (d/8 <= VPT * 512 * tiles).  SWEEP: the previous layer's local
 // probabilities are recomputed from that layer's hidden state instead of read,
 // which makes every (layer, token) workgroup independent.
-// EXACT: K == KC is known at compile time (the common K = 4 and K = 8): every `k < K` predicate and
+// EXACT: K == KC is known at compile time (K <= 8): every `k < K` predicate and
 // the generic MLP path fold away, which shortens the serial instruction stream of this latency-bound
 // kernel.
 // T: threads per workgroup.  512 gives the shortest single call (one vector of a 4096-wide row and one
@@ -626,12 +626,13 @@ static bool merge_fits(const PredictParams &p, int threads) {
     return !TREE || p.tree.n <= kMergePerThread * threads;
 }
 
-// K values that are compiled in.  Against the generic form (rows of W1 read where they are used, tests of k < K):
-// K = 3, 8000 tokens 51.2 -> 38.3 us, one token 4.3 -> 3.3 us; K = 5, 8000 tokens 103 -> 55 us, one token 5.9 -> 3.8 us;
-// quantised rows, 8000 tokens: K = 3 59.5 -> 27.3, K = 5 124 -> 35.4, K = 8 (now with the throughput shapes of K = 4)
-// 77.5 -> 41.5 us.
+// K values that are compiled in: up to 8, where the rows of every shape fit in registers.  Against the generic form, which
+// larger K take (rows of W1 read where they are used, tests of k < K), at d = 4096: one token K = 1 3.7 -> 2.9 us, 2
+// 3.9 -> 3.0, 3 4.3 -> 3.3, 5 5.9 -> 3.8, 6 6.3 -> 3.8, 7 6.8 -> 4.9; 8000 tokens 39 -> 23, 45 -> 30, 51 -> 38, 103 -> 55,
+// 118 -> 65, 134 -> 77 us; the same on quantised rows, 8000 tokens 54 -> 20, 58 -> 23, 60 -> 27, 124 -> 35, 133 -> 34,
+// 143 -> 57, and K = 8, which has their throughput shapes too, 78 -> 42 us.
 static bool predict_exact(int K) {
-    return K == 3 || K == 4 || K == 5 || K == 8;
+    return K <= 8;
 }
 
 template <int KC, bool SWEEP, bool EXACT, bool TREE>
@@ -673,13 +674,17 @@ static hipError_t launch_vpt(const PredictParams &p, hipStream_t s) {
 
 template <bool SWEEP, bool TREE>
 static hipError_t launch_kc(const PredictParams &p, hipStream_t s) {
-    if (p.K == 4) return launch_vpt<4, SWEEP, true, TREE>(p, s);
-    if (p.K == 8) return launch_vpt<8, SWEEP, true, TREE>(p, s);
-    if (!SWEEP && p.K == 3) return launch_vpt<3, false, true, TREE>(p, s);
-    if (!SWEEP && p.K == 5) return launch_vpt<5, false, true, TREE>(p, s);
-    if (p.K < 4) return launch_vpt<4, SWEEP, false, TREE>(p, s);
-    if (p.K < 8) return launch_vpt<8, SWEEP, false, TREE>(p, s);
-    return launch_vpt<16, SWEEP, false, TREE>(p, s);
+    switch (p.K) {
+        case 1: return launch_vpt<1, SWEEP, true, TREE>(p, s);
+        case 2: return launch_vpt<2, SWEEP, true, TREE>(p, s);
+        case 3: return launch_vpt<3, SWEEP, true, TREE>(p, s);
+        case 4: return launch_vpt<4, SWEEP, true, TREE>(p, s);
+        case 5: return launch_vpt<5, SWEEP, true, TREE>(p, s);
+        case 6: return launch_vpt<6, SWEEP, true, TREE>(p, s);
+        case 7: return launch_vpt<7, SWEEP, true, TREE>(p, s);
+        case 8: return launch_vpt<8, SWEEP, true, TREE>(p, s);
+        default: return launch_vpt<16, SWEEP, false, TREE>(p, s);
+    }
 }
 
 hipError_t launch_predict(const PredictParams &p, hipStream_t s) {
@@ -724,13 +729,17 @@ static hipError_t launch_q4_kc(const PredictParams &p, hipStream_t s) {
 
 template <bool TREE>
 static hipError_t launch_q4_any(const PredictParams &p, hipStream_t s) {
-    if (p.K == 4) return launch_q4_kc<4, true, TREE>(p, s);
-    if (p.K == 8) return launch_q4_kc<8, true, TREE>(p, s);
-    if (p.K == 3) return launch_q4_kc<3, true, TREE>(p, s);
-    if (p.K == 5) return launch_q4_kc<5, true, TREE>(p, s);
-    if (p.K < 4) return launch_q4_kc<4, false, TREE>(p, s);
-    if (p.K < 8) return launch_q4_kc<8, false, TREE>(p, s);
-    return launch_q4_kc<16, false, TREE>(p, s);
+    switch (p.K) {
+        case 1: return launch_q4_kc<1, true, TREE>(p, s);
+        case 2: return launch_q4_kc<2, true, TREE>(p, s);
+        case 3: return launch_q4_kc<3, true, TREE>(p, s);
+        case 4: return launch_q4_kc<4, true, TREE>(p, s);
+        case 5: return launch_q4_kc<5, true, TREE>(p, s);
+        case 6: return launch_q4_kc<6, true, TREE>(p, s);
+        case 7: return launch_q4_kc<7, true, TREE>(p, s);
+        case 8: return launch_q4_kc<8, true, TREE>(p, s);
+        default: return launch_q4_kc<16, false, TREE>(p, s);
+    }
 }
 
 hipError_t launch_predict_q4(const PredictParams &p, hipStream_t s) {

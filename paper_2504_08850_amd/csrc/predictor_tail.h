@@ -39,9 +39,10 @@ __device__ __forceinline__ void local_softmax(const float (&z)[KC], int K, float
 
 template <int KC>
 struct MlpRow {
-    // 3*KC halves of W1[j][:], valid when K == KC: 8-byte pieces, or single halves where a row is not whole pieces
-    static constexpr bool kPieces = (3 * KC) % 4 == 0;
-    std::conditional_t<kPieces, uint2, half_t> w1[kPieces ? (3 * KC + 3) / 4 : 3 * KC];
+    // 3*KC halves of W1[j][:], valid when K == KC, in the largest pieces of 4, 2 or 1 halves that a row is whole pieces of
+    static constexpr int kPiece = (3 * KC) % 4 == 0 ? 4 : (3 * KC) % 2 == 0 ? 2 : 1;
+    typedef std::conditional_t<kPiece == 4, uint2, std::conditional_t<kPiece == 2, uint32_t, half_t>> piece_t;
+    piece_t w1[3 * KC / kPiece];
     half_t w2, b1;               // as loaded; widened where they are used, so that requesting a row never waits
     bool has_b1;
 };
@@ -55,15 +56,10 @@ __device__ __forceinline__ void mlp_row_load(MlpRow<KC> &r, const half_t *W1, co
     // clamped (callers ignore units j >= H) and an absent bias reads w2 instead, masked at use.
     const int jj = min(j, H - 1);
     if (K == KC) {
-        if constexpr (MlpRow<KC>::kPieces) {
-            const uint2 *src = reinterpret_cast<const uint2 *>(W1 + (size_t)jj * 3 * KC);
+        typedef typename MlpRow<KC>::piece_t piece_t;
+        const piece_t *src = reinterpret_cast<const piece_t *>(W1 + (size_t)jj * 3 * KC);
 #pragma unroll
-            for (int q = 0; q < (3 * KC) / 4; ++q) r.w1[q] = src[q];
-        } else {
-            const half_t *src = W1 + (size_t)jj * 3 * KC;
-#pragma unroll
-            for (int t = 0; t < 3 * KC; ++t) r.w1[t] = src[t];
-        }
+        for (int q = 0; q < 3 * KC / MlpRow<KC>::kPiece; ++q) r.w1[q] = src[q];
     }
     r.w2 = w2[jj];
     r.b1 = (b1 ? b1 : w2)[jj];
@@ -83,16 +79,13 @@ __device__ __forceinline__ float mlp_unit(const MlpRow<KC> &r, const half_t *W1,
             f[KC + k] = pr[k];
             f[2 * KC + k] = pr[k] - prev[k];
         }
-        if constexpr (MlpRow<KC>::kPieces) {
+        constexpr int kP = MlpRow<KC>::kPiece;
+        typedef half_t halves_t __attribute__((ext_vector_type(kP)));
 #pragma unroll
-            for (int q = 0; q < (3 * KC) / 4; ++q) {
-                half4 w4 = __builtin_bit_cast(half4, r.w1[q]);
+        for (int q = 0; q < 3 * KC / kP; ++q) {
+            const halves_t w = __builtin_bit_cast(halves_t, r.w1[q]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) a += (float)w4[e] * f[q * 4 + e];
-            }
-        } else {
-#pragma unroll
-            for (int t = 0; t < 3 * KC; ++t) a += (float)r.w1[t] * f[t];
+            for (int e = 0; e < kP; ++e) a += (float)w[e] * f[q * kP + e];
         }
     } else {
         const half_t *src = W1 + (size_t)j * 3 * K;

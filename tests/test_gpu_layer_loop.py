@@ -335,3 +335,13 @@ def test_layer_loop_rereads_a_head_of_134_mb(sp, oracle):
     ref = check_loop(oracle, sp, t, -1.0, what="134 MB head")
     oracle.set_threads(1)
     assert ref["exit"].sum() == 4 and ref["exit_layer"][0] == 3
+
+
+@pytest.mark.parametrize("seed,K,d,H", [(0, 1, 520, 9), (0, 2, 4104, 513), (0, 6, 520, 515), (0, 7, 4104, 40)])
+def test_layer_loop_other_widths(sp, oracle, seed, K, d, H):
+    """The other K that are compiled in, rows of W1 in pieces of one and two halves."""
+    t, plant = loop_inputs(seed, d, 700, K, H, 5, 4, [2, None, 4, 0], True)
+    t = plant_hits(oracle, t, plant)
+    oracle.set_threads(8)
+    check_loop(oracle, sp, t, 0.45, what=f"loop K={K} d={d}")
+    oracle.set_threads(1)

@@ -177,3 +177,12 @@ def test_layer_loop_q4_compiled_in_widths(sp, oracle, K, d, group):
     oracle.set_threads(8)
     check_loop(oracle, sp, t, 0.45, what=f"q4 loop K={K} d={d}")
     oracle.set_threads(1)
+
+
+@pytest.mark.parametrize("seed,K,d,group", [(3, 1, 4160, 32), (0, 2, 512, 64), (2, 6, 4160, 32), (1, 7, 4104, 24)])
+def test_layer_loop_q4_other_widths(sp, oracle, seed, K, d, group):
+    """The other K that are compiled in, on quantised rows."""
+    t = plant_hits(oracle, loop_inputs_q4(seed, d, 600, K, 512, 4, 3, group, True), [2, None, 1])
+    oracle.set_threads(8)
+    check_loop(oracle, sp, t, 0.45, what=f"q4 loop K={K} d={d}")
+    oracle.set_threads(1)

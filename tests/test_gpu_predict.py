@@ -407,3 +407,46 @@ def test_predict_compiled_in_widths(sp, oracle, q4, K, d, B):
         got = {k: host(v) for k, v in out.items()}
     oracle.set_threads(1)
     check_scored(got, want, 0.5, f"K={K} d={d} B={B} q4={q4}")
+
+
+@pytest.mark.parametrize("q4", [False, True])
+@pytest.mark.parametrize("K,d,B", [(1, 1056, 129), (2, 2048, 1024), (6, 1056, 1030), (7, 5120, 130), (9, 1056, 129)])
+def test_predict_other_widths(sp, oracle, q4, K, d, B):
+    """The other K that are compiled in, rows of W1 in pieces of one and two halves, and the first that is not."""
+    from test_gpu_q4 import case, ref, run
+    t = case(d + B + K, d, 301, K, 516, B, 32, True)
+    oracle.set_threads(8)
+    if q4:
+        got, want = run(sp, t), ref(oracle, t)
+    else:
+        t["lm_head"] = (0.05 * np.random.default_rng(K).standard_normal((301, d))).astype(np.float16)
+        a = [t[k] for k in ("hidden", "gamma", "lm_head", "ids", "prev_probs", "W1", "w2", "b1", "b2")]
+        want = oracle.predict(*a)
+        out = sp.predict(*[dev(x) for x in a])
+        torch.cuda.synchronize()
+        got = {k: host(v) for k, v in out.items()}
+    oracle.set_threads(1)
+    check_scored(got, want, 0.5, f"K={K} d={d} B={B} q4={q4}")
+
+
+@pytest.mark.parametrize("K,d,H", [(1, 520, 9), (2, 4104, 513), (3, 520, 100), (5, 4104, 512), (6, 520, 515), (7, 8200, 40)])
+def test_sweep_compiled_in_widths(sp, oracle, K, d, H):
+    """Odd H: the second layer's rows of W1 start off every alignment above that of their pieces."""
+    rng = np.random.default_rng(K)
+    L, B, V = 4, 3, 60
+    t = dict(hidden=rng.standard_normal((L, B, d)), gamma=1 + 0.05 * rng.standard_normal(d),
+             lm_head=0.05 * rng.standard_normal((V, d)), W1=0.1 * rng.standard_normal((L, H, 3 * K)),
+             w2=0.1 * rng.standard_normal((L, H)), b1=0.1 * rng.standard_normal((L, H)), b2=0.1 * rng.standard_normal(L))
+    t = {k: v.astype(np.float16) for k, v in t.items()}
+    ids = np.stack([rng.choice(V, K, replace=False) for _ in range(B)]).astype(np.int32)
+    active = np.array([1, 0, 1, 1], np.int32)
+    ref = oracle.predict_sweep(t["hidden"], t["gamma"], t["lm_head"], ids, t["W1"], t["w2"], t["b1"], t["b2"],
+                               active=active)
+    out = sp.predict_sweep(dev(t["hidden"]), dev(t["gamma"]), dev(t["lm_head"]), dev(ids), dev(t["W1"]), dev(t["w2"]),
+                           dev(t["b1"]), dev(t["b2"]), active=dev(active))
+    torch.cuda.synchronize()
+    got = {k: host(v) for k, v in out.items()}
+    on = active != 0
+    check_scored({k: got[k][on] for k in ("logits", "probs", "scores", "exit")},
+                 {k: ref[k][on] for k in ("logits", "probs", "scores", "exit")}, 0.5, f"sweep K={K}")
+    assert not got["scores"][1].any() and not got["exit"][1].any()
