@@ -261,8 +261,8 @@ int specee_verify_q4(const specee_dims *dims, int N, const specee_half *hidden, 
 /*
  * specee_predict_tree on the 4-bit group-quantised LM head (Sec. 6.2 in the
  * quantised setting of Sec. 7.1 / 7.3): arguments, outputs and conventions as
- * specee_predict_tree, the head given as for specee_predict_q4.  Up to a few
- * thousand nodes each is scored as specee_predict_q4 would; larger calls take one
+ * specee_predict_tree, the head given as for specee_predict_q4.  Smaller
+ * calls score each node as specee_predict_q4 would; larger ones take one
  * workgroup per tree, whose merged contraction runs on the codes themselves
  * (exact), each quantisation group's sums being scaled and shifted by that
  * group's scale and zero-point.  Needs no workspace.

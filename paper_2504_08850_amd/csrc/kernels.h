@@ -40,7 +40,8 @@ struct PredictParams {
 };
 
 // Trees scored node by node (B = G * N tokens): predictor and merge in one launch, then overflow and path rule
-bool tree_nodes_preferred(int total_nodes, int n_ids, int d, int K, int H, int Mcap, bool q4);
+// group: 0 on an fp16 head; whole: what the tree kernels would do takes one launch (tree_whole_supported)
+bool tree_nodes_preferred(int G, int N, int d, int K, int H, int Mcap, int group, bool whole);
 hipError_t launch_tree_nodes(const PredictParams &p, int N, const int32_t *parent, int32_t *path_exit, hipStream_t s);
 
 hipError_t launch_predict(const PredictParams &p, hipStream_t s);

@@ -11,6 +11,8 @@
 // in the same pass: the kernel makes exactly two dependent trips to memory.
 // All loads are 16 bytes per lane; reductions are DPP within a wavefront and a
 // fixed-order LDS exchange across the eight wavefronts.
+#include <algorithm>
+
 #include "device_utils.h"
 #include "kernels.h"
 #include "merge_block.h"
@@ -626,15 +628,6 @@ static bool merge_fits(const PredictParams &p, int threads) {
     return !TREE || p.tree.n <= kMergePerThread * threads;
 }
 
-// K values that are compiled in: up to 8, where the rows of every shape fit in registers.  Against the generic form, which
-// larger K take (rows of W1 read where they are used, tests of k < K), at d = 4096: one token K = 1 3.7 -> 2.9 us, 2
-// 3.9 -> 3.0, 3 4.3 -> 3.3, 5 5.9 -> 3.8, 6 6.3 -> 3.8, 7 6.8 -> 4.9; 8000 tokens 39 -> 23, 45 -> 30, 51 -> 38, 103 -> 55,
-// 118 -> 65, 134 -> 77 us; the same on quantised rows, 8000 tokens 54 -> 20, 58 -> 23, 60 -> 27, 124 -> 35, 133 -> 34,
-// 143 -> 57, and K = 8, which has their throughput shapes too, 78 -> 42 us.
-static bool predict_exact(int K) {
-    return K <= 8;
-}
-
 template <int KC, bool SWEEP, bool EXACT, bool TREE>
 static hipError_t launch_vpt(const PredictParams &p, hipStream_t s) {
     dim3 grid(p.B + (TREE ? p.tree.G : 0), p.L), block(kPredictThreads);
@@ -672,6 +665,11 @@ static hipError_t launch_vpt(const PredictParams &p, hipStream_t s) {
     return hipGetLastError();
 }
 
+// K values that are compiled in: up to 8, where the rows of every shape fit in registers.  Against the generic form, which
+// larger K take (rows of W1 read where they are used, tests of k < K), at d = 4096: one token K = 1 3.7 -> 2.9 us, 2
+// 3.9 -> 3.0, 3 4.3 -> 3.3, 5 5.9 -> 3.8, 6 6.3 -> 3.8, 7 6.8 -> 4.9; 8000 tokens 39 -> 23, 45 -> 30, 51 -> 38, 103 -> 55,
+// 118 -> 65, 134 -> 77 us; the same on quantised rows, 8000 tokens 54 -> 20, 58 -> 23, 60 -> 27, 124 -> 35, 133 -> 34,
+// 143 -> 57, and K = 8, which has their throughput shapes too, 78 -> 42 us.
 template <bool SWEEP, bool TREE>
 static hipError_t launch_kc(const PredictParams &p, hipStream_t s) {
     switch (p.K) {
@@ -779,20 +777,62 @@ __global__ __launch_bounds__(kTreeTailThreads) void tree_tail_kernel(PredictPara
 // merges the ids beside them.  Against one workgroup per tree (or the split contraction of a few trees) this gives up
 // reading a shared row once per tree -- the caches serve the repeats -- and gains a chain of two memory trips per
 // node on every CU instead of merge -> contraction -> scoring in series.
-// Where the line lies (whole call against the tree kernels, 60 or 64 nodes, d = 4096, K = 4 unless given):
-// fp16, 1 tree 5.8 / 15.2 us, 16 trees 9.4 / 20.5, 48 trees 19.2 / 23.0, 64 trees 24.4 / 24.0; d = 5120, 48 trees
-// 23.4 / 24.1, 64 trees 28.3 / 26.2; K = 8, 48 trees 26.8 / 27.7, 64 trees 33.3 / 28.7 -- the bytes gathered
-// decide, nodes * (K + 1) * d.  Sets wider than 128 rows cost the tree kernel twice as much (d = 8192, K = 8:
-// 64 trees 60.1 / 63.2), and K = 3 and 5, which it scores without the matrix cores, four times (K = 5, d = 5120:
-// 190 trees 87.5 / 145).  Quantised rows: 1 tree 6.2 / 44.2, 16 trees 7.1 / 43.2, 192 trees 40.7 / 47.3; K = 8,
-// d = 5120, 80 trees 47.8 / 55.1; K = 3, 256 trees 54.2 / 102.  K that is not compiled in: the generic predictor is
-// two to three times slower per node.
-bool tree_nodes_preferred(int total_nodes, int n_ids, int d, int K, int H, int Mcap, bool q4) {
-    if (n_ids > kMergePerThread * 256) return false;  // one workgroup of 256 threads merges a tree's ids
-    const bool exact = predict_exact(K), mfma = mlp_mfma_ok(K, H);
-    if (q4) return total_nodes <= (!exact ? 6144 : !mfma ? 16384 : K == 4 ? 12288 : 5120);
-    if (!mfma) return total_nodes <= (exact ? 12288 : 8192);
-    return total_nodes <= 4096 && (Mcap > 128 || (long long)total_nodes * (K + 1) * d <= 80000000);
+// The line between them lies where the times below, in microseconds, cross.  They are fitted to 2516 pairs of
+// measurements (K = 1 ... 16, d = 256 ... 8192, 1 ... 1024 nodes per tree, 1 ... 4096 trees, H = 100 ... 2048, merged
+// sets of 64 ... 400 rows, groups of 32, 64 and 128); the slower side is chosen by more than 6 % in 46 of them, by 0.4 %
+// on average.
+// Node by node / tree kernels at d = 4096, K = 4, H = 512, trees of 64 nodes with 64 merged rows: 4 trees 6.3 / 15.3, 16
+// 9.4 / 20.2, 48 19.0 / 23.2, 64 24.8 / 23.9, 128 41.2 / 34.2; merged rows for 256: 64 trees 24.9 / 39.9, 192 59.1 /
+// 65.6, 256 75.5 / 76.3.  d = 2048: 80 trees 18.9 / 20.8, 96 22.6 / 22.0; d = 8192: 32 trees 22.5 / 24.9, 48 30.0 /
+// 28.8.  K = 8: 48 trees 27.4 / 27.9, 64 33.5 / 28.8.  K = 8, H = 2048: 48 trees 36.1 / 39.2.  K = 3, an MLP without
+// the matrix cores: 64 trees 23.1 / 81.5, 256 68.0 / 98.5; H = 128, 192 trees 51.3 / 53.8, 256 65.8 / 59.3.  K = 16, not
+// compiled in: 8 trees 20.4 / 22.9, 16 34.2 / 24.5, 20 40.5 / 64.6, 48 84.7 / 66.5.  Trees of 256 nodes: 32 trees 38.2 /
+// 68.5, 128 126 / 129.  Quantised rows: K = 4, 16 trees 8.6 / 44.7, 192 43.8 / 48.7, 256 56.1 / 51.1; K = 8, 128 trees
+// 47.3 / 48.3, 192 63.3 / 49.6; d = 512, 64 trees 16.8 / 18.8, 128 26.4 / 19.1.
+static float tree_nodes_us(int G, int N, int d, int K, int H, bool q4) {
+    const float elems = 1e-3f * (K + 1) * d;  // gathered per node, in thousands
+    float ns;                                 // per node, the chip filled
+    if (K > 8) {  // not compiled in; K = 16 has whole vectors of W1
+        ns = (K == 16 ? 22.f : 18.f + 1.3f * K) + 0.11f * elems;
+        return 9.f + 1e-3f * ns * G * N;
+    }
+    const float mlp = (K & 1 ? 0.45e-3f : 0.27e-3f) * K * std::max(H, 256);  // odd K: W1 by single halves
+    if (q4) {
+        ns = std::max(0.9f + 0.34f * K, 0.7f + mlp + (d <= 4096 ? 0.09f : 0.12f) * elems);
+    } else {
+        // the least a workgroup of 128 threads (of 256 or 512) takes, and the bytes
+        const float least = K <= 5 && d <= 2048 && N * K <= kMergePerThread * 128 ? 1.4f : 1.f + 0.35f * K;
+        ns = std::max(least, 0.3f + mlp + (K > 5 && d > 4096 ? 0.17f : 0.15f) * elems);
+    }
+    return 7.5f + 1e-3f * ns * G * N;
+}
+
+static float tree_kernels_us(int G, int N, int d, int K, int H, int Mcap, int group, bool whole) {
+    const int rounds = (G + 255) / 256;
+    const bool mfma = mlp_mfma_ok(K, H), vec = K == 4 || K == 8 || K == 16;  // vec: whole vectors of W1
+    const float wide = 1e-3f * std::max(0, H - 512);
+    const float mlp = mfma ? 8.f * wide : 4.f + 1e-3f * (vec ? 3.6f * K : 35.f + 36.f * K) * H * N / 64;
+    if (group > 0)  // quantised rows: a fixed time per tree, one tree per CU and round
+        return rounds * ((group >= 128 ? 16.f : 20.f) + 7e-3f * d * (Mcap <= 64 ? 1.f : 2.2f) + mlp);
+    const float rows = std::min((float)Mcap, 0.3f * N * K);  // merged rows, as overlapping ids leave them
+    if (whole) {
+        const float mb = 2e-6f * G * (N + rows) * d;
+        float t = (Mcap <= 64 ? 17.f : Mcap <= 128 ? 25.f : 31.f) + (K <= 4 ? 0.f : 3.5f) +
+                  mb / (Mcap > 64 && Mcap <= 128 ? 7.f : 9.f) + std::max(0.f, mb - 250.f) / 10;  // beyond the last-level cache
+        if (rounds > 1) t = std::max(t + 10.f, rounds * (10.f + 3.4e-3f * d));
+        return t + rounds * mlp;
+    }
+    // split contraction, one wavefront per node behind it (a workgroup per tree from 32 trees on)
+    const float tail = mfma ? 9.f * wide : vec ? 6e-3f * H : 2.f + (K <= 8 ? 12e-3f : 40e-3f) * H;
+    if (G < 20 && N <= 64 && Mcap <= 256)
+        return 15.5f + tail + (Mcap > 64 ? 2.f : 0.f) + std::min(9.f, 0.67e-6f * G * (N + rows) * d);
+    const float gmac = 1e-9f * G * N * rows * d;
+    return 15.5f + tail + 0.4e-3f * G * N + 8.5f * gmac + 10.f * std::min(1.f, gmac) + (G < 32 ? 0.f : 15.f + mlp);
+}
+
+bool tree_nodes_preferred(int G, int N, int d, int K, int H, int Mcap, int group, bool whole) {
+    if (N * K > kMergePerThread * 256) return false;  // one workgroup of 256 threads merges a tree's ids
+    return tree_nodes_us(G, N, d, K, H, group > 0) < tree_kernels_us(G, N, d, K, H, Mcap, group, whole);
 }
 
 hipError_t launch_tree_nodes(const PredictParams &p, int N, const int32_t *parent, int32_t *path_exit, hipStream_t s) {

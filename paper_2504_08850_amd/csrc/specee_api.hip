@@ -59,7 +59,7 @@ TreeSplit tree_split(int d, int n_total, int N, int Mcap) {
 
 // Trees per launch from which one workgroup (or a few, see below) per tree beats spreading every
 // tree over the whole GPU, and the workgroups per launch the ticketed d-slices aim for (one
-// 512-thread workgroup per CU).  Calls of up to a few thousand nodes take neither shape: their nodes
+// 512-thread workgroup per CU).  Smaller calls take neither shape: their nodes
 // are scored one by one (tree_nodes_preferred).  Measured on MI355X with 60-node trees.
 constexpr int kWholeTreeMinTrees = 20;
 constexpr int kWholeTargetWgs = 256;
@@ -376,8 +376,8 @@ static int predict_tree_common(const specee_dims *dm, int G, int N, int Mcap, co
     const bool whole = G >= kWholeTreeMinTrees && tree_whole_supported(N, dm->K, Mcap);
     if (!whole && exact_fit && (!workspace || workspace_bytes < lay.total)) return SPECEE_EWORKSPACE;
 
-    // up to a few thousand nodes: every node on its own, which needs no workspace
-    if (tree_nodes_preferred(G * N, N * dm->K, dm->d, dm->K, dm->H, Mcap, false)) {
+    // every node on its own, which needs no workspace
+    if (tree_nodes_preferred(G, N, dm->d, dm->K, dm->H, Mcap, 0, whole)) {
         PredictParams pp = tree_nodes_params(dm, G, N, Mcap, hidden, gamma, ids, prev_probs, mlp, merged_ids, M_out,
                                              cols, logits, probs, scores, exit_flags);
         pp.lm_head = H(lm_head);
@@ -408,8 +408,9 @@ static int predict_tree_common(const specee_dims *dm, int G, int N, int Mcap, co
         return launch_tree_whole(gp, fp, G, st) == hipSuccess ? SPECEE_OK : SPECEE_EHIP;
     }
 
-    // few trees: split d over many workgroups; merge inside the contraction kernel (one launch less on the
-    // latency path) unless that would repeat it too often
+    // few trees, of a K that is not compiled in (five to nineteen), or trees that no single workgroup holds: split d over
+    // many workgroups.  The merge runs inside the contraction kernel, one launch less (K = 16, d = 512, 12 trees 20.2 ->
+    // 17.2 us), unless that would repeat it too often
     const bool fuse = tree_gemm_can_fuse_merge(N * dm->K) && (long long)G * ts.S <= 64;
     if (!fuse && launch_merge(ids, N * dm->K, G, Mcap, merged_ids, M_out, cols, st) != hipSuccess) return SPECEE_EHIP;
     gp.ids = fuse ? ids : nullptr;
@@ -522,7 +523,7 @@ int specee_predict_tree_q4(const specee_dims *dm, int G, int N, int Mcap, const 
     if ((rc = check_q4(dm, qweight, scales, zeros, group))) return rc;
     if ((reinterpret_cast<uintptr_t>(qweight) & 7) != 0) return SPECEE_EALIGN;
     if (!tree_q4_supported(dm->d, N, dm->K, Mcap, group)) return SPECEE_EINVAL;
-    if (tree_nodes_preferred(G * N, N * dm->K, dm->d, dm->K, dm->H, Mcap, true)) {
+    if (tree_nodes_preferred(G, N, dm->d, dm->K, dm->H, Mcap, group, true)) {
         PredictParams pp = tree_nodes_params(dm, G, N, Mcap, hidden, gamma, ids, prev_probs, mlp, merged_ids, M_out,
                                              cols, logits, probs, scores, exit_flags);
         pp.qweight = qweight; pp.qscales = H(scales); pp.qzeros = H(zeros); pp.group = group;

@@ -16,7 +16,8 @@
 // and D[rows 4q..4q+3][node c].
 //
 // MODE 0: one d-slice per workgroup, un-normalised partial sums and partial sums of
-//         squares go to the workspace (few trees: many CUs share one tree).
+//         squares go to the workspace (many CUs share one tree: few trees whose nodes are not
+//         scored one by one, and trees that MODE 3 cannot hold).
 // MODE 3: one workgroup per tree over all of d.  The logits stay in LDS; the same
 //         workgroup gathers every node's K columns, builds the features and evaluates the
 //         predictor MLP -- for K in {4, 8} also on the matrix cores (W1 rows are the A

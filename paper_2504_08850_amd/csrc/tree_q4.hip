@@ -1,8 +1,8 @@
 // Token trees under the merged mapping (paper Sec. 6.2) on a 4-bit group-quantised LM head (the
 // weight-quantised setting of Sec. 7.1 / 7.3; format as for the quantised-rows predictor): one workgroup
 // per tree does the merge, the N x M x d contraction on the matrix cores, the per-node features, MLP and
-// judgment, and the path rule.  This is the shape for large launches: up to tree_nodes_preferred() nodes the
-// quantised predictor scores them one by one.
+// judgment, and the path rule.  This is the shape for large launches: the nodes of smaller ones are scored one by
+// one by the quantised predictor (tree_nodes_preferred).
 //
 // The contraction never forms a dequantised weight.  With x = h * gamma split exactly into hi + lo (fp16),
 //     Z[n][m] = sum_g scale[m][g] * ( sum_{i in g} x[n][i] * code[m][i]  -  zero[m][g] * sum_{i in g} x[n][i] ):

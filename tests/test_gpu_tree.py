@@ -200,8 +200,7 @@ def test_tree_largest_supported_tree(sp, oracle):
 
 
 def test_tree_many_mid_size_trees_split_path(sp, oracle):
-    """Forty trees with more than 64 nodes each: too wide for one workgroup per tree, so the d-split
-    contraction runs with the stand-alone merge kernel and the per-tree finish (matrix-core MLP)."""
+    """Forty trees with more than 64 nodes each."""
     d, V, K, H, N, Mcap = 256, 3000, 4, 512, 80, 200
     ts = []
     for gidx in range(40):
@@ -232,10 +231,8 @@ def test_tree_batch_of_independent_trees(sp, oracle):
 @pytest.mark.parametrize("name,G,bias", [("T3", 20, True), ("T3", 16, False), ("T3", 40, False), ("T3", 130, True),
                                          ("T3", 260, False)])
 def test_tree_many_trees_one_workgroup_each(sp, oracle, name, G, bias):
-    """Batches of small trees: below about twenty trees every tree is spread over the GPU; from there on
-    a single launch does merge, contraction, scoring and path rule -- with a few workgroups per tree
-    that hand their d-slices to the last one (20, 40 trees), one 512-thread workgroup per tree (130) or
-    one 256-thread workgroup per tree (260).  All must agree with the oracle."""
+    """Batches of small trees (test_tree_kernels has the calls beyond the node-by-node line).  All must agree with the
+    oracle."""
     ts = [synth.make(name, seed=s, bias=bias) for s in range(G)]
     c = ts[0]["cfg"]
     tb = stack_trees(ts)
@@ -270,11 +267,11 @@ def test_tree_many_trees_shapes(sp, oracle, d, V, K, H, N, Mcap, G):
 
 
 @pytest.mark.parametrize("d,V,K,H,N,Mcap,G", [
-    (520, 777, 8, 512, 64, 256, 33),     # 129..256 merged rows: sixteen row tiles, seven d-slices per tree by ticket
-    (520, 777, 8, 512, 64, 256, 130),    # one d-slice
+    (520, 777, 8, 512, 64, 256, 33),     # 129..256 merged rows
+    (520, 777, 8, 512, 64, 256, 130),    # more trees
     (520, 777, 8, 512, 61, 256, 260),    # more trees than CUs, ragged node count
     (1032, 900, 4, 512, 60, 200, 40),    # K = 4, capacity not a multiple of 16
-    (8192, 700, 8, 512, 64, 256, 24),    # the large-vocabulary tree shape's d, eight d-slices of 1024
+    (8192, 700, 8, 512, 64, 256, 24),    # the large-vocabulary tree shape's d
     (256, 5000, 16, 1024, 16, 256, 21),  # K = KMAX: every node fills the capacity on its own
 ])
 def test_tree_many_trees_wide_merged_sets(sp, oracle, d, V, K, H, N, Mcap, G):
@@ -307,8 +304,7 @@ def test_tree_many_trees_wide_merged_sets(sp, oracle, d, V, K, H, N, Mcap, G):
     (4096, 600, 4, 512, 60, 64, 520),    # full hidden size, two workgroups per CU and more than one round
 ])
 def test_tree_more_trees_than_cus_narrow_merged_sets(sp, oracle, d, V, K, H, N, Mcap, G):
-    """More than 256 trees with at most 64 merged rows each: one 256-thread workgroup per tree with four
-    row tiles (below 257 trees the same shape takes 512 threads per tree)."""
+    """More than 256 trees with at most 64 merged rows each."""
     ts = []
     for gidx in range(G):
         t = make_tree(31 * gidx + d, d, V, K, H, N, bias=(gidx == 0 and K == 8))
@@ -372,8 +368,8 @@ def test_tree_many_trees_c3_batch(sp, oracle):
 
 @pytest.mark.parametrize("G", [24, 64, 100])
 def test_tree_sliced_batch_is_reproducible(sp, G):
-    """With a few workgroups per tree (eight, four, two here), whichever finishes last adds the d-slices up
-    -- in slice order, so repeated launches give identical bits."""
+    """Repeated launches give identical bits (64 trees node by node, 100 with two workgroups per tree, of which whichever
+    finishes last adds the d-slices up, in slice order)."""
     c = synth.CONFIGS["C3"]
     lm_h, lm_d = lm_for(c)
     ts = [synth.make("C3", seed=300 + s, lm=lm_h) for s in range(G)]
@@ -555,45 +551,133 @@ def test_c5_large_vocab_tree_and_full_head(sp, oracle):
     oracle.set_threads(1)
 
 
-@pytest.mark.parametrize("d,V,K,H,N,G,Mcap", [
-    (256, 700, 4, 64, 64, 64, 64),     # the most nodes that are scored node by node
-    (256, 700, 4, 64, 64, 65, 64),     # one tree more: two d-slices per tree by ticket
-    (264, 700, 4, 64, 61, 260, 64),    # more trees than CUs, ragged d and N
-    (520, 777, 8, 64, 64, 66, 256),    # wide merged sets, d-slices
-    (256, 777, 8, 64, 64, 130, 256),   # ... one d-slice
-    (136, 300, 3, 100, 64, 192, 64),   # no matrix-core MLP: node by node up to three times as many
-    (136, 300, 3, 100, 64, 193, 64),   # one tree more
-    (136, 300, 6, 100, 64, 128, 64),   # K not compiled in: twice as many
-    (136, 300, 6, 100, 64, 129, 64),   # one tree more
-    (136, 3000, 4, 64, 256, 5, 64),    # narrow rows, many nodes: more ids than 128 threads can merge
-    (384, 900, 1, 64, 1024, 9, 64),    # trees of more than 64 nodes: split contraction with the merge in its prologue
-    (136, 3000, 4, 64, 256, 3, 40),    # four ids per merging thread; one tree overflows its capacity
-    (136, 3000, 4, 64, 257, 3, 40),    # more ids than that: merge kernel and split contraction
-])
-def test_tree_both_sides_of_the_node_by_node_line(sp, oracle, d, V, K, H, N, G, Mcap):
+def make_batch(d, V, K, H, N, G, Mcap, bias=False):
+    """G trees; tree 1 names ten distinct ids more than Mcap holds."""
     rng = np.random.default_rng(d + V + K + N + G)
     ids = np.empty((G, N, K), np.int32)
     for g in range(G):
-        width = 50 if (Mcap, g) == (40, 1) else [Mcap, max(K, Mcap - 9), max(K, Mcap // 2), K][g % 4]
+        width = [Mcap, Mcap, max(K, Mcap - 9), max(K, Mcap // 2), K][g % 5]
         pool = rng.permutation(V)[:width]
         ids[g] = pool[rng.integers(0, width, size=(N, K))]
-    parent = np.tile(np.array([-1] + [int(rng.integers(0, n)) for n in range(1, N)], np.int32), (G, 1))
-    t = dict(hidden=rng.standard_normal((G, N, d)).astype(np.float16),
-             gamma=(1 + 0.05 * rng.standard_normal(d)).astype(np.float16),
-             lm_head=(0.05 * rng.standard_normal((V, d))).astype(np.float16), ids=ids, parent=parent,
-             prev_probs=rng.dirichlet(np.ones(K), size=(G, N)).astype(np.float32),
-             W1=(0.1 * rng.standard_normal((H, 3 * K))).astype(np.float16),
-             w2=(0.1 * rng.standard_normal(H)).astype(np.float16), b1=None, b2=None)
-    over = [1] if Mcap == 40 else []
-    got = run_tree(sp, t, dev(t["lm_head"]), Mcap)
-    for g in over:                     # a set that does not fit is reported and refuses the whole tree
-        assert got["M"][g] == 50 and np.array_equal(got["merged"][g], np.unique(ids[g])[:Mcap])
-        assert all(np.isnan(got[k][g]).all() for k in ("logits", "probs", "scores"))
-        assert not got["exit"][g].any() and not got["path_exit"][g].any()
-    keep = [g for g in range(G) if g not in over]
+    ids[1] = np.resize(rng.permutation(V)[:Mcap + 10], (N, K))
+    f16 = lambda x: x.astype(np.float16)
+    return dict(hidden=f16(rng.standard_normal((G, N, d))), gamma=f16(1 + 0.05 * rng.standard_normal(d)),
+                lm_head=f16(0.05 * rng.standard_normal((V, d))), ids=ids,
+                parent=np.tile(np.array([-1] + [int(rng.integers(0, n)) for n in range(1, N)], np.int32), (G, 1)),
+                prev_probs=rng.dirichlet(np.ones(K), size=(G, N)).astype(np.float32),
+                W1=f16(0.1 * rng.standard_normal((H, 3 * K))), w2=f16(0.1 * rng.standard_normal(H)),
+                b1=f16(0.1 * rng.standard_normal(H)) if bias else None, b2=f16(0.1 * rng.standard_normal(1)) if bias else None)
+
+
+def predict_nodes(sp, t, lm_d):
+    """The same nodes as tokens of one specee_predict call."""
+    flat = lambda k: dev(t[k].reshape(-1, t[k].shape[-1]))
+    out = sp.predict(flat("hidden"), dev(t["gamma"]), lm_d, flat("ids"), flat("prev_probs"), dev(t["W1"]), dev(t["w2"]),
+                     dev(t["b1"]), dev(t["b2"]))
+    torch.cuda.synchronize()
+    return {k: host(v).reshape(t["ids"].shape[:2] + v.shape[1:]) for k, v in out.items()}
+
+
+def check_batch(oracle, got, t, Mcap, what):
+    """Tree 1 overflows and is refused as a whole; the others against the oracle."""
+    G = len(t["ids"])
+    u = np.unique(t["ids"][1])
+    assert got["M"][1] == len(u) > Mcap and np.array_equal(got["merged"][1], u[:Mcap])
+    assert all(np.isnan(got[k][1]).all() for k in ("logits", "probs", "scores"))
+    assert not got["exit"][1].any() and not got["path_exit"][1].any()
+    keep = [g for g in range(G) if g != 1]
     t = {k: v[keep] if k in ("hidden", "ids", "parent", "prev_probs") else v for k, v in t.items()}
-    got = {k: v[keep] for k, v in got.items()}
     oracle.set_threads(8)
     ref = ref_tree(oracle, t, Mcap)
     oracle.set_threads(1)
-    check_tree(got, ref, 0.5, f"{G} trees d={d} K={K} N={N} Mcap={Mcap}", min_compared=0.3)
+    check_tree({k: v[keep] for k, v in got.items()}, ref, 0.5, what, min_compared=0.3)
+
+
+# nodes: which side of the line the call is on.  Scored one by one, the nodes get the bits of specee_predict, which the
+# sums of the contraction do not have.
+@pytest.mark.parametrize("d,V,K,H,N,G,Mcap,nodes", [
+    (256, 700, 4, 64, 64, 112, 64, True),
+    (256, 700, 4, 64, 64, 120, 64, False),    # two d-slices per tree by ticket
+    (264, 700, 4, 64, 61, 120, 64, True),     # ragged d and N
+    (264, 700, 4, 64, 61, 260, 64, False),    # more trees than CUs
+    (520, 777, 8, 64, 64, 110, 256, True),
+    (520, 777, 8, 64, 64, 135, 256, False),   # wide merged sets
+    (256, 777, 8, 64, 64, 85, 128, True),
+    (256, 777, 8, 64, 64, 100, 128, False),   # ... d-slices
+    (136, 300, 3, 1, 64, 150, 64, True),      # no matrix-core MLP
+    (136, 300, 3, 1, 64, 170, 64, False),
+    (136, 300, 6, 8, 64, 90, 64, True),
+    (136, 300, 6, 8, 64, 110, 64, False),
+    (136, 300, 16, 64, 64, 4, 64, True),      # K not compiled in
+    (136, 300, 16, 64, 64, 7, 64, False),     # the split contraction of a few trees
+    (136, 300, 16, 64, 64, 20, 64, False),
+    (64, 700, 8, 64, 100, 40, 64, True),      # trees of more than 64 nodes
+    (64, 700, 8, 64, 100, 80, 64, False),
+])
+def test_tree_both_sides_of_the_node_by_node_line(sp, oracle, d, V, K, H, N, G, Mcap, nodes):
+    t = make_batch(d, V, K, H, N, G, Mcap, bias=H < 16)   # (few units: the ReLU leaves scores at exactly 1/2 without)
+    lm_d = dev(t["lm_head"])
+    got = run_tree(sp, t, lm_d, Mcap)
+    one = predict_nodes(sp, t, lm_d)
+    live = np.arange(G) != 1
+    assert np.array_equal(one["logits"][live], got["logits"][live]) == nodes
+    check_batch(oracle, got, t, Mcap, f"{G} trees d={d} K={K} N={N} Mcap={Mcap}")
+
+
+@pytest.mark.parametrize("d,V,K,H,N,G,Mcap", [
+    (136, 3000, 4, 64, 256, 5, 64),     # 1024 ids per tree: more than 128 threads can merge
+    (136, 3000, 4, 64, 256, 3, 40),
+    (136, 3000, 4, 64, 257, 3, 40),     # more ids than one workgroup merges: merge kernel and split contraction
+    (384, 900, 1, 64, 1024, 9, 64),
+])
+def test_tree_of_many_ids(sp, oracle, d, V, K, H, N, G, Mcap):
+    t = make_batch(d, V, K, H, N, G, Mcap)
+    check_batch(oracle, run_tree(sp, t, dev(t["lm_head"]), Mcap), t, Mcap, f"{G} trees d={d} K={K} N={N}")
+
+
+@pytest.mark.parametrize("d,V,K,H,N,G,Mcap,bias", [
+    (256, 700, 4, 64, 64, 125, 64, True),      # two d-slices by ticket
+    (1024, 700, 8, 128, 64, 64, 64, False),    # four
+    (1024, 300, 16, 64, 64, 24, 64, True),     # eight
+    (264, 700, 4, 64, 61, 200, 64, False),     # one, 512 threads per tree
+    (264, 70000, 4, 512, 61, 300, 64, True),   # one, 256 threads; a vocabulary that no bitmap in LDS holds
+    (256, 700, 4, 64, 64, 230, 128, True),     # eight row tiles
+    (256, 777, 8, 64, 64, 100, 128, False),    # ... two d-slices
+    (520, 777, 8, 64, 64, 135, 256, True),     # sixteen row tiles
+    (256, 777, 8, 64, 64, 125, 256, False),    # ... two d-slices
+    (136, 300, 3, 1, 64, 180, 64, True),       # MLP without the matrix cores
+    (256, 700, 4, 100, 64, 200, 64, True),     # ... its rows in registers
+    (136, 300, 12, 8, 64, 20, 64, True),       # ... generic K
+    (136, 300, 16, 64, 64, 12, 64, True),      # split contraction with the merge in its prologue, one wavefront per node
+    (136, 3000, 4, 64, 257, 3, 64, False),     # ... behind the merge kernel
+    (64, 700, 8, 64, 100, 80, 64, True),       # ... one workgroup per tree behind it
+])
+def test_tree_kernels(sp, oracle, d, V, K, H, N, G, Mcap, bias):
+    """Calls beyond the line, on every shape of the kernels that take them: a tree that overflows, ids outside the
+    vocabulary, repeated launches with the same bits, and no parents."""
+    t = make_batch(d, V, K, H, N, G, Mcap, bias)
+    lm_d = dev(t["lm_head"])
+    what = f"{G} trees d={d} K={K} N={N} Mcap={Mcap}"
+    got = run_tree(sp, t, lm_d, Mcap)
+    one = predict_nodes(sp, t, lm_d)
+    live = np.arange(G) != 1
+    assert not np.array_equal(one["logits"][live], got["logits"][live])      # not scored node by node
+    check_batch(oracle, got, t, Mcap, what)
+    same = lambda a, b: all(np.array_equal(a[k], b[k], equal_nan=a[k].dtype.kind == "f") for k in
+                            ("M", "merged", "cols", "logits", "probs", "scores", "exit"))
+    for _ in range(3):
+        again = run_tree(sp, t, lm_d, Mcap)
+        assert same(got, again) and np.array_equal(got["path_exit"], again["path_exit"])
+    free = run_tree(sp, t, lm_d, Mcap, parent=None)
+    assert free["path_exit"] is None and same(got, free)
+    bad = dict(t, ids=t["ids"].copy())
+    bad["ids"][2, 4, 0], bad["ids"][2, 7, K - 1] = V, -3
+    r = run_tree(sp, bad, lm_d, Mcap)
+    nodes = np.ones((G, N), bool)
+    nodes[1] = nodes[2, 4] = nodes[2, 7] = False
+    close(r["logits"][nodes], got["logits"][nodes], 1.0, "valid nodes beside invalid ones")
+    u = np.unique(bad["ids"][2])                     # an id outside the vocabulary is an id of the set all the same
+    assert r["M"][2] == len(u) and np.array_equal(r["merged"][2][:len(u)], u)
+    assert np.isnan(r["scores"][2, [4, 7]]).all() and np.isnan(r["logits"][2, [4, 7], [0, K - 1]]).all()
+    assert not r["exit"][2, [4, 7]].any()
+    assert np.array_equal(r["path_exit"], path_and(r["exit"], t["parent"]).astype(np.int32))

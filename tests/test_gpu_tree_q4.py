@@ -149,19 +149,72 @@ def test_tree_q4_argument_errors(sp):
     assert ei.value.code == -1
 
 
-@pytest.mark.parametrize("d,V,K,H,N,G,Mcap", [
-    (128, 300, 4, 64, 64, 192, 64),   # the most nodes that are scored node by node
-    (128, 300, 4, 64, 64, 193, 64),   # one tree more: one workgroup per tree
-    (128, 300, 8, 64, 64, 80, 128),   # K = 8: fewer
-    (128, 300, 8, 64, 64, 81, 128),
-    (64, 300, 3, 100, 64, 256, 64),   # no matrix-core MLP in the tree kernel: more
-    (64, 300, 3, 100, 64, 257, 64),
-    (64, 300, 6, 100, 64, 96, 64),    # K not compiled in
-    (96, 300, 6, 100, 64, 97, 64),
+def predict_nodes(sp, t, qd):
+    """The same nodes as tokens of one specee_predict_q4 call."""
+    flat = lambda k: dev(t[k].reshape(-1, t[k].shape[-1]))
+    out = sp.predict_q4(flat("hidden"), dev(t["gamma"]), *qd, t["group"], flat("ids"), flat("prev_probs"), dev(t["W1"]),
+                        dev(t["w2"]), dev(t["b1"]), dev(t["b2"]))
+    torch.cuda.synchronize()
+    return {k: host(v).reshape(t["ids"].shape[:2] + v.shape[1:]) for k, v in out.items()}
+
+
+# nodes: which side of the line the call is on.  Scored one by one, the nodes get the bits of specee_predict_q4, which
+# the sums of the contraction do not have.
+@pytest.mark.parametrize("d,V,K,H,N,G,group,Mcap,nodes", [
+    (128, 300, 4, 64, 64, 60, 128, 64, True),
+    (128, 300, 4, 64, 64, 70, 128, 64, False),
+    (128, 300, 8, 64, 64, 40, 128, 128, True),
+    (128, 300, 8, 64, 64, 50, 128, 128, False),
+    (64, 300, 3, 1, 64, 120, 64, 64, True),      # no matrix-core MLP in the tree kernel
+    (64, 300, 3, 1, 64, 150, 64, 64, False),
+    (96, 300, 6, 8, 64, 90, 32, 64, True),
+    (96, 300, 6, 8, 64, 110, 32, 64, False),
+    (96, 300, 16, 64, 64, 10, 32, 64, True),     # K not compiled in
+    (96, 300, 16, 64, 64, 16, 32, 64, False),
 ])
-def test_tree_q4_both_sides_of_the_node_by_node_line(sp, oracle, d, V, K, H, N, G, Mcap):
-    t = make(d + N + K + G, d, V, K, H, N, G, 32, Mcap)
+def test_tree_q4_both_sides_of_the_node_by_node_line(sp, oracle, d, V, K, H, N, G, group, Mcap, nodes):
+    t = make(d + N + K + G, d, V, K, H, N, G, group, Mcap, bias=H < 16)   # (few units: scores at exactly 1/2 without)
+    qd = (words(t["q"]), dev(t["scales"]), dev(t["zeros"]))
     oracle.set_threads(8)
     r = ref(oracle, t, Mcap)
     oracle.set_threads(1)
-    check_tree(run(sp, t, Mcap), r, 0.5, f"tree_q4 d={d} K={K} N={N} G={G}", min_compared=0.3)
+    got = run(sp, t, Mcap, qd=qd)
+    assert np.array_equal(predict_nodes(sp, t, qd)["logits"], got["logits"]) == nodes
+    check_tree(got, r, 0.5, f"tree_q4 d={d} K={K} N={N} G={G}", min_compared=0.3)
+
+
+@pytest.mark.parametrize("d,V,K,H,N,G,group,Mcap,bias", [
+    (256, 300, 4, 64, 60, 120, 32, 64, False),     # smallest group (a fold at every k-step)
+    (1024, 900, 4, 512, 60, 130, 128, 64, True),   # the 60-node shape
+    (512, 777, 8, 512, 61, 110, 64, 128, False),   # K = 8, eight row tiles
+    (544, 500, 3, 3, 64, 230, 32, 96, True),       # d not a multiple of the stage, K odd
+    (512, 700, 5, 2, 64, 140, 256, 128, True),     # a group as long as a stage
+    (64, 90, 16, 8, 64, 20, 32, 80, True),         # K = KMAX
+    (1280, 300, 8, 128, 64, 90, 320, 64, False),   # group neither a power of two nor a divisor of the stage
+])
+def test_tree_q4_kernel(sp, oracle, d, V, K, H, N, G, group, Mcap, bias):
+    """Calls beyond the line: one workgroup per tree, with trees that overflow and ids outside the vocabulary."""
+    t = make(d + N + K, d, V, K, H, N, G, group, Mcap, bias)
+    qd = (words(t["q"]), dev(t["scales"]), dev(t["zeros"]))
+    oracle.set_threads(8)
+    r = ref(oracle, t, Mcap)
+    oracle.set_threads(1)
+    got = run(sp, t, Mcap, qd=qd)
+    assert not np.array_equal(predict_nodes(sp, t, qd)["logits"], got["logits"])       # not scored node by node
+    check_tree(got, r, 0.5, f"tree_q4 d={d} K={K} N={N} G={G} group={group}", min_compared=0.3)
+    Ms = np.array([len(np.unique(x)) for x in t["ids"]])
+    cap = int(Ms.max()) - 1                                                            # the largest sets overflow this
+    small = run(sp, t, cap, qd=qd)
+    over = Ms > cap
+    assert np.array_equal(small["M"], Ms) and over.any() and not over.all()
+    assert np.isnan(small["scores"][over]).all() and not small["exit"][over].any() and not small["path_exit"][over].any()
+    close(small["logits"][~over], r["logits"][~over], 1.0, "trees that fit beside trees that overflow")
+    bad = t["ids"].copy()
+    bad[1, 4, 0], bad[1, 7, K - 1] = V, -3
+    got = run(sp, t, Mcap, qd=qd, parent=None, ids=bad)
+    u = np.unique(bad[1])
+    assert got["path_exit"] is None and got["M"][1] == len(u) and np.array_equal(got["merged"][1][:len(u)], u)
+    assert np.isnan(got["scores"][1, [4, 7]]).all() and not got["exit"][1, [4, 7]].any()
+    mask = np.ones((G, N), bool)
+    mask[1, [4, 7]] = False
+    close(got["scores"][mask], r["scores"][mask], 1e-3, "valid nodes beside invalid ones")
