@@ -15,6 +15,7 @@
 
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <tuple>
 #include <utility>
@@ -203,5 +204,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", "Argument marshalling o
 }  // namespace
 
 PyMODINIT_FUNC PyInit__binding(void) {
-    return PyModule_Create(&module);
+    PyObject *m = PyModule_Create(&module);
+    // what this file was compiled against: tensors of another version may be laid out differently
+    if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
 }

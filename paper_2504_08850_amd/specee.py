@@ -16,6 +16,7 @@ _PKG = Path(__file__).resolve().parent
 LIB_PATH = _PKG / "libspecee.so"
 _lib = None
 _binding = None
+_REBUILD = "build it with `python -m paper_2504_08850_amd.build` (it takes g++ and torch's headers beside hipcc)"
 
 OP_PREDICT, OP_PREDICT_SWEEP, OP_PREDICT_TREE, OP_LM_HEAD, OP_VERIFY, OP_LAYER_LOOP, OP_VERIFY_Q4, \
     OP_PREDICT_TREE_Q4 = range(8)
@@ -66,8 +67,13 @@ def _call():
         lib()
         path = _PKG / "_binding.so"
         if not path.exists():
-            raise FileNotFoundError(f"{path} is missing: build it with `python -m paper_2504_08850_amd.build`")
-        from . import _binding as native
+            raise FileNotFoundError(f"{path} is missing: {_REBUILD}")
+        try:
+            from . import _binding as native
+        except ImportError as e:  # symbols of another torch
+            raise ImportError(f"{path} does not load with torch {torch.__version__}: {_REBUILD}") from e
+        if native.torch_version != torch.__version__.split("+")[0]:
+            raise ImportError(f"{path} was built against torch {native.torch_version}, not {torch.__version__}: {_REBUILD}")
         _binding = native
     return _binding
 

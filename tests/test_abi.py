@@ -166,3 +166,13 @@ def test_native_marshalling_refuses_what_the_library_must_not_see(sp):
         call.specee_predict(*empty)
     with pytest.raises(TypeError):                                   # dimensions that are no tuple of six
         call.specee_predict((8, 1), *empty[1:], 0)
+
+
+def test_native_marshalling_belongs_to_one_torch(sp, monkeypatch):
+    import torch
+    native = sp._call()
+    assert native.torch_version == torch.__version__.split("+")[0]
+    monkeypatch.setattr(sp, "_binding", None)
+    monkeypatch.setattr(native, "torch_version", "1.0.0")
+    with pytest.raises(ImportError, match="was built against torch 1.0.0"):
+        sp._call()
