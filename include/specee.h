@@ -210,7 +210,7 @@ int specee_predict_tree_static(const specee_dims *dims, int G, int N, int Mcap, 
  * dims->K and dims->H are ignored.  Workspace: SPECEE_OP_LM_HEAD with n = N.
  * A single hidden state is taken to find the head in HBM, as in a decode loop
  * whose layers' weights pass through the last-level cache between two calls (here,
- * in specee_verify and for the first verification of a token in specee_layer_loop).
+ * in specee_verify and for a token's first verification in specee_layer_loop).
  */
 int lm_head_gemv(const specee_dims *dims, int N, const specee_half *hidden, const specee_half *gamma,
                  const specee_half *lm_head, float *out, void *workspace, size_t workspace_bytes, void *stream);

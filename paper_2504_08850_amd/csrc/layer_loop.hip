@@ -38,6 +38,7 @@ struct LoopRare {
     int32_t *cand_idx, *arrive, *abort;
     long long spin_limit;
 };
+constexpr int kLoopStreamFirst = 4;  // verifications of a token that read the head with the hint under STREAM = 2
 constexpr int kLoopMaskLds = 1024;  // layers of the active mask kept in LDS (deeper stacks read the rest in place)
 
 // KC / EXACT / VPT as in predict_kernel.  KEEP: the K rows stay in registers across layers (up to 64
@@ -46,7 +47,7 @@ constexpr int kLoopMaskLds = 1024;  // layers of the active mask kept in LDS (de
 // 2 = quantised head read word by word.  On a quantised head the token's K rows are dequantised once, into
 // the float registers that hold them anyway (with the RMSNorm weight folded in), so the predictor of a layer is
 // the same code; the verification streams the codes (q4_head_rows).  Needs KEEP (K <= 8).
-// STREAM: verifications that read the head with the non-temporal hint -- 0 none, 1 all, 2 a token's first.
+// STREAM: verifications that read the head with the non-temporal hint -- 0 none, 1 all, 2 a token's first four.
 template <int KC, int VPT, bool EXACT, int STREAM, int HEAD = 0>
 __global__ __launch_bounds__(kLoopThreads) void layer_loop_kernel(LoopParams p) {
     constexpr bool KEEP = KC * VPT <= 16 && KC <= 8;
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(kLoopThreads) void layer_loop_kernel(LoopParams p) 
                                         }
                                     });
         } else {
-            if (STREAM == 1 || (STREAM == 2 && meetings == 0))
+            if (STREAM == 1 || (STREAM == 2 && meetings < kLoopStreamFirst))
                 head_argmax_rows<true>(p.lm_head, d, row_begin, row_end, wave, kLoopWaves, lane, xa, xb, r, bv, bi);
             else
                 head_argmax_rows<false>(p.lm_head, d, row_begin, row_end, wave, kLoopWaves, lane, xa, xb, r, bv, bi);
@@ -461,18 +462,18 @@ __global__ void layer_loop_empty_kernel(int32_t *exit_layer, int32_t *token, int
 template <int KC, int VPT, bool EXACT>
 static hipError_t launch_loop_one(LoopParams p, int max_wgs, hipStream_t s) {
     constexpr bool kCanQ4 = KC * VPT <= 16 && KC <= 8;
-    // A token's later verifications re-read the head, as several states do.  Back to back, 32 verifications without the
-    // hint / with it always / for the first only: 262 MB 1416 / 1430 / 1416 us, 205 MB 1169 / 1234 / 1171, 164 MB
-    // 982 / 1011 / 983; one verification of a head from HBM: 60.4 / 54.9 / 54.6, 53.1 / 48.7 / 48.6, 46.0 / 42.2 /
-    // 41.9 us.  What the first pass leaves out of the cache the second has to fetch: two of them, from HBM, 105.3 / 100.4
-    // / 106.4, 90.4 / 87.0 / 92.2, 77.3 / 74.5 / 78.9 us.  Wider shapes have no registers for a second copy of the
-    // streaming loop (K = 8, d > 4096: 25 -> 54 spilled) and read a head that the cache can keep without the hint.
-    void (*kern)(LoopParams) = layer_loop_kernel<KC, VPT, EXACT, 0>;
-    if (head_streams(p.d, p.V, 2)) {
-        kern = layer_loop_kernel<KC, VPT, EXACT, 1>;
-    } else if constexpr (KC * VPT <= 8) {
-        if (head_streams(p.d, p.V, p.B)) kern = layer_loop_kernel<KC, VPT, EXACT, 2>;
-    }
+    // A token's later verifications re-read the head, and of a head well below the size of the last-level cache they
+    // would find more there without the hint; but the first of them that goes without has to fetch what the hint kept
+    // out.  So such a head is read with it by a token's first four verifications (most tokens make one or two).  Without
+    // the hint / always / first four, head from HBM: 205 MB, 1 verification 52.8 / 48.3 / 48.3 us, 2 90.2 / 86.9 / 86.8,
+    // 4 163 / 164 / 164, 5 199 / 203 / 210, 8 308 / 318 / 320, 32 1182 / 1244 / 1194; 164 MB, 1 46.2 / 42.2 / 41.9, 4 141 /
+    // 139 / 139, 8 265 / 269 / 274, 32 1007 / 1049 / 1016.  At 262 MB, about the size of that cache, the hint is as good
+    // or better for any number (1 60.5 / 54.9, 8 382 / 374, 32 1479 / 1465 us; on another box 32 took 1431 / 1462).
+    // Wider shapes have no registers for a second copy of the streaming loop (K = 8, d > 4096: 25 -> 54 spilled).
+    const bool stream = head_streams(p.d, p.V, p.B);
+    void (*kern)(LoopParams) = stream ? layer_loop_kernel<KC, VPT, EXACT, 1> : layer_loop_kernel<KC, VPT, EXACT, 0>;
+    if constexpr (KC * VPT <= 8)
+        if (stream && (size_t)p.V * p.d * sizeof(half_t) <= ((size_t)224 << 20)) kern = layer_loop_kernel<KC, VPT, EXACT, 2>;
     size_t lds = (size_t)p.d * sizeof(float);
     int quantum = kLoopWaves * kHeadRows;
     if (p.qweight) {

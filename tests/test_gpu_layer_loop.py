@@ -327,14 +327,13 @@ def test_layer_loop_compiled_in_widths(sp, oracle, seed, K, d, H):
 
 
 def test_layer_loop_rereads_a_head_of_134_mb(sp, oracle):
-    """One token, a head above the line of the non-temporal hint: the first verification reads it with the hint, the
-    later ones without; two vectors per thread (the 262 MB head of the 7B shape above has one)."""
-    t, plant = loop_inputs(1, 8192, 8200, 4, 512, 4, 1, [3], False)
+    """One token, six verifications of a head above the line of the non-temporal hint: four with it, two without."""
+    t, plant = loop_inputs(2, 8192, 8200, 4, 512, 6, 1, [5], False)
     t = plant_hits(oracle, t, plant)
     oracle.set_threads(8)
     ref = check_loop(oracle, sp, t, -1.0, what="134 MB head")
     oracle.set_threads(1)
-    assert ref["exit"].sum() == 4 and ref["exit_layer"][0] == 3
+    assert ref["exit"].sum() == 6 and ref["exit_layer"][0] == 5
 
 
 @pytest.mark.parametrize("seed,K,d,H", [(0, 1, 520, 9), (0, 2, 4104, 513), (0, 6, 520, 515), (0, 7, 4104, 40)])
