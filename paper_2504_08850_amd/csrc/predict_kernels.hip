@@ -777,10 +777,10 @@ __global__ __launch_bounds__(kTreeTailThreads) void tree_tail_kernel(PredictPara
 // merges the ids beside them.  Against one workgroup per tree (or the split contraction of a few trees) this gives up
 // reading a shared row once per tree -- the caches serve the repeats -- and gains a chain of two memory trips per
 // node on every CU instead of merge -> contraction -> scoring in series.
-// The line between them lies where the times below, in microseconds, cross.  They are fitted to 2516 pairs of
+// The line between them lies where the times below, in microseconds, cross.  They are fitted to 2958 pairs of
 // measurements (K = 1 ... 16, d = 256 ... 8192, 1 ... 1024 nodes per tree, 1 ... 4096 trees, H = 100 ... 2048, merged
-// sets of 64 ... 400 rows, groups of 32, 64 and 128); the slower side is chosen by more than 6 % in 46 of them, by 0.4 %
-// on average.
+// sets of 64 ... 400 rows, groups of 32, 64 and 128, rows in the last-level cache or from HBM); the slower side is chosen
+// by more than 6 % in 58 of them, by 0.4 % on average.
 // Node by node / tree kernels at d = 4096, K = 4, H = 512, trees of 64 nodes with 64 merged rows: 4 trees 6.3 / 15.3, 16
 // 9.4 / 20.2, 48 19.0 / 23.2, 64 24.8 / 23.9, 128 41.2 / 34.2; merged rows for 256: 64 trees 24.9 / 39.9, 192 59.1 /
 // 65.6, 256 75.5 / 76.3.  d = 2048: 80 trees 18.9 / 20.8, 96 22.6 / 22.0; d = 8192: 32 trees 22.5 / 24.9, 48 30.0 /
@@ -818,7 +818,7 @@ static float tree_kernels_us(int G, int N, int d, int K, int H, int Mcap, int gr
     if (whole) {
         const float mb = 2e-6f * G * (N + rows) * d;
         float t = (Mcap <= 64 ? 17.f : Mcap <= 128 ? 25.f : 31.f) + (K <= 4 ? 0.f : 3.5f) +
-                  mb / (Mcap > 64 && Mcap <= 128 ? 7.f : 9.f) + std::max(0.f, mb - 250.f) / 10;  // beyond the last-level cache
+                  mb / (Mcap <= 64 ? 9.f : 7.5f) + std::max(0.f, mb - 250.f) / 10;  // beyond the last-level cache
         if (rounds > 1) t = std::max(t + 10.f, rounds * (10.f + 3.4e-3f * d));
         return t + rounds * mlp;
     }
