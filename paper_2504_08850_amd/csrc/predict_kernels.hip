@@ -618,9 +618,14 @@ __global__ void first_exit_kernel(const int32_t *exit_flags, int L, int B, int32
 }
 
 constexpr int kBatchMinTokens = 1024;  // tokens per launch from which the throughput shapes are used
-// The same on quantised rows, whose workgroups of 128 threads pay earlier (d = 4096, K = 4: 128 tokens 4.2 us either
-// way, 512 tokens 5.9 -> 5.5, 900 tokens 8.4 -> 5.8 us; d = 5120: 128 tokens 5.0 -> 4.5, 900 tokens 10.8 -> 8.2 us).
-constexpr int kQ4BatchMinTokens = 128;
+// The same on quantised rows, whose small workgroups pay earlier.  In chunks of 32 elements, K >= 3 (d = 4096, K = 4: 128
+// tokens 4.2 us either way, 512 tokens 5.9 -> 5.5, 900 tokens 8.4 -> 5.8 us; d = 5120: 128 tokens 5.0 -> 4.5, 900 tokens
+// 10.8 -> 8.2 us); K <= 2, with fewer rows to unpack (K = 2: 128 tokens 3.7 -> 3.9, 400 tokens 4.8 either way, 900 tokens
+// 6.7 -> 5.2 us); word by word (d = 4104, K = 4 / 8: 128 tokens 5.0 -> 5.3 / 6.6 -> 6.9, 512 tokens 7.1 -> 7.0 / 10.2 ->
+// 9.7 us).
+constexpr int q4_batch_min_tokens(int K, bool wide) {
+    return !wide ? 512 : K <= 2 ? 400 : 128;
+}
 
 // A tree's ids are merged by one workgroup of the launch, at most kMergePerThread of them per thread.
 template <bool TREE>
@@ -701,19 +706,20 @@ static hipError_t launch_q4_kc(const PredictParams &p, hipStream_t s) {
         // chunks of 32 elements per thread when the format allows it (group % 32 == 0, rows 16-byte aligned):
         // B=8000 at d=4096: 37 -> 29 us, at d=8192: 71 -> 58 us
         const bool wide_ok = p.group % 32 == 0 && p.d % 32 == 0 && (reinterpret_cast<uintptr_t>(p.qweight) & 15) == 0;
-        if (wide_ok && p.B >= kQ4BatchMinTokens && p.d <= 32 * 128 && merge_fits<TREE>(p, 128)) {
+        const bool batch = p.B >= q4_batch_min_tokens(KC, wide_ok);
+        if (wide_ok && batch && p.d <= 32 * 128 && merge_fits<TREE>(p, 128)) {
             hipLaunchKernelGGL((predict_q4_wide_kernel<KC, 128, 1, 4, TREE>), grid, dim3(128), lds, s, p);
             return hipGetLastError();
         }
-        if (wide_ok && p.B >= kQ4BatchMinTokens && p.d <= 32 * 256) {
+        if (wide_ok && batch && p.d <= 32 * 256) {
             hipLaunchKernelGGL((predict_q4_wide_kernel<KC, 256, 1, 2, TREE>), grid, dim3(256), lds, s, p);
             return hipGetLastError();
         }
-        if (p.B >= kQ4BatchMinTokens && nv <= 4 * 128 && merge_fits<TREE>(p, 128)) {
+        if (batch && nv <= 4 * 128 && merge_fits<TREE>(p, 128)) {
             hipLaunchKernelGGL((predict_q4_kernel<KC, 4, true, 128, 4, TREE>), grid, dim3(128), lds, s, p);
             return hipGetLastError();
         }
-        if (p.B >= kQ4BatchMinTokens && nv <= 4 * 256) {
+        if (batch && nv <= 4 * 256) {
             hipLaunchKernelGGL((predict_q4_kernel<KC, 4, true, 256, 2, TREE>), grid, dim3(256), lds, s, p);
             return hipGetLastError();
         }

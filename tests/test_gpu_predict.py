@@ -410,7 +410,7 @@ def test_predict_compiled_in_widths(sp, oracle, q4, K, d, B):
 
 
 @pytest.mark.parametrize("q4", [False, True])
-@pytest.mark.parametrize("K,d,B", [(1, 1056, 129), (2, 2048, 1024), (6, 1056, 1030), (7, 5120, 130), (9, 1056, 129)])
+@pytest.mark.parametrize("K,d,B", [(1, 1056, 129), (1, 5120, 400), (2, 2048, 399), (2, 2048, 1024), (6, 1056, 1030), (7, 5120, 130), (9, 1056, 129)])
 def test_predict_other_widths(sp, oracle, q4, K, d, B):
     """The other K that are compiled in, rows of W1 in pieces of one and two halves, and the first that is not."""
     from test_gpu_q4 import case, ref, run

@@ -178,3 +178,13 @@ def test_q4_argument_errors(sp):
             sp.predict_q4(dev(t["hidden"]), dev(t["gamma"]), qd[0], dev(np.ones((20, 64 // group), np.float16)),
                           dev(np.ones((20, 64 // group), np.float16)), group, dev(t["ids"]), dev(t["prev_probs"]),
                           dev(t["W1"]), dev(t["w2"]))
+
+
+@pytest.mark.parametrize("d,K,B,group", [(1040, 4, 511, 104), (1040, 4, 512, 104), (4104, 8, 512, 24), (8200, 2, 512, 8)])
+def test_q4_word_path_on_both_sides_of_the_throughput_line(sp, oracle, d, K, B, group):
+    """Formats without chunks of 32 elements: workgroups of 512 threads, then of 128 and 256, and rows too long for those."""
+    t = case(d + K + B, d, 201, K, 500, B, group, True)
+    oracle.set_threads(8)
+    r = ref(oracle, t)
+    oracle.set_threads(1)
+    check_scored(run(sp, t), r, 0.5, f"q4 words d={d} K={K} B={B}")
