@@ -462,18 +462,19 @@ __global__ void layer_loop_empty_kernel(int32_t *exit_layer, int32_t *token, int
 template <int KC, int VPT, bool EXACT>
 static hipError_t launch_loop_one(LoopParams p, int max_wgs, hipStream_t s) {
     constexpr bool kCanQ4 = KC * VPT <= 16 && KC <= 8;
-    // A token's later verifications re-read the head, and of a head well below the size of the last-level cache they
-    // would find more there without the hint; but the first of them that goes without has to fetch what the hint kept
-    // out.  So such a head is read with it by a token's first four verifications (most tokens make one or two).  Without
-    // the hint / always / first four, head from HBM: 205 MB, 1 verification 52.8 / 48.3 / 48.3 us, 2 90.2 / 86.9 / 86.8,
-    // 4 163 / 164 / 164, 5 199 / 203 / 210, 8 308 / 318 / 320, 32 1182 / 1244 / 1194; 164 MB, 1 46.2 / 42.2 / 41.9, 4 141 /
-    // 139 / 139, 8 265 / 269 / 274, 32 1007 / 1049 / 1016.  At 262 MB, about the size of that cache, the hint is as good
-    // or better for any number (1 60.5 / 54.9, 8 382 / 374, 32 1479 / 1465 us; on another box 32 took 1431 / 1462).
-    // Wider shapes have no registers for a second copy of the streaming loop (K = 8, d > 4096: 25 -> 54 spilled).
+    // A token's later verifications re-read the head, and without the hint they find some of it in the last-level cache;
+    // but the first of them that goes without has to fetch what the hint kept out.  So a head that this cache can keep is
+    // read with the hint by a token's first four verifications (most tokens make one or two).  Without the hint / always /
+    // first four, head from HBM: 262 MB, 1 verification 60.5 / 54.9 / 54.9 us, 2 106.7 / 100.9 / 100.9, 4 198.7 / 192.2 /
+    // 192.0, 5 244.5 / 236.8 / 245.6, 8 382 / 374 / 383, 32 1479 / 1465 / 1481 (on two other boxes 1431 / 1462 and, back to
+    // back, 1465 / 1519); 205 MB, 1 52.8 / 48.3 / 48.3, 4 163 / 164 / 164, 5 199 / 203 / 210, 8 308 / 318 / 320, 32 1182 /
+    // 1244 / 1194; 164 MB, 1 46.2 / 42.2 / 41.9, 4 141 / 139 / 139, 8 265 / 269 / 274, 32 1007 / 1049 / 1016.
+    // Wider shapes have no registers for a second copy of the streaming loop (K = 8, d > 4096: 25 -> 54 spilled) and
+    // keep the hint.
     const bool stream = head_streams(p.d, p.V, p.B);
     void (*kern)(LoopParams) = stream ? layer_loop_kernel<KC, VPT, EXACT, 1> : layer_loop_kernel<KC, VPT, EXACT, 0>;
     if constexpr (KC * VPT <= 8)
-        if (stream && (size_t)p.V * p.d * sizeof(half_t) <= ((size_t)224 << 20)) kern = layer_loop_kernel<KC, VPT, EXACT, 2>;
+        if (stream && !head_streams(p.d, p.V, 2)) kern = layer_loop_kernel<KC, VPT, EXACT, 2>;
     size_t lds = (size_t)p.d * sizeof(float);
     int quantum = kLoopWaves * kHeadRows;
     if (p.qweight) {
