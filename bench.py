@@ -729,7 +729,7 @@ def main():
                                                 "frac_of_8TBps": b1 / us1 / 1e3 / HBM_PEAK_GBS}
         extra["c5_tree_N64_V128256"]["speedup_vs_full_head_N64"] = us64 / us_tree
         # throughput mode for this shape: G trees per launch (merged sets of ~140 rows: sixteen row tiles per
-        # workgroup, d-slices by ticket below 256 trees), two batches in rotation
+        # workgroup; 64 trees are scored node by node), two batches in rotation
         for G in (64, 256):
             batches, bytes_tree = [], 0
             for b in range(2):
