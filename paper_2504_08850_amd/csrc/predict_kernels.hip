@@ -40,6 +40,22 @@ __device__ __forceinline__ void merge_one_tree(const TreeMergeParams &m, int g) 
     }
 }
 
+// Workgroups are dealt to the eight XCDs in turn, by their number in the launch.  The nodes of a launch of trees are
+// numbered so that each XCD gets one consecutive eighth of them: the nodes of a tree then share an L2, and a row that
+// several of them name is fetched into it once, instead of into up to eight of them (64 nodes, d = 4096, K = 4: 32 trees
+// 14.6 -> 12.2 us, 64 24.8 -> 21.8; K = 8, d = 8192, 64 trees 59.9 -> 53.2; quantised rows, 64 trees 19.2 -> 18.6).  The
+// merge workgroups come first, padded to a multiple of eight.  Returns this workgroup's node, or -1 if it has none.
+constexpr int kXcds = 8;
+__host__ __device__ __forceinline__ int tree_merge_wgs(int G) {
+    return (G + kXcds - 1) / kXcds * kXcds;
+}
+__device__ __forceinline__ int tree_node(int G, int nodes) {
+    const int j = (int)blockIdx.x - tree_merge_wgs(G);
+    const int per = (nodes + kXcds - 1) / kXcds;
+    const int b = (j % kXcds) * per + j / kXcds;
+    return b < nodes ? b : -1;
+}
+
 // KC: speculative rows held in flight (K <= KC).  VPT: 16-byte vectors per
 // thread per row (d/8 <= VPT * 512 * tiles).  SWEEP: the previous layer's local
 // probabilities are recomputed from that layer's hidden state instead of read,
@@ -55,10 +71,12 @@ __device__ __forceinline__ void merge_one_tree(const TreeMergeParams &m, int g) 
 // TREE: the tokens are the nodes of p.tree.G trees; the first p.tree.G workgroups merge the trees' ids.
 template <int KC, int VPT, bool SWEEP, bool EXACT, int T = kPredictThreads, int MU = 1, bool TREE = false>
 __global__ __launch_bounds__(T) void predict_kernel(PredictParams p) {
-    if (TREE && (int)blockIdx.x < p.tree.G) {
-        merge_one_tree<T>(p.tree, blockIdx.x);
+    if (TREE && (int)blockIdx.x < tree_merge_wgs(p.tree.G)) {
+        if ((int)blockIdx.x < p.tree.G) merge_one_tree<T>(p.tree, blockIdx.x);
         return;
     }
+    const int b = TREE ? tree_node(p.tree.G, p.B) : (int)blockIdx.x;
+    if (TREE && b < 0) return;
     constexpr int kWaves = T / kWave;
     // throughput shape: hidden states pass through once, so they are read with the non-temporal hint; the
     // LM-head rows are not -- tokens of a batch share rows, and the hint costs those re-reads their cache
@@ -71,7 +89,6 @@ __global__ __launch_bounds__(T) void predict_kernel(PredictParams p) {
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = tid >> 6;
-    const int b = TREE ? (int)blockIdx.x - p.tree.G : (int)blockIdx.x;
     const int l = blockIdx.y;
     const int K = EXACT ? KC : p.K, H = p.H, d = p.d;
     const int nv = d >> 3;
@@ -355,15 +372,16 @@ __device__ __forceinline__ void q4_tail(const PredictParams &p, int b, int K, fl
 // and turn the K rows into K serial trips to memory; unused data is zeroed by selects instead.
 template <int KC, int VPT, bool EXACT, int T = kPredictThreads, int MU = 1, bool TREE = false>
 __global__ __launch_bounds__(T) void predict_q4_kernel(PredictParams p) {
-    if (TREE && (int)blockIdx.x < p.tree.G) {
-        merge_one_tree<T>(p.tree, blockIdx.x);
+    if (TREE && (int)blockIdx.x < tree_merge_wgs(p.tree.G)) {
+        if ((int)blockIdx.x < p.tree.G) merge_one_tree<T>(p.tree, blockIdx.x);
         return;
     }
+    const int b = TREE ? tree_node(p.tree.G, p.B) : (int)blockIdx.x;
+    if (TREE && b < 0) return;
     constexpr int kWaves = T / kWave;
     __shared__ float red[kWaves][KC + 1];
     __shared__ float red_u[kWaves];
     const int tid = threadIdx.x;
-    const int b = TREE ? (int)blockIdx.x - p.tree.G : (int)blockIdx.x;
     const int K = EXACT ? KC : p.K, H = p.H, d = p.d;
     const int nv = d >> 3, ng = d / p.group;
 
@@ -488,16 +506,17 @@ __global__ __launch_bounds__(T) void predict_q4_kernel(PredictParams p) {
 // what a CU runs out of first with rows this short.  CPT: chunks per thread (d <= 32 * T * CPT).
 template <int KC, int T, int CPT, int MU, bool TREE = false>
 __global__ __launch_bounds__(T) void predict_q4_wide_kernel(PredictParams p) {
-    if (TREE && (int)blockIdx.x < p.tree.G) {
-        merge_one_tree<T>(p.tree, blockIdx.x);
+    if (TREE && (int)blockIdx.x < tree_merge_wgs(p.tree.G)) {
+        if ((int)blockIdx.x < p.tree.G) merge_one_tree<T>(p.tree, blockIdx.x);
         return;
     }
+    const int b = TREE ? tree_node(p.tree.G, p.B) : (int)blockIdx.x;
+    if (TREE && b < 0) return;
     constexpr int kWaves = T / kWave;
     constexpr int K = KC;
     __shared__ float red[kWaves][KC + 1];
     __shared__ float red_u[kWaves];
     const int tid = threadIdx.x;
-    const int b = TREE ? (int)blockIdx.x - p.tree.G : (int)blockIdx.x;
     const int H = p.H, d = p.d;
     const int nc = d >> 5, nv = d >> 3, ng = d / p.group;
 
@@ -627,6 +646,11 @@ constexpr int q4_batch_min_tokens(int K, bool wide) {
     return !wide ? 512 : K <= 2 ? 400 : 128;
 }
 
+// Workgroups of a launch of trees: the merges, and eight equal shares of the nodes.
+static int tree_wgs(const PredictParams &p) {
+    return tree_merge_wgs(p.tree.G) + (p.B + kXcds - 1) / kXcds * kXcds;
+}
+
 // A tree's ids are merged by one workgroup of the launch, at most kMergePerThread of them per thread.
 template <bool TREE>
 static bool merge_fits(const PredictParams &p, int threads) {
@@ -635,7 +659,7 @@ static bool merge_fits(const PredictParams &p, int threads) {
 
 template <int KC, bool SWEEP, bool EXACT, bool TREE>
 static hipError_t launch_vpt(const PredictParams &p, hipStream_t s) {
-    dim3 grid(p.B + (TREE ? p.tree.G : 0), p.L), block(kPredictThreads);
+    dim3 grid(TREE ? tree_wgs(p) : p.B, p.L), block(kPredictThreads);
     const size_t lds = TREE ? (size_t)merge_lds_ints(p.tree.n) * sizeof(int32_t) : 0;
     const int nv = p.d >> 3;
     if constexpr (!SWEEP && EXACT && KC <= 8) {
@@ -696,7 +720,7 @@ hipError_t launch_predict(const PredictParams &p, hipStream_t s) {
 
 template <int KC, bool EXACT, bool TREE>
 static hipError_t launch_q4_kc(const PredictParams &p, hipStream_t s) {
-    const dim3 grid(p.B + (TREE ? p.tree.G : 0)), block(kPredictThreads);
+    const dim3 grid(TREE ? tree_wgs(p) : p.B), block(kPredictThreads);
     const size_t lds = TREE ? (size_t)merge_lds_ints(p.tree.n) * sizeof(int32_t) : 0;
     const int nv = p.d >> 3;
     if constexpr (EXACT && KC <= 8) {
@@ -786,15 +810,15 @@ __global__ __launch_bounds__(kTreeTailThreads) void tree_tail_kernel(PredictPara
 // The line between them lies where the times below, in microseconds, cross.  They are fitted to 2958 pairs of
 // measurements (K = 1 ... 16, d = 256 ... 8192, 1 ... 1024 nodes per tree, 1 ... 4096 trees, H = 100 ... 2048, merged
 // sets of 64 ... 400 rows, groups of 32, 64 and 128, rows in the last-level cache or from HBM); the slower side is chosen
-// by more than 6 % in 58 of them, by 0.4 % on average.
-// Node by node / tree kernels at d = 4096, K = 4, H = 512, trees of 64 nodes with 64 merged rows: 4 trees 6.3 / 15.3, 16
-// 9.4 / 20.2, 48 19.0 / 23.2, 64 24.8 / 23.9, 128 41.2 / 34.2; merged rows for 256: 64 trees 24.9 / 39.9, 192 59.1 /
-// 65.6, 256 75.5 / 76.3.  d = 2048: 80 trees 18.9 / 20.8, 96 22.6 / 22.0; d = 8192: 32 trees 22.5 / 24.9, 48 30.0 /
-// 28.8.  K = 8: 48 trees 27.4 / 27.9, 64 33.5 / 28.8.  K = 8, H = 2048: 48 trees 36.1 / 39.2.  K = 3, an MLP without
-// the matrix cores: 64 trees 23.1 / 81.5, 256 68.0 / 98.5; H = 128, 192 trees 51.3 / 53.8, 256 65.8 / 59.3.  K = 16, not
-// compiled in: 8 trees 20.4 / 22.9, 16 34.2 / 24.5, 20 40.5 / 64.6, 48 84.7 / 66.5.  Trees of 256 nodes: 32 trees 38.2 /
-// 68.5, 128 126 / 129.  Quantised rows: K = 4, 16 trees 8.6 / 44.7, 192 43.8 / 48.7, 256 56.1 / 51.1; K = 8, 128 trees
-// 47.3 / 48.3, 192 63.3 / 49.6; d = 512, 64 trees 16.8 / 18.8, 128 26.4 / 19.1.
+// by more than 6 % in 69 of them, by 0.4 % on average.
+// Node by node / tree kernels at d = 4096, K = 4, H = 512, trees of 64 nodes with 64 merged rows: 4 trees 6.4 / 15.3, 16
+// 8.9 / 20.2, 48 16.9 / 23.2, 64 21.8 / 23.9, 80 25.7 / 26.0, 128 37.6 / 34.2; merged rows for 256: 64 trees 22.7 / 39.9,
+// 192 53.5 / 65.6, 256 69.1 / 76.3.  d = 2048: 80 trees 16.3 / 20.8, 128 24.6 / 24.0; d = 8192: 32 trees 19.4 / 24.9, 48
+// 27.1 / 28.8, 64 34.4 / 34.3.  K = 8: 48 trees 23.8 / 27.9, 64 30.3 / 28.8.  K = 8, H = 2048: 48 trees 32.1 / 39.2.
+// K = 3, an MLP without the matrix cores: 64 trees 21.0 / 81.5, 256 65.5 / 98.5; H = 128, 192 trees 47.9 / 53.8, 256
+// 62.0 / 59.3.  K = 16, not compiled in: 8 trees 20.5 / 22.9, 16 33.0 / 24.5, 20 39.3 / 64.6, 48 83.1 / 66.5.  Trees of
+// 256 nodes: 32 trees 37.0 / 68.5, 128 120 / 129.  Quantised rows: K = 4, 16 trees 8.7 / 44.7, 192 41.9 / 48.7, 256
+// 52.5 / 51.2; K = 8, 128 trees 44.6 / 48.3, 192 61.0 / 49.6; d = 512, 64 trees 16.9 / 18.8, 128 26.5 / 19.2.
 static float tree_nodes_us(int G, int N, int d, int K, int H, bool q4) {
     const float elems = 1e-3f * (K + 1) * d;  // gathered per node, in thousands
     float ns;                                 // per node, the chip filled
@@ -804,11 +828,11 @@ static float tree_nodes_us(int G, int N, int d, int K, int H, bool q4) {
     }
     const float mlp = (K & 1 ? 0.45e-3f : 0.27e-3f) * K * std::max(H, 256);  // odd K: W1 by single halves
     if (q4) {
-        ns = std::max(0.9f + 0.34f * K, 0.7f + mlp + (d <= 4096 ? 0.09f : 0.12f) * elems);
+        ns = std::max(0.9f + 0.34f * K, 0.7f + mlp + (d <= 4096 ? 0.08f : 0.11f) * elems);
     } else {
         // the least a workgroup of 128 threads (of 256 or 512) takes, and the bytes
         const float least = K <= 5 && d <= 2048 && N * K <= kMergePerThread * 128 ? 1.4f : 1.f + 0.35f * K;
-        ns = std::max(least, 0.3f + mlp + (K > 5 && d > 4096 ? 0.17f : 0.15f) * elems);
+        ns = std::max(least, 0.3f + mlp + (K > 5 && d > 4096 ? 0.16f : 0.13f) * elems);
     }
     return 7.5f + 1e-3f * ns * G * N;
 }

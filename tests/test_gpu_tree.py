@@ -624,6 +624,19 @@ def test_tree_both_sides_of_the_node_by_node_line(sp, oracle, d, V, K, H, N, G, 
     check_batch(oracle, got, t, Mcap, f"{G} trees d={d} K={K} N={N} Mcap={Mcap}")
 
 
+@pytest.mark.parametrize("N,G", [(1, 1), (7, 1), (8, 1), (9, 1), (3, 5), (61, 9)])
+def test_tree_nodes_shared_out_over_the_xcds(sp, N, G):
+    """Fewer nodes than XCDs, one per XCD, shares that do not come out even: every node is scored, as its own token."""
+    t = make_batch(264, 300, 4, 64, N, max(G, 2), 64)
+    t = {k: v[:G] if k in ("hidden", "ids", "parent", "prev_probs") else v for k, v in t.items()}
+    t["ids"] %= 40                                    # (no merged set overflows)
+    lm_d = dev(t["lm_head"])
+    got, one = run_tree(sp, t, lm_d, 64), predict_nodes(sp, t, lm_d)
+    for k in ("logits", "probs", "scores", "exit"):
+        assert np.array_equal(got[k], one[k]), k
+    assert [int(m) for m in got["M"]] == [len(np.unique(i)) for i in t["ids"]]
+
+
 @pytest.mark.parametrize("d,V,K,H,N,G,Mcap", [
     (136, 3000, 4, 64, 256, 5, 64),     # 1024 ids per tree: more than 128 threads can merge
     (136, 3000, 4, 64, 256, 3, 40),
