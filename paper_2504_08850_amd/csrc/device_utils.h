@@ -71,12 +71,17 @@ __device__ __forceinline__ void dpp_argmax_step(float &v, int &i) {
     }
 }
 
-// Arg-max over a wavefront, lowest index on ties; every lane returns the winner.
-__device__ __forceinline__ void wave_argmax(float &v, int &i) {
+// Arg-max over 16 lanes (a DPP row), lowest index on ties; every lane returns its row's winner.
+__device__ __forceinline__ void row16_argmax(float &v, int &i) {
     dpp_argmax_step<kDppXor1>(v, i);
     dpp_argmax_step<kDppXor2>(v, i);
     dpp_argmax_step<kDppHalfMirror>(v, i);
     dpp_argmax_step<kDppMirror>(v, i);
+}
+
+// Arg-max over a wavefront, lowest index on ties; every lane returns the winner.
+__device__ __forceinline__ void wave_argmax(float &v, int &i) {
+    row16_argmax(v, i);
 #pragma unroll
     for (int off = 16; off <= 32; off <<= 1) {
         float ov = __shfl_xor(v, off, kWave);

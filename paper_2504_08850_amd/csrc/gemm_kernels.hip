@@ -36,12 +36,12 @@ constexpr int kLdsRow = kKC + 8;  // halves per LDS row: 144 bytes, keeps 16-byt
 // PD: stages of global loads kept in flight per wavefront.  The stage loop is free of
 // branches (loads past the end are issued on clamped addresses and contribute zeros): a load
 // under a branch makes the compiler drain every outstanding load at the join.
-// NT: n-tiles of 16 hidden states per workgroup.
+// NT: n-tiles of 16 hidden states per workgroup, two or four.
 template <int TPW, int MODE, int PD, int NT>
 // (two wavefronts per SIMD asked for: unbounded, the 256-row shape took 272 registers, i.e. one workgroup per CU)
 __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmParams p) {
     constexpr int kNB = 16 * NT;                 // hidden states per workgroup
-    constexpr int HV = kNB > 32 ? kNB / 32 : 1;  // vectors of x per thread and stage (NT = 1: two threads per vector)
+    constexpr int HV = kNB / 32;                 // vectors of x per thread and stage
     __shared__ __attribute__((aligned(16))) half_t lds_hi[2][kNB][kLdsRow];
     __shared__ __attribute__((aligned(16))) half_t lds_lo[2][kNB][kLdsRow];
     __shared__ float lds_ssq[kNB];
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
         rowptr[tp] = p.lm_head + (size_t)m * d;
     }
     // ---- B side: this thread stages vector column vc of hidden states r0 (and r0+32)
-    const int vc = tid & 7, r0 = (tid >> 3) & (kNB < 32 ? kNB - 1 : 31);
+    const int vc = tid & 7, r0 = tid >> 3;
     const half_t *hptr[HV];
     bool hok[HV];
 #pragma unroll
@@ -259,15 +259,13 @@ static int lm_head_tpw(int V) {
 
 // Measured on MI355X (N = 16..64): 256-row tiles with two stages in flight for large vocabularies
 // (4.9 TB/s at 128256 x 8192), 128-row tiles with four stages for 32000-row heads (4.3-4.4 TB/s).
-// Up to 32 hidden states the 128-row tiles carry one or two n-tiles instead of four: less of x to build, read back and
-// multiply per stage (head from HBM: 32000 x 4096, N = 16 68.3 -> 59.7 us, N = 32 71.0 -> 63.7 us; 50280 x 2048 60.5 ->
-// 58.4 us).  The 256-row tiles do not gain (128256 x 8192, N = 16: 409 -> 418 us) and keep four.
+// Up to 32 hidden states the 128-row tiles carry two n-tiles instead of four: less of x to build, read back and multiply
+// per stage (head from HBM: 32000 x 4096, N = 32 71.0 -> 63.7 us).  The 256-row tiles do not gain and keep four.  Up to 16
+// states, and more of them on a small head, go to head_states.hip.
 template <int MODE>
 static hipError_t launch_stream(const GemmParams &p, hipStream_t st) {
     if (lm_head_tpw(p.V) == 4)
         launch_one<MODE, 4, 2, 4>(p, st);
-    else if (p.N <= 16)
-        launch_one<MODE, 2, 4, 1>(p, st);
     else if (p.N <= 32)
         launch_one<MODE, 2, 4, 2>(p, st);
     else

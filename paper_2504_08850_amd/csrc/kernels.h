@@ -178,7 +178,7 @@ hipError_t launch_lm_head_q4_argmax(int d, int V, float eps, int N, const half_t
                                     float *best_val, int32_t *best_idx, const int32_t *gate, const int32_t *done,
                                     hipStream_t s);
 
-// The same for several hidden states on the matrix cores, 16 states per pass over the codes (lm_head_q4_mfma.hip)
+// The same for several hidden states on the matrix cores, for groups that head_states.hip does not do (lm_head_q4_mfma.hip)
 bool lm_head_q4_mfma_preferred(int d, int V, int N, int group, const uint32_t *qweight);
 int lm_head_q4_mfma_workgroups(int V);  // never more than lm_head_q4_workgroups(V)
 hipError_t launch_lm_head_q4_mfma(int d, int V, float eps, int N, const half_t *hidden, const half_t *gamma,
@@ -188,5 +188,22 @@ hipError_t launch_lm_head_q4_mfma_argmax(int d, int V, float eps, int N, const h
                                          const uint32_t *qweight, const half_t *scales, const half_t *zeros,
                                          int group, float *best_val, int32_t *best_idx, const int32_t *gate,
                                          const int32_t *done, hipStream_t s);
+
+// Up to 16 hidden states per pass over the head, fp16 or quantised (head_states.hip): all logits, or `workgroups`
+// arg-max candidates per state (head_states_workgroups with the number that the caller has room for)
+struct HeadQ4 {
+    const uint32_t *qweight;  // null: fp16 head
+    const half_t *scales, *zeros;
+    int group;
+};
+bool head_states_q4_ok(int group);  // groups of 128 and 64
+bool head_states_q4_preferred(int d, int V, int N, int group);
+bool head_states_preferred(int d, int V, int N);
+int head_states_workgroups(int d, int V, int group, int limit);
+hipError_t launch_head_states(int d, int V, float eps, int N, const half_t *hidden, const half_t *gamma,
+                              const half_t *lm_head, const HeadQ4 &q4, float *out, hipStream_t s);
+hipError_t launch_head_states_argmax(int d, int V, float eps, int N, const half_t *hidden, const half_t *gamma,
+                                     const half_t *lm_head, const HeadQ4 &q4, int workgroups, float *best_val,
+                                     int32_t *best_idx, const int32_t *gate, const int32_t *done, hipStream_t s);
 
 }  // namespace specee

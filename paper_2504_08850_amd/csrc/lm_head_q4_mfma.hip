@@ -25,6 +25,9 @@
 // wavefront would make the LDS reads the bound.  B sits in LDS in fragment order, double-buffered: a wavefront's
 // read is 64 consecutive 16-byte pieces, without bank conflicts.
 //
+// Groups of exactly 128 and 64 go to head_states.hip where they gain from the matrix cores (same shapes: 23.8 us, groups of
+// 64 25.0 us); this kernel does the other multiples of 32.
+//
 // Measured against the vector kernel, 32000 x 4096, groups of 128 (70 MB): 16 states 193 -> 27.2 us, 8 states
 // 106 -> 25.6 us, 2 states 32.1 -> 25.8 us; with arg-max, 16 states 195 -> 29.9 us.  Groups of 64 (twice the folds):
 // 191 -> 34.3 us.  50280 x 2048, 16 states: 171 -> 28.8 us.  The time hardly depends on the number of states: the

@@ -286,8 +286,12 @@ int lm_head_gemv(const specee_dims *dm, int N, const specee_half *hidden, const 
     if (misaligned(hidden) || misaligned(gamma) || misaligned(lm_head)) return SPECEE_EALIGN;
     if (misaligned(out)) return SPECEE_EALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // one or two hidden states: stream the head once per state on the vector units;
-    // more: one pass over the head on the matrix cores
+    // one hidden state (two on a small head): stream the head once per state on the vector units;
+    // more: one pass over the head per 16 or per 64 of them on the matrix cores
+    if (head_states_preferred(dm->d, dm->V, N))
+        return launch_head_states(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), H(lm_head), HeadQ4{}, out, st) == hipSuccess
+                   ? SPECEE_OK
+                   : SPECEE_EHIP;
     hipError_t e = (N <= 2) ? launch_lm_head_gemv(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), H(lm_head), out, st)
                             : launch_lm_head_gemm(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), H(lm_head), out, st);
     return e == hipSuccess ? SPECEE_OK : SPECEE_EHIP;
@@ -469,13 +473,15 @@ int lm_head_gemv_q4(const specee_dims *dm, int N, const specee_half *hidden, con
     if ((rc = check_q4(dm, qweight, scales, zeros, group))) return rc;
     if (!hidden || !gamma || !out) return SPECEE_EINVAL;
     if (misaligned(hidden) || misaligned(gamma)) return SPECEE_EALIGN;
-    // vector units: a pass over the head per state; matrix cores: a pass per 16 states
-    const bool mfma = lm_head_q4_mfma_preferred(dm->d, dm->V, N, group, qweight);
-    const auto launch = mfma ? launch_lm_head_q4_mfma : launch_lm_head_q4;
-    return launch(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), qweight, H(scales), H(zeros), group, out,
-                  static_cast<hipStream_t>(stream)) == hipSuccess
-               ? SPECEE_OK
-               : SPECEE_EHIP;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const HeadQ4 q4{qweight, H(scales), H(zeros), group};
+    // matrix cores: a pass over the head per 16 states; vector units: a pass per state
+    const auto launch = lm_head_q4_mfma_preferred(dm->d, dm->V, N, group, qweight) ? launch_lm_head_q4_mfma : launch_lm_head_q4;
+    const hipError_t e =
+        head_states_q4_preferred(dm->d, dm->V, N, group)
+            ? launch_head_states(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), nullptr, q4, out, st)
+            : launch(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), qweight, H(scales), H(zeros), group, out, st);
+    return e == hipSuccess ? SPECEE_OK : SPECEE_EHIP;
 }
 
 int specee_verify_q4(const specee_dims *dm, int N, const specee_half *hidden, const specee_half *gamma,
@@ -490,18 +496,27 @@ int specee_verify_q4(const specee_dims *dm, int N, const specee_half *hidden, co
     if ((rc = check_q4(dm, qweight, scales, zeros, group))) return rc;
     if (!hidden || !gamma || !ids || !token || !max_logit || !hit) return SPECEE_EINVAL;
     if (misaligned(hidden) || misaligned(gamma) || misaligned(workspace)) return SPECEE_EALIGN;
-    // the workspace is sized for the vector kernel's candidates; the matrix-core kernel leaves at most as many
+    // the workspace is sized for the vector kernel's candidates; the kernels for several states leave at most as many
     const size_t half_ws = align256((size_t)N * lm_head_q4_workgroups(dm->V) * sizeof(float));
     if (!workspace || workspace_bytes < 2 * half_ws) return SPECEE_EWORKSPACE;
     float *best_val = static_cast<float *>(workspace);
     int32_t *best_idx = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + half_ws);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool mfma = lm_head_q4_mfma_preferred(dm->d, dm->V, N, group, qweight);
-    const int P = mfma ? lm_head_q4_mfma_workgroups(dm->V) : lm_head_q4_workgroups(dm->V);
-    const auto launch = mfma ? launch_lm_head_q4_mfma_argmax : launch_lm_head_q4_argmax;
-    if (launch(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), qweight, H(scales), H(zeros), group, best_val, best_idx,
-               gate, done, st) != hipSuccess)
-        return SPECEE_EHIP;
+    const HeadQ4 q4{qweight, H(scales), H(zeros), group};
+    int P = lm_head_q4_workgroups(dm->V);
+    hipError_t e;
+    if (head_states_q4_preferred(dm->d, dm->V, N, group)) {
+        P = head_states_workgroups(dm->d, dm->V, group, P);
+        e = launch_head_states_argmax(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), nullptr, q4, P, best_val, best_idx,
+                                      gate, done, st);
+    } else {
+        const bool mfma = lm_head_q4_mfma_preferred(dm->d, dm->V, N, group, qweight);
+        if (mfma) P = lm_head_q4_mfma_workgroups(dm->V);
+        const auto launch = mfma ? launch_lm_head_q4_mfma_argmax : launch_lm_head_q4_argmax;
+        e = launch(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), qweight, H(scales), H(zeros), group, best_val, best_idx,
+                   gate, done, st);
+    }
+    if (e != hipSuccess) return SPECEE_EHIP;
     return launch_verify_finish(best_val, best_idx, P, N, ids, dm->K, gate, done, token, max_logit, hit, st) ==
                    hipSuccess
                ? SPECEE_OK
@@ -629,16 +644,24 @@ int specee_verify(const specee_dims *dm, int N, const specee_half *hidden, const
     if (!hidden || !gamma || !lm_head || !ids || !token || !max_logit || !hit) return SPECEE_EINVAL;
     if (misaligned(hidden) || misaligned(gamma) || misaligned(lm_head) || misaligned(workspace)) return SPECEE_EALIGN;
     const bool vec = N <= 2;
-    const int P = vec ? lm_head_gemv_workgroups(dm->V) : lm_head_gemm_workgroups(dm->V);
+    int P = vec ? lm_head_gemv_workgroups(dm->V) : lm_head_gemm_workgroups(dm->V);
     const size_t half_ws = align256((size_t)N * P * sizeof(float));
     if (!workspace || workspace_bytes < 2 * half_ws) return SPECEE_EWORKSPACE;
     float *best_val = static_cast<float *>(workspace);
     int32_t *best_idx = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + half_ws);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipError_t e = vec ? launch_lm_head_argmax_gemv(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), H(lm_head),
-                                                    best_val, best_idx, gate, done, st)
-                       : launch_lm_head_argmax_gemm(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), H(lm_head),
-                                                    best_val, best_idx, gate, done, st);
+    const bool states = head_states_preferred(dm->d, dm->V, N);
+    if (states) P = head_states_workgroups(dm->d, dm->V, 0, P);
+    hipError_t e;
+    if (states)
+        e = launch_head_states_argmax(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), H(lm_head), HeadQ4{}, P, best_val,
+                                      best_idx, gate, done, st);
+    else if (vec)
+        e = launch_lm_head_argmax_gemv(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), H(lm_head), best_val, best_idx, gate,
+                                       done, st);
+    else
+        e = launch_lm_head_argmax_gemm(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), H(lm_head), best_val, best_idx, gate,
+                                       done, st);
     if (e != hipSuccess) return SPECEE_EHIP;
     e = launch_verify_finish(best_val, best_idx, P, N, ids, dm->K, gate, done, token, max_logit, hit, st);
     return e == hipSuccess ? SPECEE_OK : SPECEE_EHIP;

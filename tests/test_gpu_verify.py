@@ -181,3 +181,68 @@ def test_multi_state_head_and_verify_by_tiles_of_states(sp, oracle, N):
     tok = out["token"].cpu().numpy()
     assert np.array_equal(tok, got.argmax(axis=1))
     assert np.array_equal(out["max_logit"].cpu().numpy(), got[np.arange(N), tok])
+
+
+def head_rows(rng, V, d, group):
+    """A head: what the library takes, and the same in float64 as weights and as bounds of what is summed for one."""
+    if not group:
+        w = (0.05 * rng.standard_normal((V, d))).astype(np.float16)
+        return (dev(w),), w.astype(np.float64), np.abs(w.astype(np.float64))
+    codes = rng.integers(0, 16, (V, d), dtype=np.uint32)
+    q = (codes.reshape(V, d // 8, 8) << (4 * np.arange(8, dtype=np.uint32))).sum(axis=2, dtype=np.uint32)
+    s = rng.uniform(0.004, 0.02, (V, d // group)).astype(np.float16)
+    z = rng.uniform(5, 10, (V, d // group)).astype(np.float16)
+    s64, z64 = (np.repeat(a.astype(np.float64), group, axis=1) for a in (s, z))
+    return (dev(q.view(np.int32)), dev(s), dev(z), group), s64 * (codes - z64), s64 * (codes + z64)
+
+
+@pytest.mark.parametrize("d,V,N,group,hscale", [
+    (8, 1, 3, 0, 1.0), (72, 17, 16, 0, 1.0), (512, 16, 15, 0, 1.0), (520, 33, 17, 0, 1.0),  # rows end in a wavefront
+    (1032, 6007, 2, 0, 1.0), (2048, 4099, 64, 0, 1.0), (4096, 4111, 16, 0, 1.0),            # several tiles, passes of states
+    (4104, 47, 15, 0, 1.0), (8192, 515, 16, 0, 1.0), (16384, 40, 3, 0, 1.0),                # two, two and four passes over rows
+    (1024, 129, 8, 0, 2.0 ** -13), (1024, 129, 8, 0, 16000.0),
+    (64, 2003, 15, 64, 1.0), (192, 1700, 16, 64, 1.0), (128, 8003, 2, 128, 1.0),
+    (2048, 1603, 15, 64, 1.0), (3072, 1009, 16, 128, 1.0), (4096, 1103, 17, 128, 1.0),
+    (4224, 1003, 16, 128, 1.0), (4608, 1601, 16, 64, 1.0), (5120, 1001, 16, 128, 1.0),
+    (8192, 1503, 16, 64, 1.0), (16384, 1001, 16, 128, 1.0),
+    (2048, 1603, 16, 128, 2.0 ** -13), (4608, 1603, 16, 64, 16000.0),
+])
+def test_head_of_several_states_by_shares_of_the_row(sp, d, V, N, group, hscale):
+    """fp32 sums of exact products: a term passes at most 512 additions in a wavefront's share of the row (32 per matrix
+    instruction, 16 of them), 16 shares, four passes and a handful of folds and factors, each off by 2^-24 of what it has
+    summed.  h and gamma are scaled by their shares' norms to between 2^5 and 2^8 before x is cut, so that what lies below
+    the normal halves is off by 2^-25 of that, at most 2^-28 of the product of the norms."""
+    rng = np.random.default_rng(d + V + N)
+    h = (rng.standard_normal((N, d)).clip(-4, 4) * hscale).astype(np.float16)
+    g = (1 + 0.05 * rng.standard_normal(d)).astype(np.float16)
+    head, w, absw = head_rows(rng, V, d, group)
+    logits, verify = (sp.lm_head_gemv_q4, sp.verify_q4) if group else (sp.lm_head_gemv, sp.verify)
+    h64, g64 = h.astype(np.float64), g.astype(np.float64)
+    r = 1.0 / np.sqrt((h64 ** 2).mean(axis=1, keepdims=True) + 1e-5)
+    ref = r * ((h64 * g64) @ w.T)
+    norms = np.sqrt((h64 ** 2).sum(axis=1, keepdims=True) * (g64 ** 2).sum())
+    bound = r * ((512 + 16 + 4 + 16) * 2.0 ** -24 * (np.abs(h64 * g64) @ absw.T) + 2.0 ** -28 * norms * absw.sum(axis=1))
+    got = host(logits(dev(h), dev(g), *head, out=torch.full((N, V), float("nan"), device="cuda")))
+    assert np.all(np.abs(got - ref) <= bound)
+    ids = np.stack([rng.choice(V, min(V, 3), replace=False) for _ in range(N)]).astype(np.int32)
+    v = {k: host(a) for k, a in verify(dev(h), dev(g), *head, dev(ids)).items()}
+    # the same sums decide, and the lowest of equal rows wins
+    assert np.array_equal(v["token"], got.argmax(axis=1)) and np.array_equal(v["max_logit"], got.max(axis=1))
+    bad = h.copy()
+    bad[0, d - 1], bad[N // 2, 0] = np.inf, np.nan
+    b = host(logits(dev(bad), dev(g), *head))
+    rest = np.setdiff1d(np.arange(N), [0, N // 2])
+    assert np.isnan(b[[0, N // 2]]).all() and np.array_equal(b[rest], got[rest])
+
+
+def test_head_of_several_states_more_tiles_than_sums_wait_in_lds(sp):
+    """Two passes over the rows and 33 tiles for the first workgroups: the sums of a row do not depend on the split."""
+    d, V, N = 4104, 131100, 3
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    h, g = torch.randn(N, d, generator=gen, device="cuda").half(), torch.ones(d, device="cuda").half()
+    w = torch.randn(V, d, generator=gen, device="cuda", dtype=torch.float16)
+    got = sp.lm_head_gemv(h, g, w)
+    assert torch.equal(got[:, :1500], sp.lm_head_gemv(h, g, w[:1500].contiguous()))
+    assert torch.equal(got[:, V - 1500:], sp.lm_head_gemv(h, g, w[V - 1500:].contiguous()))
+    out = sp.verify(h, g, w, torch.zeros(N, 1, dtype=torch.int32, device="cuda"))
+    assert torch.equal(out["token"].long(), got.argmax(dim=1)) and torch.equal(out["max_logit"], got.max(dim=1).values)
