@@ -549,7 +549,7 @@ def main():
         res["fires_everywhere_accepted_exit_layer"] = int(torch.stack([v["hit"] for v in vo]).flatten().nonzero()[0])
         res["launches_per_layer"] = 3
         extra["layer_loop_device_control_7b"] = res
-        # the same loop as ONE persistent launch (specee_layer_loop): no launch per layer, nothing after the exit
+        # the same loop as one call (specee_layer_loop): no launch per layer, the exit decided on the device
         ids_rand = up(t2["ids"]).clone()
         lo = sp.layer_loop(hid_l, gamma, lm, ids_rand, W1, w2, threshold=2.0)
         lws = lo.pop("_workspace")

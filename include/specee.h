@@ -209,8 +209,8 @@ int specee_predict_tree_static(const specee_dims *dims, int G, int N, int Mcap, 
  * (Sec. 4.3.3).  out [N][V] fp32 = RMSNorm(hidden[n]) . lm_head[v].
  * dims->K and dims->H are ignored.  Workspace: SPECEE_OP_LM_HEAD with n = N.
  * A single hidden state is taken to find the head in HBM, as in a decode loop
- * whose layers' weights pass through the last-level cache between two calls (here,
- * in specee_verify and for a token's first verification in specee_layer_loop).
+ * whose layers' weights pass through the last-level cache between two calls (here
+ * and in specee_verify).
  */
 int lm_head_gemv(const specee_dims *dims, int N, const specee_half *hidden, const specee_half *gamma,
                  const specee_half *lm_head, float *out, void *workspace, size_t workspace_bytes, void *stream);
@@ -279,14 +279,14 @@ int specee_predict_tree_q4(const specee_dims *dims, int G, int N, int Mcap, cons
                            int32_t *exit_flags, int32_t *path_exit, void *stream);
 
 /*
- * The early-exit decode loop of B tokens down L layers in one launch (Sec. 4.3.3:
+ * The early-exit decode loop of B tokens down L layers in one call (Sec. 4.3.3:
  * a positive prediction is followed by verification, and the token leaves the
  * model at the first layer whose verification accepts a speculative token;
  * Sec. 5.3: only the layers of the active set run their predictor).  For each
  * token, layer by layer: specee_predict with the local probabilities of the
  * token's previous active layer; if the exit flag is set, specee_verify on the
- * same hidden state; on a hit the loop ends for that token.  Nothing is
- * evaluated after a token's exit, and the host takes no part in any decision.
+ * same hidden state; on a hit the loop ends for that token.  What lies after a
+ * token's exit counts as not evaluated, and the host takes no part in any decision.
  *   hidden [L][B][d] (every layer's hidden state exists before the call),
  *   ids [B][K], prev0 [B][K] or NULL (zeros), mlp with leading L (as for
  *   specee_predict_sweep), active [L] int32 or NULL (all layers active).
@@ -296,14 +296,17 @@ int specee_predict_tree_q4(const specee_dims *dims, int G, int N, int Mcap, cons
  *   (inactive, or after its exit) hold zeros (ver_token -1).
  *   exit_layer [B]: layer at which the token left the model, -1 if it ran the
  *   whole stack; token [B]: the accepted token or -1.
- *   status [B]: 0, or 1 if the token's workgroups could not meet (see below);
+ *   status [B]: 0, or 1 if the workgroups could not meet (see below);
  *   its outputs from the failing layer on are then the not-evaluated values.
- * One group of workgroups per token stays on the GPU for the whole call and meets
- * once per verification, so the call needs every one of its workgroups resident
- * at once: the grid is sized to what the device holds, B must not exceed 64, and
- * the GPU should not be shared with other kernels while it runs.  Every wait in
- * the kernel is bounded: spin_limit polls (0: a default worth a few seconds), after
- * which the token is given up with status 1 -- the call never hangs.
+ * The predictors of all layers come first; the verifications follow, up to 16 of
+ * them, of whatever tokens and layers, in one pass over the head.  (On a quantised
+ * head in groups other than 128 and 64: layer by layer, one group of workgroups per
+ * token.)  The workgroups stay on the GPU and meet once per pass, so the call needs
+ * every one of them resident at once: the grid is sized to what the device holds, B
+ * must not exceed 64, and the GPU should not be shared with other kernels while it
+ * runs.  Every wait in the kernel is bounded: spin_limit polls (0: a default worth a
+ * second or more), after which the tokens that are not done are given up with
+ * status 1 -- the call never hangs.
  * Limits: d <= 8192, B <= 64.  Workspace: SPECEE_OP_LAYER_LOOP with n = B.
  */
 int specee_layer_loop(const specee_dims *dims, int L, int B, const specee_half *hidden, const specee_half *gamma,

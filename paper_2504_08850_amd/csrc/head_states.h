@@ -12,6 +12,8 @@
 //     of two matrix steps by exchanging halves of 16 lanes.  Every register of a tile is asked for again, for a later
 //     tile, as soon as it has been used: 128 KB per CU are in flight all the time;
 //   * every eight tiles (four, with sixteen wavefronts) the partial sums meet in LDS and are added in ascending order of elements.
+// Shorter rows (d <= 2048) leave room for several workgroups on a CU, or for several groups of wavefronts in one workgroup,
+// which take the tiles in turn and meet together.
 // Longer rows (d > 4096) are done in passes over the workgroup's rows, 4096 elements or less at a time; the sums of
 // the passes wait in LDS.
 //
@@ -148,14 +150,15 @@ __device__ __forceinline__ int hs_element(int j, int q) {
     return 32 * j + 8 * q;  // fp16 head: 64 contiguous bytes of a row
 }
 
-// Logits of rows [16 * tile_begin, 16 * tile_end) (tile_begin < tile_end, at most kHsMaxTiles tiles if there are several passes) for 16 states, by
-// the whole workgroup of chunks / CPW wavefronts: state_row(n) is the hidden state of slot n, valid for n < 16.
+// Logits of rows [16 * tile_begin, 16 * tile_end) (tile_begin < tile_end, at most kHsMaxTiles tiles if there are several
+// passes) for 16 states, by the whole workgroup of row_groups * chunks / CPW wavefronts (row_groups a power of two, at
+// most hs_block(CPW)): state_row(n) is the hidden state of slot n, valid for n < 16.
 // emit(row, n, y) is called by the lanes of the first wavefronts, all of a wavefront's lanes together and rows ascending
 // for each lane: row may lie past the end (>= V), y[r] is the logit of state n + r, n = 4 * (lane / 16).
 // LW: 0 = fp16 head, else the group is 32 * LW.  RAGGED: rows end before the passes do (d != passes * chunks * 128).
 template <int LW, int CPW, bool RAGGED, class StateRow, class Emit>
-__device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned char *smem, int tile_begin, int tile_end,
-                                                 StateRow state_row, Emit emit) {
+__device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned char *smem, int row_groups, int tile_begin,
+                                                 int tile_end, StateRow state_row, Emit emit) {
     constexpr bool Q4 = LW != 0;
     constexpr int kHsBlock = hs_block(CPW);
     constexpr int kSteps = CPW * 4;            // matrix steps of a tile
@@ -163,8 +166,9 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
     constexpr int kDepth = 1;                  // tiles in flight (two or four, with codes: no gain)
     constexpr int kSpw = Q4 ? CPW * 4 / (Q4 ? LW : 1) : 1;  // sub-chunks of a wavefront
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int W = p.chunks / CPW;
+    const int W = p.chunks / CPW, G = row_groups;
+    const int wg_wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = row_groups == 1 ? 0 : wg_wave / W, wave = wg_wave - group * W;
     const int c = lane & 15, q = lane >> 4;
     const int d = p.d, ng = Q4 ? d / (32 * LW) : 1;
 
@@ -253,7 +257,7 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < kDepth; ++s) {
-            const int t = tile_begin + s;
+            const int t = tile_begin + group + s * G;
 #pragma unroll
             for (int i = 0; i < kLoads / 2; ++i) load_pair(t, s, i);
             if constexpr (Q4) load_scales(t, s);
@@ -316,7 +320,7 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
             const int nb = min(kHsBlock, tile_end - tb);
             const int pbuf = p.buffers == 2 ? buf : 0;
             auto tile = [&](int i, int slot) {
-                const int tn = tb + i + kDepth;
+                const int tn = tb + i + kDepth * G;
                 const int ln = hs_opaque(lane), tq = ln >> 4;
                 floatx4 acc = {0.f, 0.f, 0.f, 0.f};
                 if constexpr (Q4) {
@@ -369,18 +373,14 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
                 acc *= *reinterpret_cast<const floatx4 *>(unscale_lds + wave * kHsStates + 4 * tq);
                 part[((pbuf * W + wave) * kHsBlock + i) * kWave + ln] = acc;
             };
-            static_assert(kHsBlock % kDepth == 0, "a block starts with slot 0");
-            for (int i = 0; i < nb; i += kDepth) {
-#pragma unroll
-                for (int u = 0; u < kDepth; ++u)
-                    if (i + u < nb) tile(i + u, u);
-            }
+            static_assert(kDepth == 1, "a block starts with slot 0");
+            for (int i = group; i < nb; i += G) tile(i, 0);
             __syncthreads();
             if (tb == tile_begin) {
                 for (int w = 0; w < W; ++w) ssq_total += ssq_lds[w * kHsStates + c];
                 rms = 1.0f / sqrtf(ssq_total / (float)d + p.eps);  // (used in the last pass)
             }
-            for (int i = wave; i < nb; i += W) {
+            for (int i = wg_wave; i < nb; i += G * W) {
                 const int ln = hs_opaque(lane), lq = ln >> 4;
                 const floatx4 *src = part + (pbuf * W * kHsBlock + i) * kWave + ln;
                 floatx4 y = *src;

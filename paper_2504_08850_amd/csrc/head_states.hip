@@ -42,7 +42,7 @@ __global__ __launch_bounds__(hs_max_waves(CPW) * kWave) void head_states_kernel(
     const int most = p.hs.passes > 1 ? kHsMaxTiles : t1 - t0;
     for (int t = t0; t < t1; t += most)
         head_states_rows<LW, CPW, RAGGED>(
-            p.hs, hs_smem, t, min(t1, t + most), [&](int n) { return p.hidden + (size_t)min(n0 + n, p.N - 1) * p.hs.d; },
+            p.hs, hs_smem, 1, t, min(t1, t + most), [&](int n) { return p.hidden + (size_t)min(n0 + n, p.N - 1) * p.hs.d; },
             [&](int row, int n, floatx4 y) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {

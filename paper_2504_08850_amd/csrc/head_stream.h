@@ -1,6 +1,5 @@
 // Streaming of full LM-head rows against one normalised hidden state held in LDS: the inner loop of
-// the full-vocabulary head (paper Sec. 4.1, Sec. 4.3.3), shared by the stand-alone head kernels and by
-// the verification pass of the persistent layer loop.
+// the full-vocabulary head (paper Sec. 4.1, Sec. 4.3.3) for one state at a time.
 #pragma once
 #include "device_utils.h"
 
@@ -84,8 +83,7 @@ __device__ __forceinline__ void head_argmax_rows(const half_t *lm_head, int d, i
 // loses a twentieth.  Arg-max without / with the hint, heads alternating so that none stays: 262 MB 52.2 / 47.1 us,
 // 206 MB 46.9 / 41.4, 164 MB 41.6 / 38.5, 135 MB 37.5 / 34.4; the same head back to back: 42.3 / 43.4, 35.0 / 37.1,
 // 33.6 / 33.5, 32.1 / 29.8 us.  Several states of one call re-read the head right behind each other and keep the
-// cache's help (layer loop, three tokens, 262 MB: 166 us against 177 with the hint; 197 MB: 133 / 162).  What the layer
-// loop does with a single token's verifications is said at its launch.
+// cache's help (three at a time, 262 MB: 166 us against 177 with the hint; 197 MB: 133 / 162).
 inline bool head_streams(int d, int V, int states) {
     return (size_t)V * d * sizeof(half_t) > ((size_t)(states == 1 ? 128 : 288) << 20);
 }

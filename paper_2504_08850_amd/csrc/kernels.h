@@ -37,6 +37,10 @@ struct PredictParams {
     float *logits, *probs, *scores;
     int32_t *exit_flags;
     TreeMergeParams tree;  // launch_tree_nodes only
+    struct {               // launch_loop_scores only (ver_token null otherwise)
+        int32_t *ver_token, *hit, *arrive, *abort;
+        unsigned long long *lines;
+    } loop;
 };
 
 // Trees scored node by node (B = G * N tokens): predictor and merge in one launch, then overflow and path rule
@@ -48,7 +52,11 @@ hipError_t launch_predict(const PredictParams &p, hipStream_t s);
 hipError_t launch_predict_q4(const PredictParams &p, hipStream_t s);
 hipError_t launch_predict_sweep(const PredictParams &p, int32_t *first_exit, hipStream_t s);
 
-// Persistent early-exit loop over the layers of B tokens (layer_loop.hip)
+// Early-exit loop over the layers of B tokens: all predictors, then verifications of up to 16 (layer, token) pairs per pass
+// over the head (loop_verify.hip), or, on a quantised head of other groups than 128 and 64, layer by layer (layer_loop.hip)
+constexpr int kLoopLine = 16;      // words of 8 bytes between two ...
+constexpr int kLoopKeys = 3 * 16;  // ... arg-max slots, three passes' worth of them, and, behind them,
+constexpr int kLoopNotes = 64;     // ... notes on how a pass went
 struct LoopParams {
     int d, V, K, H, L, B;
     float eps, threshold;
@@ -65,14 +73,17 @@ struct LoopParams {
     float *logits, *probs, *scores;            // [L][B][K], [L][B][K], [L][B]
     int32_t *exit_flags, *ver_token, *hit;     // [L][B]
     int32_t *exit_layer, *token, *status;      // [B]
-    int rows_per_wg;        // LM-head rows per workgroup in a verification pass (set by the launcher)
-    int32_t *arrive;        // [B] arrival counters of the groups, zero at launch
-    int32_t *abort;         // [1] zero at launch; set by a group that could not meet
-    float *cand_val;        // [2][B][workgroups per token] arg-max candidates
+    int rows_per_wg;        // layer by layer: LM-head rows per workgroup in a verification (set by the launcher)
+    int32_t *arrive;        // [B] arrival counters of the groups (of the grid: [1]), cleared by the first launch
+    int32_t *abort;         // [1] cleared likewise; set by a group that could not meet
+    float *cand_val;        // layer by layer: [2][B][workgroups per token] arg-max candidates
     int32_t *cand_idx;
+    unsigned long long *lines;  // passes: arg-max slots and notes, in the same space, cleared by the first launch
     long long spin_limit;   // polls of the arrival counter before a meeting is given up
 };
 hipError_t launch_layer_loop(const LoopParams &p, int max_wgs, hipStream_t s);
+hipError_t launch_loop_scores(const LoopParams &p, hipStream_t s);
+hipError_t launch_loop_verify(const LoopParams &p, int max_wgs, hipStream_t s);
 
 #define SPECEE_KMAX_INTERNAL 16
 

@@ -1,19 +1,17 @@
-// The early-exit decode loop of a token down the layer stack in ONE launch (paper Sec. 4.3.3 dataflow
-// -- predict, verify after a positive prediction, leave the model at the first accepted verification --
-// with the active-predictor set of the scheduler, Sec. 5.3).
+// The early-exit decode loop of a token down the layer stack in ONE launch (paper Sec. 4.3.3 dataflow, Sec. 5.3 active
+// set) on a 4-bit group-quantised head whose groups are neither 128 nor 64: what loop_verify.hip, which does all other
+// heads, has no pass for.
 //
-// A launch of one kernel per step costs about two microseconds on this system even when the kernel is
-// empty, which is as much as the predictor itself; and a static sequence of launches cannot stop at the
-// exit.  Here a group of Pg workgroups stays resident for a token and walks the layers:
+// A group of Pg workgroups stays resident for a token and walks the layers:
 //   * the predictor of a layer is evaluated redundantly by every workgroup of the group (its reads hit
 //     in L2 after the first workgroup): all of them reach the same exit decision with no communication,
-//     so a layer that does not fire costs no synchronisation.  Such a layer measures 1.7 us at d = 4096:
+//     so a layer that does not fire costs no synchronisation.  Such a layer measures 1.9 us at d = 4096:
 //     about 600 instructions of one wavefront's stream (hidden state to float, sum of squares, K dot
 //     products, two workgroup-wide reductions, softmax and MLP), not memory, which is prefetched one
 //     active layer ahead;
-//   * the K speculative LM-head rows and the RMSNorm weight do not change from layer to layer: they are
-//     loaded once and stay in registers, so a layer reads only its hidden state and its predictor;
-//   * when the predictor fires, the group streams the whole LM head once (workgroup w takes a block
+//   * the K speculative LM-head rows and the RMSNorm weight do not change from layer to layer: the rows are dequantised
+//     once, with the weight folded in, and stay in registers, so a layer reads only its hidden state and its predictor;
+//   * when the predictor fires, the group streams the codes of the whole LM head once (workgroup w takes a block
 //     of rows), every workgroup leaves its arg-max candidate in the workspace, the group meets at an
 //     arrival counter, and every workgroup combines all candidates itself -- again the same decision
 //     everywhere.  One group-wide meeting per verification, none otherwise;
@@ -22,7 +20,6 @@
 // occupancy the runtime reports, and every wait is bounded (spin limit), so a group that cannot meet
 // (another kernel holds the CUs) ends with status 1 instead of hanging.
 #include "device_utils.h"
-#include "head_stream.h"
 #include "q4_head_stream.h"
 #include "kernels.h"
 #include "predictor_tail.h"
@@ -38,23 +35,14 @@ struct LoopRare {
     int32_t *cand_idx, *arrive, *abort;
     long long spin_limit;
 };
-constexpr int kLoopStreamFirst = 4;  // verifications of a token that read the head with the hint under STREAM = 2
 constexpr int kLoopMaskLds = 1024;  // layers of the active mask kept in LDS (deeper stacks read the rest in place)
 
-// KC / EXACT / VPT as in predict_kernel.  KEEP: the K rows stay in registers across layers (up to 64
-// registers of them; wider shapes read their rows again at every layer, from L2).
-// HEAD: 0 = fp16 LM head, 1 = 4-bit group-quantised head read in 16-byte chunks (group % 32 == 0, aligned rows),
-// 2 = quantised head read word by word.  On a quantised head the token's K rows are dequantised once, into
-// the float registers that hold them anyway (with the RMSNorm weight folded in), so the predictor of a layer is
-// the same code; the verification streams the codes (q4_head_rows).  Needs KEEP (K <= 8).
-// STREAM: verifications that read the head with the non-temporal hint -- 0 none, 1 all, 2 a token's first four.
-template <int KC, int VPT, bool EXACT, int STREAM, int HEAD = 0>
+// KC / VPT as in predict_kernel (K == KC, at most 8).
+// WIDE: the head is read in 16-byte chunks (group % 32 == 0, aligned rows), otherwise word by word.
+template <int KC, int VPT, bool WIDE>
 __global__ __launch_bounds__(kLoopThreads) void layer_loop_kernel(LoopParams p) {
-    constexpr bool KEEP = KC * VPT <= 16 && KC <= 8;
-    constexpr bool Q4 = HEAD != 0;
-    static_assert(!Q4 || KEEP, "the quantised head needs the rows kept in registers");
-    extern __shared__ float4 loop_lds_x[];  // verification: x = h * gamma as two float4 planes, [2][d/8]
-                                            // (quantised head: then [d/group] per-group sums of x)
+    extern __shared__ float4 loop_lds_x[];  // verification: x = h * gamma as two float4 planes, [2][d/8], and
+                                            // [d/group] per-group sums of x
     __shared__ __attribute__((aligned(16))) float red[KC + 1][kLoopWaves];  // [value][wavefront]: a value's partial
     __shared__ __attribute__((aligned(16))) float red_u[kLoopWaves];        // sums are two 16-byte reads
     static_assert(kLoopWaves == 8, "the cross-wavefront sums below read two float4 per value");
@@ -69,7 +57,8 @@ __global__ __launch_bounds__(kLoopThreads) void layer_loop_kernel(LoopParams p) 
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int w = blockIdx.x, b = blockIdx.y, Pg = gridDim.x, B = p.B;
-    const int K = EXACT ? KC : p.K, H = p.H, d = p.d, L = p.L;
+    constexpr int K = KC;
+    const int H = p.H, d = p.d, L = p.L;
     const int nv = d >> 3;
     const bool writer = w == 0;  // the workgroup of the group that writes the token's outputs
     floatx4 *xa = reinterpret_cast<floatx4 *>(loop_lds_x);
@@ -90,41 +79,18 @@ __global__ __launch_bounds__(kLoopThreads) void layer_loop_kernel(LoopParams p) 
         for (int k = 0; k < KC; ++k)
             if (k < K) prev[k] = p.prev0[(size_t)b * K + k];
     }
-    const half_t *rows[KC];
     size_t rowi[KC];
     bool bad_id = false;
 #pragma unroll
     for (int k = 0; k < KC; ++k) {
         const bool ok = idv[k] >= 0 && idv[k] < p.V;
-        if (k < K && !ok) bad_id = true;
+        if (!ok) bad_id = true;
         rowi[k] = (size_t)(ok ? idv[k] : 0);
-        rows[k] = Q4 ? nullptr : p.lm_head + rowi[k] * d;
     }
-    half8 wv[KC][VPT];
-    auto load_rows = [&]() {
-#pragma unroll
-        for (int k = 0; k < KC; ++k)
-#pragma unroll
-            for (int u = 0; u < VPT; ++u) {
-                const int v = tid + u * kLoopThreads;
-                const half8 x = load_half8(rows[k] + min(v, nv - 1) * 8);
-                wv[k][u] = (k < K && v < nv) ? x : zero_half8();
-            }
-    };
-    if (KEEP && !Q4) load_rows();
-    // KEEP: the rows stay for the whole call, so they are kept as floats with the RMSNorm weight folded in
-    // (the product of two halves is exact in fp32): a layer then costs one conversion of its hidden state
-    // and K + 1 FMAs per element instead of twice as many instructions.
-    float wg[KEEP ? KC : 1][KEEP ? VPT : 1][8];
-    if (KEEP && !Q4) {
-#pragma unroll
-        for (int k = 0; k < KC; ++k)
-#pragma unroll
-            for (int u = 0; u < VPT; ++u)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) wg[KEEP ? k : 0][KEEP ? u : 0][e] = (float)wv[k][u][e] * (float)gv[u][e];
-    }
-    if (Q4) {
+    // The rows stay for the whole call, as floats with the RMSNorm weight folded in: a layer then costs one conversion of
+    // its hidden state and K + 1 FMAs per element.
+    float wg[KC][VPT][8];
+    {
         // element e of vector v is the code in bits 4e of word v of the row; its group is (8v) / group
         const int ng = d / p.group;
 #pragma unroll
@@ -136,11 +102,11 @@ __global__ __launch_bounds__(kLoopThreads) void layer_loop_kernel(LoopParams p) 
                 const uint32_t word = p.qweight[rowi[k] * nv + vc];
                 const int gi = (vc * 8) / p.group;
                 const float sc = (float)p.qscales[rowi[k] * ng + gi], zp = (float)p.qzeros[rowi[k] * ng + gi];
-                const bool live = k < K && v < nv;
+                const bool live = v < nv;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float wq = sc * ((float)((word >> (4 * e)) & 15u) - zp);
-                    wg[KEEP ? k : 0][KEEP ? u : 0][e] = live ? wq * (float)gv[u][e] : 0.f;
+                    wg[k][u][e] = live ? wq * (float)gv[u][e] : 0.f;
                 }
             }
     }
@@ -230,7 +196,6 @@ __global__ __launch_bounds__(kLoopThreads) void layer_loop_kernel(LoopParams p) 
 #pragma unroll
         for (int u = 0; u < VPT; ++u) hv[u] = tid + u * kLoopThreads < nv ? hv_pf[u] : zero_half8();
         prefetch(min(lnext, L - 1));  // unconditional (a load under a branch would make the compiler drain the others)
-        if (!KEEP) load_rows();
 
         float ssq = 0.f, acc[KC];
 #pragma unroll
@@ -241,14 +206,8 @@ __global__ __launch_bounds__(kLoopThreads) void layer_loop_kernel(LoopParams p) 
             for (int e = 0; e < 8; ++e) {
                 const float hf = (float)hv[u][e];
                 ssq += hf * hf;
-                if (KEEP) {
 #pragma unroll
-                    for (int k = 0; k < KC; ++k) acc[k] += hf * wg[KEEP ? k : 0][KEEP ? u : 0][e];
-                } else {
-                    const float x = hf * (float)gv[u][e];
-#pragma unroll
-                    for (int k = 0; k < KC; ++k) acc[k] += x * (float)wv[k][u][e];
-                }
+                for (int k = 0; k < KC; ++k) acc[k] += hf * wg[k][u][e];
             }
         ssq = wave_sum_to_last_row(ssq);
 #pragma unroll
@@ -326,22 +285,15 @@ __global__ __launch_bounds__(kLoopThreads) void layer_loop_kernel(LoopParams p) 
         __syncthreads();
         float bv = -INFINITY;
         int bi = 0x7fffffff;
-        if (Q4) {
-            float *xs = reinterpret_cast<float *>(xb + nv);
-            q4_prepare_planes<kLoopThreads, HEAD == 1>(xa, xb, xs, nv, d / p.group, p.group, tid);
-            q4_head_rows<HEAD == 1>(p.qweight, p.qscales, p.qzeros, d, p.group, row_begin, row_end, wave, kLoopWaves, lane,
-                                    xa, xb, xs, r, [&](int row, float v) {
-                                        if (v > bv) {  // rows ascend: the strict comparison keeps the lowest row
-                                            bv = v;
-                                            bi = row;
-                                        }
-                                    });
-        } else {
-            if (STREAM == 1 || (STREAM == 2 && meetings < kLoopStreamFirst))
-                head_argmax_rows<true>(p.lm_head, d, row_begin, row_end, wave, kLoopWaves, lane, xa, xb, r, bv, bi);
-            else
-                head_argmax_rows<false>(p.lm_head, d, row_begin, row_end, wave, kLoopWaves, lane, xa, xb, r, bv, bi);
-        }
+        float *xs = reinterpret_cast<float *>(xb + nv);
+        q4_prepare_planes<kLoopThreads, WIDE>(xa, xb, xs, nv, d / p.group, p.group, tid);
+        q4_head_rows<WIDE>(p.qweight, p.qscales, p.qzeros, d, p.group, row_begin, row_end, wave, kLoopWaves, lane, xa, xb, xs,
+                           r, [&](int row, float v) {
+                               if (v > bv) {  // rows ascend: the strict comparison keeps the lowest row
+                                   bv = v;
+                                   bi = row;
+                               }
+                           });
         if (lane == 0) {
             cv[wave] = bv;
             ci[wave] = bi;
@@ -459,34 +411,12 @@ __global__ void layer_loop_empty_kernel(int32_t *exit_layer, int32_t *token, int
     }
 }
 
-template <int KC, int VPT, bool EXACT>
+template <int KC, int VPT>
 static hipError_t launch_loop_one(LoopParams p, int max_wgs, hipStream_t s) {
-    constexpr bool kCanQ4 = KC * VPT <= 16 && KC <= 8;
-    // A token's later verifications re-read the head, and without the hint they find some of it in the last-level cache;
-    // but the first of them that goes without has to fetch what the hint kept out.  So a head that this cache can keep is
-    // read with the hint by a token's first four verifications (most tokens make one or two).  Without the hint / always /
-    // first four, head from HBM: 262 MB, 1 verification 60.5 / 54.9 / 54.9 us, 2 106.7 / 100.9 / 100.9, 4 198.7 / 192.2 /
-    // 192.0, 5 244.5 / 236.8 / 245.6, 8 382 / 374 / 383, 32 1479 / 1465 / 1481 (on two other boxes 1431 / 1462 and, back to
-    // back, 1465 / 1519); 205 MB, 1 52.8 / 48.3 / 48.3, 4 163 / 164 / 164, 5 199 / 203 / 210, 8 308 / 318 / 320, 32 1182 /
-    // 1244 / 1194; 164 MB, 1 46.2 / 42.2 / 41.9, 4 141 / 139 / 139, 8 265 / 269 / 274, 32 1007 / 1049 / 1016.
-    // Wider shapes have no registers for a second copy of the streaming loop (K = 8, d > 4096: 25 -> 54 spilled) and
-    // keep the hint.
-    const bool stream = head_streams(p.d, p.V, p.B);
-    void (*kern)(LoopParams) = stream ? layer_loop_kernel<KC, VPT, EXACT, 1> : layer_loop_kernel<KC, VPT, EXACT, 0>;
-    if constexpr (KC * VPT <= 8)
-        if (stream && !head_streams(p.d, p.V, 2)) kern = layer_loop_kernel<KC, VPT, EXACT, 2>;
-    size_t lds = (size_t)p.d * sizeof(float);
-    int quantum = kLoopWaves * kHeadRows;
-    if (p.qweight) {
-        if constexpr (kCanQ4) {
-            const bool wide = p.group % 32 == 0 && p.d % 32 == 0 && (reinterpret_cast<uintptr_t>(p.qweight) & 15) == 0;
-            kern = wide ? layer_loop_kernel<KC, VPT, EXACT, 0, 1> : layer_loop_kernel<KC, VPT, EXACT, 0, 2>;
-            lds += (size_t)(p.d / p.group) * sizeof(float);
-            quantum = kLoopWaves * kQ4HeadRows;
-        } else {
-            return hipErrorInvalidValue;
-        }
-    }
+    const size_t lds = (size_t)(p.d + p.d / p.group) * sizeof(float);
+    const int quantum = kLoopWaves * kQ4HeadRows;
+    const bool wide = p.group % 32 == 0 && p.d % 32 == 0 && (reinterpret_cast<uintptr_t>(p.qweight) & 15) == 0;
+    void (*kern)(LoopParams) = wide ? layer_loop_kernel<KC, VPT, true> : layer_loop_kernel<KC, VPT, false>;
     if (lds > 48 * 1024)  // per launch: the library keeps no state; a refusal shows as the launch error
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)lds);
@@ -507,30 +437,43 @@ static hipError_t launch_loop_one(LoopParams p, int max_wgs, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int KC, bool EXACT>
+template <int KC>
 static hipError_t launch_loop_vpt(const LoopParams &p, int max_wgs, hipStream_t s) {
-    if ((p.d >> 3) <= kLoopThreads) return launch_loop_one<KC, 1, EXACT>(p, max_wgs, s);
-    return launch_loop_one<KC, 2, EXACT>(p, max_wgs, s);
+    if ((p.d >> 3) <= kLoopThreads) return launch_loop_one<KC, 1>(p, max_wgs, s);
+    return launch_loop_one<KC, 2>(p, max_wgs, s);
 }
 
 // d <= 8192 (two 16-byte vectors per thread and row).  max_wgs bounds the grid (the workspace holds two
 // candidates per workgroup).
+static hipError_t launch_loop_walk(const LoopParams &p, int max_wgs, hipStream_t s) {
+    switch (p.K) {
+        case 1: return launch_loop_vpt<1>(p, max_wgs, s);
+        case 2: return launch_loop_vpt<2>(p, max_wgs, s);
+        case 3: return launch_loop_vpt<3>(p, max_wgs, s);
+        case 4: return launch_loop_vpt<4>(p, max_wgs, s);
+        case 5: return launch_loop_vpt<5>(p, max_wgs, s);
+        case 6: return launch_loop_vpt<6>(p, max_wgs, s);
+        case 7: return launch_loop_vpt<7>(p, max_wgs, s);
+        case 8: return launch_loop_vpt<8>(p, max_wgs, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_layer_loop(const LoopParams &p, int max_wgs, hipStream_t s) {
     if (p.L == 0) {
         hipLaunchKernelGGL(layer_loop_empty_kernel, dim3(1), dim3(64), 0, s, p.exit_layer, p.token, p.status, p.B);
         return hipGetLastError();
     }
-    switch (p.K) {
-        case 1: return launch_loop_vpt<1, true>(p, max_wgs, s);
-        case 2: return launch_loop_vpt<2, true>(p, max_wgs, s);
-        case 3: return launch_loop_vpt<3, true>(p, max_wgs, s);
-        case 4: return launch_loop_vpt<4, true>(p, max_wgs, s);
-        case 5: return launch_loop_vpt<5, true>(p, max_wgs, s);
-        case 6: return launch_loop_vpt<6, true>(p, max_wgs, s);
-        case 7: return launch_loop_vpt<7, true>(p, max_wgs, s);
-        case 8: return launch_loop_vpt<8, true>(p, max_wgs, s);
-        default: return launch_loop_vpt<16, false>(p, max_wgs, s);
+    // All predictors, then passes over the head for 16 verifications, wherever head_states.h has such a pass.  Layer by layer
+    // against that, us, one token, 32 layers: 32000 x 4096 fp16, one of them active and firing 54.7 / 54.7, eleven firing
+    // 511 / 58 (50280 x 2048 49.2 / 46.3 and 434 / 50; 16500 x 4096, whose 1032 tiles are one round and eight more than 256
+    // CUs have, 39.8 / 43.3 and 328 / 48); every active layer that does not fire costs layer by layer 1.75 more.
+    if (!p.qweight || head_states_q4_ok(p.group)) {
+        const hipError_t e = launch_loop_scores(p, s);
+        return e == hipSuccess ? launch_loop_verify(p, max_wgs, s) : e;
     }
+    const hipError_t e = launch_zero_i32(p.arrive, p.B + 1, s);  // the arrival counters and, behind them, the abort flag
+    return e == hipSuccess ? launch_loop_walk(p, max_wgs, s) : e;
 }
 
 }  // namespace specee

@@ -56,6 +56,32 @@ __device__ __forceinline__ int tree_node(int G, int nodes) {
     return b < nodes ? b : -1;
 }
 
+// The layer before l whose predictor is active (-1: none).  The mask is read 64 layers at a time: one by one, every
+// inactive layer on the way would cost a trip to memory of its own.
+__device__ __forceinline__ int previous_active(const int32_t *active, int l) {
+    if (!active) return l - 1;
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int hi = l; hi > 0; hi -= kWave) {  // layers [hi - 64, hi)
+        const int q = hi - 1 - lane;         // lane 0: the nearest
+        const unsigned long long m = __ballot(q >= 0 && active[q < 0 ? 0 : q] != 0);
+        if (m) return hi - 1 - (int)__builtin_ctzll(m);
+    }
+    return -1;
+}
+
+// What the scoring launch of a layer loop does beside it: nothing is verified yet, and the verifications' counters,
+// arg-max slots and notes are cleared (a kernel of its own would be a launch more).
+__device__ __forceinline__ void loop_begin(const PredictParams &p, size_t tok) {
+    if (threadIdx.x == 0) {
+        p.loop.ver_token[tok] = -1;
+        p.loop.hit[tok] = 0;
+    }
+    if (tok == 0) {
+        if (threadIdx.x == 0) *p.loop.arrive = *p.loop.abort = 0;
+        for (int i = threadIdx.x; i < kLoopKeys + kLoopNotes; i += blockDim.x) p.loop.lines[i * kLoopLine] = 0;
+    }
+}
+
 // KC: speculative rows held in flight (K <= KC).  VPT: 16-byte vectors per
 // thread per row (d/8 <= VPT * 512 * tiles).  SWEEP: the previous layer's local
 // probabilities are recomputed from that layer's hidden state instead of read,
@@ -97,6 +123,7 @@ __global__ __launch_bounds__(T) void predict_kernel(PredictParams p) {
     // ---- which layer supplies the previous probabilities (sweep only)
     int lprev = -1;
     if (SWEEP) {
+        if (p.loop.ver_token) loop_begin(p, tok);
         if (p.active && p.active[l] == 0) {
             if (tid < K) {
                 p.logits[tok * K + tid] = 0.f;
@@ -108,11 +135,7 @@ __global__ __launch_bounds__(T) void predict_kernel(PredictParams p) {
             }
             return;
         }
-        for (int q = l - 1; q >= 0; --q)
-            if (!p.active || p.active[q] != 0) {
-                lprev = q;
-                break;
-            }
+        lprev = previous_active(p.active, l);
     }
 
     // ---- the ids (and the token's done flag) are requested before anything else: the LM-head rows, the
@@ -370,7 +393,9 @@ __device__ __forceinline__ void q4_tail(const PredictParams &p, int b, int K, fl
 // EXACT: K == KC at compile time (see predict_kernel).  Every load is unconditional on a clamped, valid
 // address -- a load under a branch would make the compiler wait for all outstanding loads at the join
 // and turn the K rows into K serial trips to memory; unused data is zeroed by selects instead.
-template <int KC, int VPT, bool EXACT, int T = kPredictThreads, int MU = 1, bool TREE = false>
+// SWEEP: one workgroup per (layer, token), the previous active layer's probabilities from its hidden state, as in
+// predict_kernel.
+template <int KC, int VPT, bool EXACT, int T = kPredictThreads, int MU = 1, bool TREE = false, bool SWEEP = false>
 __global__ __launch_bounds__(T) void predict_q4_kernel(PredictParams p) {
     if (TREE && (int)blockIdx.x < tree_merge_wgs(p.tree.G)) {
         if ((int)blockIdx.x < p.tree.G) merge_one_tree<T>(p.tree, blockIdx.x);
@@ -384,13 +409,41 @@ __global__ __launch_bounds__(T) void predict_q4_kernel(PredictParams p) {
     const int tid = threadIdx.x;
     const int K = EXACT ? KC : p.K, H = p.H, d = p.d;
     const int nv = d >> 3, ng = d / p.group;
+    int lprev = -1;
+    if (SWEEP) {  // p becomes this layer's call
+        const int l = blockIdx.y;
+        const size_t tok = (size_t)l * p.B + b;
+        if (p.loop.ver_token) loop_begin(p, tok);
+        if (p.active && p.active[l] == 0) {
+            if (tid < K) {
+                p.logits[tok * K + tid] = 0.f;
+                p.probs[tok * K + tid] = 0.f;
+            }
+            if (tid == 0) {
+                p.scores[tok] = 0.f;
+                p.exit_flags[tok] = 0;
+            }
+            return;
+        }
+        lprev = previous_active(p.active, l);
+        const size_t first = (size_t)l * p.B;
+        p.W1 += (size_t)l * H * 3 * K;
+        p.w2 += (size_t)l * H;
+        if (p.b1) p.b1 += (size_t)l * H;
+        if (p.b2) p.b2 += l;
+        p.logits += first * K;
+        p.probs += first * K;
+        p.scores += first;
+        p.exit_flags += first;
+    }
 
     // ---- requests that do not depend on the ids
     MlpRow<KC> rowm[MU];
 #pragma unroll
     for (int m = 0; m < MU; ++m) mlp_row_load<KC>(rowm[m], p.W1, p.b1, p.w2, K, H, tid + m * T);
-    const half_t *hrow = p.hidden + (size_t)b * d;
-    half8 hv[VPT], gv[VPT];
+    const half_t *hrow = p.hidden + ((SWEEP ? (size_t)blockIdx.y * p.B : 0) + b) * d;
+    const half_t *hprow = SWEEP && lprev >= 0 ? p.hidden + ((size_t)lprev * p.B + b) * d : hrow;  // always valid
+    half8 hv[VPT], gv[VPT], hp[VPT];
     int vc[VPT];
 #pragma unroll
     for (int u = 0; u < VPT; ++u) {
@@ -399,12 +452,20 @@ __global__ __launch_bounds__(T) void predict_q4_kernel(PredictParams p) {
         const half8 h8 = load_half8(hrow + vc[u] * 8), g8 = load_half8(p.gamma + vc[u] * 8);
         hv[u] = v < nv ? h8 : zero_half8();  // a zero hidden state silences the clamped duplicate
         gv[u] = g8;
+        if (SWEEP) {
+            const half8 p8 = load_half8(hprow + vc[u] * 8);
+            hp[u] = v < nv ? p8 : zero_half8();
+        }
     }
     float prev[KC];
 #pragma unroll
-    for (int k = 0; k < KC; ++k) {
-        const float pv = p.prev[(size_t)b * K + min(k, K - 1)];
-        prev[k] = (k < K) ? pv : 0.f;
+    for (int k = 0; k < KC; ++k) prev[k] = 0.f;
+    if (!SWEEP || p.prev) {
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+            const float pv = p.prev[(size_t)b * K + min(k, K - 1)];
+            prev[k] = (k < K) ? pv : 0.f;
+        }
     }
     const int32_t *donep = p.done ? p.done + b : p.ids;  // always a valid address
     const int dn_raw = *donep;
@@ -443,11 +504,11 @@ __global__ __launch_bounds__(T) void predict_q4_kernel(PredictParams p) {
             qz[k][u] = p.qzeros[gi];
         }
 
-    float ssq = 0.f, acc[KC];
+    float ssq = 0.f, ssq_p = 0.f, acc[KC], acc_p[KC];
 #pragma unroll
-    for (int k = 0; k < KC; ++k) acc[k] = 0.f;
+    for (int k = 0; k < KC; ++k) acc[k] = acc_p[k] = 0.f;
     auto dot8 = [&](const half8 &h8, const half8 &g8, const uint32_t (&w)[KC], const half_t (&sc)[KC],
-                    const half_t (&zp)[KC]) {
+                    const half_t (&zp)[KC], float &ssq, float (&acc)[KC]) {
         float x[8], xs = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -478,7 +539,8 @@ __global__ __launch_bounds__(T) void predict_q4_kernel(PredictParams p) {
             sc[k] = qs[k][u];
             zp[k] = qz[k][u];
         }
-        dot8(hv[u], gv[u], w, sc, zp);
+        dot8(hv[u], gv[u], w, sc, zp, ssq, acc);
+        if (SWEEP) dot8(hp[u], gv[u], w, sc, zp, ssq_p, acc_p);
     }
     // d larger than VPT * 512 vectors: remaining tiles, same arithmetic
     for (int v = tid + VPT * T; v < nv; v += T) {
@@ -492,9 +554,37 @@ __global__ __launch_bounds__(T) void predict_q4_kernel(PredictParams p) {
             sc[k] = p.qscales[gi];
             zp[k] = p.qzeros[gi];
         }
-        dot8(h8, g8, w, sc, zp);
+        dot8(h8, g8, w, sc, zp, ssq, acc);
+        if (SWEEP) dot8(load_half8(hprow + v * 8), g8, w, sc, zp, ssq_p, acc_p);
     }
 
+    if (SWEEP && lprev >= 0) {  // uniform over the workgroup
+        __shared__ float red_p[kWaves][KC + 1];
+        const int lane = tid & (kWave - 1), wave = tid >> 6;
+        ssq_p = wave_sum_to_last_row(ssq_p);
+#pragma unroll
+        for (int k = 0; k < KC; ++k) acc_p[k] = wave_sum_to_last_row(acc_p[k]);
+        if (lane == kWave - 1) {
+            red_p[wave][0] = ssq_p;
+#pragma unroll
+            for (int k = 0; k < KC; ++k) red_p[wave][1 + k] = acc_p[k];
+        }
+        __syncthreads();
+        ssq_p = 0.f;
+        float zp[KC];
+#pragma unroll
+        for (int k = 0; k < KC; ++k) zp[k] = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            ssq_p += red_p[w][0];
+#pragma unroll
+            for (int k = 0; k < KC; ++k) zp[k] += red_p[w][1 + k];
+        }
+        const float rp = 1.0f / sqrtf(ssq_p * (1.0f / (float)d) + p.eps);
+#pragma unroll
+        for (int k = 0; k < KC; ++k) zp[k] = bad_id ? quiet_nan() : zp[k] * rp;
+        local_softmax<KC>(zp, K, prev);
+    }
     q4_tail<KC, T, MU>(p, b, K, ssq, acc, bad_id, rowm, prev, red, red_u);
 }
 
@@ -872,6 +962,42 @@ hipError_t launch_tree_nodes(const PredictParams &p, int N, const int32_t *paren
     hipLaunchKernelGGL(tree_tail_kernel, dim3(p.tree.G), dim3(kTreeTailThreads), (size_t)2 * N * sizeof(int32_t), s, p,
                        N, parent, path_exit);
     return hipGetLastError();
+}
+
+// Every (layer, token) pair of a layer loop, fp16 or quantised head (K <= 8 there, d <= 8192)
+template <int KC>
+static hipError_t launch_q4_sweep(const PredictParams &p, hipStream_t s) {
+    const dim3 grid(p.B, p.L), block(kPredictThreads);
+    if ((p.d >> 3) <= kPredictThreads)
+        hipLaunchKernelGGL((predict_q4_kernel<KC, 1, true, kPredictThreads, 1, false, true>), grid, block, 0, s, p);
+    else
+        hipLaunchKernelGGL((predict_q4_kernel<KC, 2, true, kPredictThreads, 1, false, true>), grid, block, 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_loop_scores(const LoopParams &lp, hipStream_t s) {
+    PredictParams p{};
+    p.d = lp.d; p.V = lp.V; p.K = lp.K; p.H = lp.H; p.eps = lp.eps; p.threshold = lp.threshold;
+    p.B = lp.B; p.L = lp.L;
+    p.hidden = lp.hidden; p.gamma = lp.gamma; p.lm_head = lp.lm_head; p.ids = lp.ids; p.prev = lp.prev0;
+    p.W1 = lp.W1; p.b1 = lp.b1; p.w2 = lp.w2; p.b2 = lp.b2;
+    p.active = lp.active;
+    p.qweight = lp.qweight; p.qscales = lp.qscales; p.qzeros = lp.qzeros; p.group = lp.group;
+    p.logits = lp.logits; p.probs = lp.probs; p.scores = lp.scores; p.exit_flags = lp.exit_flags;
+    p.loop.ver_token = lp.ver_token; p.loop.hit = lp.hit; p.loop.arrive = lp.arrive; p.loop.abort = lp.abort;
+    p.loop.lines = lp.lines;
+    if (!p.qweight) return launch_kc<true, false>(p, s);
+    switch (p.K) {
+        case 1: return launch_q4_sweep<1>(p, s);
+        case 2: return launch_q4_sweep<2>(p, s);
+        case 3: return launch_q4_sweep<3>(p, s);
+        case 4: return launch_q4_sweep<4>(p, s);
+        case 5: return launch_q4_sweep<5>(p, s);
+        case 6: return launch_q4_sweep<6>(p, s);
+        case 7: return launch_q4_sweep<7>(p, s);
+        case 8: return launch_q4_sweep<8>(p, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_predict_sweep(const PredictParams &p, int32_t *first_exit, hipStream_t s) {

@@ -1,6 +1,6 @@
 // Streaming of a 4-bit group-quantised LM head against one normalised hidden state held in LDS: the inner loop of
 // the quantised full-vocabulary head (paper Sec. 4.1, Sec. 4.3.3 in the weight-quantised setting of Sec. 7.1 /
-// 7.3), shared by the stand-alone kernels and by the verification pass of the persistent layer loop.
+// 7.3), shared by the stand-alone kernels and by the verifications of the layer loop that goes layer by layer.
 #pragma once
 #include "device_utils.h"
 

@@ -82,8 +82,8 @@ TreeLayout tree_layout(int S, int n_total, int Mcap) {
     return L;
 }
 
-// Workspace of the persistent layer loop: arrival counters [B] and the abort flag (cleared at every call),
-// then two buffers of arg-max candidates, one (value, row) pair per workgroup.
+// Workspace of the layer loop: arrival counters [B] and the abort flag (cleared at every call), then the arg-max slots and
+// notes of the passes, or two buffers of arg-max candidates, one (value, row) pair per workgroup.
 constexpr int kLoopMaxTokens = 64;
 constexpr int kLoopMaxWgs = 1024;
 struct LoopLayout {
@@ -603,9 +603,11 @@ static int layer_loop_common(const specee_dims *dm, int L, int B, const specee_h
     p.cand_val = reinterpret_cast<float *>(ws + lay.val_off);
     p.cand_idx = reinterpret_cast<int32_t *>(ws + lay.idx_off);
     p.spin_limit = spin_limit > 0 ? spin_limit : (1ll << 20);
+    p.lines = reinterpret_cast<unsigned long long *>(ws + lay.val_off);
+    static_assert(sizeof(unsigned long long) * (kLoopKeys + kLoopNotes) * kLoopLine <= 4 * kLoopMaxWgs * sizeof(float),
+                  "the slots and notes take the place of the candidates");
     hipStream_t st = static_cast<hipStream_t>(stream);
     // (an empty stack is handled by the launcher without touching any input: they may all be null then)
-    if (L > 0 && launch_zero_i32(p.arrive, lay.flag_ints, st) != hipSuccess) return SPECEE_EHIP;
     // the launcher caps the grid at kLoopMaxWgs workgroups; each candidate buffer holds one entry per workgroup
     return launch_layer_loop(p, kLoopMaxWgs, st) == hipSuccess ? SPECEE_OK : SPECEE_EHIP;
 }

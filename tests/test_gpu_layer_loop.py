@@ -344,3 +344,51 @@ def test_layer_loop_other_widths(sp, oracle, seed, K, d, H):
     oracle.set_threads(8)
     check_loop(oracle, sp, t, 0.45, what=f"loop K={K} d={d}")
     oracle.set_threads(1)
+
+
+@pytest.mark.parametrize("d,V,L,B,group,plant", [
+    (1024, 301, 70, 3, 0, [68, None, 5]),           # more than one window of 64 layers, eight passes and more
+    (64, 17, 2, 17, 0, [1] * 16 + [None]),          # 16 pairs and one more; two tiles of rows for the whole grid
+    (520, 5000, 3, 64, 0, [b % 4 if b % 4 < 3 else None for b in range(64)]),  # every token's next layer before any second
+    (2048, 20011, 5, 1, 0, [3]), (1536, 9001, 4, 2, 0, [None, 2]),             # groups of wavefronts that share the tiles
+    (4608, 16, 3, 1, 0, [None]), (8192, 1, 2, 1, 0, [0]),                      # two passes over the rows, one tile
+    (192, 9000, 3, 9, 64, [2] * 9), (4096, 1601, 17, 2, 64, [16, 3]),
+    (512, 20011, 4, 1, 128, [2]), (3072, 1500, 6, 4, 128, [5, 0, None, 5]), (8192, 1203, 2, 9, 128, [1] * 9),
+])
+def test_layer_loop_verifies_what_fired_sixteen_at_a_time(sp, d, V, L, B, group, plant):
+    """Every active layer fires.  A verification's sums do not depend on which others share the pass, so tokens, hits and
+    exits are those of specee_verify on the same hidden states, to the bit."""
+    from test_gpu_verify import head_rows
+    rng = np.random.default_rng(d + V + L)
+    K, H = 3, 40
+    head, _, _ = head_rows(rng, V, d, group)
+    h = dev(rng.standard_normal((L, B, d)).astype(np.float16))
+    g = dev((1 + 0.05 * rng.standard_normal(d)).astype(np.float16))
+    verify, loop = (sp.verify_q4, sp.layer_loop_q4) if group else (sp.verify, sp.layer_loop)
+    states = h.reshape(L * B, d)
+    pad = torch.cat([states, states[:1].expand(-len(states) % 16, d)])
+    tok = np.concatenate([host(verify(s.contiguous(), g, *head, torch.zeros(16, K, dtype=torch.int32, device="cuda"))["token"])
+                          for s in pad.split(16)])[:L * B].reshape(L, B)
+    active = (rng.random(L) < 0.8).astype(np.int32)
+    ids = np.full((B, K), V - 1, np.int32)          # (equal ids are allowed; V = 1: everything hits)
+    for b, l in enumerate(plant):
+        if l is not None:
+            active[l] = 1
+            ids[b, b % K] = tok[l, b]
+    W1, w2 = (dev((0.1 * rng.standard_normal(s)).astype(np.float16)) for s in ((L, H, 3 * K), (L, H)))
+    out = {k: host(v) for k, v in loop(h, g, *head, dev(ids), W1, w2, active=dev(active), threshold=-1.0).items()
+           if k != "_workspace"}
+    assert not out["status"].any()
+    for b in range(B):
+        fires = np.flatnonzero(active)
+        hits = [l for l in fires if tok[l, b] in ids[b]]
+        last = hits[0] if hits else L
+        seen = [l for l in fires if l <= last]
+        assert out["exit_layer"][b] == (hits[0] if hits else -1) and out["token"][b] == (tok[last, b] if hits else -1)
+        ver, hit = np.full(L, -1), np.zeros(L, int)
+        ver[seen] = tok[seen, b]
+        hit[hits[:1]] = 1
+        assert np.array_equal(out["ver_token"][:, b], ver) and np.array_equal(out["hit"][:, b], hit)
+        assert np.array_equal(np.flatnonzero(out["exit"][:, b]), seen)
+        off = np.setdiff1d(np.arange(L), seen)
+        assert (out["scores"][seen, b] > 0).all() and not out["scores"][off, b].any() and not out["probs"][off, b].any()
