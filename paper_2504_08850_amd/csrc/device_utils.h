@@ -71,6 +71,18 @@ __device__ __forceinline__ void dpp_argmax_step(float &v, int &i) {
     }
 }
 
+// Two loads of whole lines -- lane (q, c): 16-byte piece q + 4 * (c / 8) of row c % 8 (a) and of row 8 + c % 8 (b) -- as
+// two operands: pieces 0..3 (a) and 4..7 (b) of rows 0..15, piece q (4 + q) of row c on lane (q, c).
+__device__ __forceinline__ void whole_lines(uintx4 &a, uintx4 &b) {
+    constexpr int kRor8 = 0x128;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int x = (int)a[e], y = (int)b[e];
+        a[e] = (uint32_t)__builtin_amdgcn_update_dpp(x, y, kRor8, 0xF, 0xC, false);  // lanes 8..15: b's lanes 0..7
+        b[e] = (uint32_t)__builtin_amdgcn_update_dpp(y, x, kRor8, 0xF, 0x3, false);  // lanes 0..7: a's lanes 8..15
+    }
+}
+
 // Arg-max over 16 lanes (a DPP row), lowest index on ties; every lane returns its row's winner.
 __device__ __forceinline__ void row16_argmax(float &v, int &i) {
     dpp_argmax_step<kDppXor1>(v, i);

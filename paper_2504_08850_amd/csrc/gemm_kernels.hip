@@ -6,14 +6,13 @@
 //
 // Mapping onto v_mfma_f32_16x16x32_f16 (64 lanes; lane = 16*q + c):
 //   A operand = LM-head rows: lane holds 8 consecutive halves of row (m0 + c) at a k-offset
-//               chosen by q -- exactly one 16-byte global load, so streamed rows feed the
-//               matrix core with no LDS hop;
+//               chosen by q -- as one 16-byte global load leaves them, so streamed rows feed
+//               the matrix core with no LDS hop;
 //   B operand = x = h*gamma for hidden state (n0 + c), same k-offsets, shared by the four
 //               wavefronts through double-buffered LDS;
 //   D         = lane holds Y[m0 + 4q .. 4q+3][n0 + c]  -> one 16-byte store.
 // Any assignment of k-slots to (q, element) is valid as long as A and B use the same one;
-// it is chosen so that the four q-groups of a row read 128 contiguous bytes per
-// 64-element stage (q*32 bytes + 16*j).
+// it is chosen so that the loads of a 64-element stage take 128 contiguous bytes of a row.
 //
 // x is not representable in fp16 (it is a product of two fp16 numbers), and rounding it
 // would cost ~4e-4 of a logit's standard deviation.  It is split exactly instead:
@@ -37,7 +36,9 @@ constexpr int kLdsRow = kKC + 8;  // halves per LDS row: 144 bytes, keeps 16-byt
 // branches (loads past the end are issued on clamped addresses and contribute zeros): a load
 // under a branch makes the compiler drain every outstanding load at the join.
 // NT: n-tiles of 16 hidden states per workgroup, two or four.
-template <int TPW, int MODE, int PD, int NT>
+// LINES: a load takes whole 128-byte lines of eight rows, with the non-temporal hint, and two of them become the operands
+// of two matrix steps by exchanging halves of 16 lanes; otherwise two loads share the lines of sixteen rows.
+template <int TPW, int MODE, int PD, int NT, bool LINES>
 // (two wavefronts per SIMD asked for: unbounded, the 256-row shape took 272 registers, i.e. one workgroup per CU)
 __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmParams p) {
     constexpr int kNB = 16 * NT;                 // hidden states per workgroup
@@ -61,13 +62,17 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
     const int nchunks = (d + kKC - 1) / kKC;
     const int m0 = blockIdx.x * (16 * TPW * kGemmWaves);
 
-    // ---- A side: this lane's rows (clamped: rows past the end are loaded but never stored)
-    const half_t *rowptr[TPW];
+    // ---- A side: this lane's rows (clamped: rows past the end are loaded but never stored), row c of a tile or rows c % 8
+    // and 8 + c % 8, and its first element of a stage
+    const half_t *rowptr[TPW][2];
 #pragma unroll
-    for (int tp = 0; tp < TPW; ++tp) {
-        const int m = min(m0 + (wave * TPW + tp) * 16 + c, M - 1);
-        rowptr[tp] = p.lm_head + (size_t)m * d;
-    }
+    for (int tp = 0; tp < TPW; ++tp)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            rowptr[tp][j] = p.lm_head + (size_t)min(m0 + (wave * TPW + tp) * 16 + (LINES ? (c & 7) + 8 * j : c), M - 1) * d;
+    const int piece = LINES ? 8 * (q + 4 * (c >> 3)) : q * 16;
+    // elements of step j that this lane multiplies
+    auto elem = [&](int j) { return LINES ? j * 32 + q * 8 : q * 16 + j * 8; };
     // ---- B side: this thread stages vector column vc of hidden states r0 (and r0+32)
     const int vc = tid & 7, r0 = tid >> 3;
     const half_t *hptr[HV];
@@ -79,13 +84,20 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
         hptr[i] = p.hidden + (size_t)(hok[i] ? n : 0) * d;
     }
 
-    half8 a_buf[PD][TPW][2], h_buf[PD][HV], g_buf[PD];
+    uintx4 a_buf[PD][TPW][2];
+    half8 h_buf[PD][HV], g_buf[PD];
     auto issue = [&](int kc, int slot) {
         const int k0 = kc * kKC;
 #pragma unroll
         for (int tp = 0; tp < TPW; ++tp)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) a_buf[slot][tp][j] = load_half8(rowptr[tp] + min(k0 + q * 16 + j * 8, d - 8));
+            for (int j = 0; j < 2; ++j) {
+                if constexpr (LINES)  // (past the last stage no row: with the hint it would come from memory again)
+                    a_buf[slot][tp][j] = __builtin_nontemporal_load(reinterpret_cast<const uintx4 *>(
+                        k0 < d ? rowptr[tp][j] + (k0 + piece) : p.gamma));
+                else
+                    a_buf[slot][tp][j] = *reinterpret_cast<const uintx4 *>(rowptr[tp][j] + min(k0 + piece + j * 8, d - 8));
+            }
         const int ko = min(k0 + vc * 8, d - 8);
         g_buf[slot] = load_half8(p.gamma + ko);
 #pragma unroll
@@ -131,9 +143,13 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
             half8 a_cur[TPW][2];
 #pragma unroll
             for (int tp = 0; tp < TPW; ++tp)
+            {
+                uintx4 a[2] = {a_buf[u][tp][0], a_buf[u][tp][1]};
+                if (LINES) whole_lines(a[0], a[1]);
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
-                    a_cur[tp][j] = (kc * kKC + q * 16 + j * 8 < d) ? a_buf[u][tp][j] : zero_half8();
+                    a_cur[tp][j] = kc * kKC + elem(j) < d ? __builtin_bit_cast(half8, a[j]) : zero_half8();
+            }
             __syncthreads();
             issue(kc + PD, u);
 #pragma unroll
@@ -141,8 +157,8 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
                 half8 bh[NT], bl[NT];
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
-                    bh[nt] = *reinterpret_cast<const half8 *>(&lds_hi[buf][nt * 16 + c][q * 16 + j * 8]);
-                    bl[nt] = *reinterpret_cast<const half8 *>(&lds_lo[buf][nt * 16 + c][q * 16 + j * 8]);
+                    bh[nt] = *reinterpret_cast<const half8 *>(&lds_hi[buf][nt * 16 + c][elem(j)]);
+                    bl[nt] = *reinterpret_cast<const half8 *>(&lds_lo[buf][nt * 16 + c][elem(j)]);
                 }
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
@@ -245,11 +261,17 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
     }
 }
 
+// Whole lines: of rows that consist of them, and on heads of more than 128 MB.  Halves of lines / whole lines, us, 24 and 64
+// states: 128256 x 8192 399 / 373, 437 / 411; 131072 x 4096 259 / 218, 270 / 234; 32000 x 4096 66.2 / 61.2, 76 / 70.4;
+// 50280 x 2048 59.0 / 53.0, 68.4 / 62.5; 20000 x 2048 (82 MB, from the last-level cache) 23.0 / 29.4, 30.6 / 34.2;
+// 20011 x 4104 62.7 / 65.0, 75.4 / 76.5.
 template <int MODE, int TPW, int PD, int NT>
 static void launch_one(const GemmParams &p, hipStream_t st) {
     const int rows_per_wg = 16 * TPW * kGemmWaves;
     dim3 grid((p.V + rows_per_wg - 1) / rows_per_wg, 1, (p.N + 16 * NT - 1) / (16 * NT));
-    hipLaunchKernelGGL((full_head_gemm_kernel<TPW, MODE, PD, NT>), grid, dim3(kGemmThreads), 0, st, p);
+    const bool lines = p.d % kKC == 0 && (size_t)p.V * p.d * sizeof(half_t) > ((size_t)128 << 20);
+    hipLaunchKernelGGL((lines ? full_head_gemm_kernel<TPW, MODE, PD, NT, true> : full_head_gemm_kernel<TPW, MODE, PD, NT, false>),
+                       grid, dim3(kGemmThreads), 0, st, p);
 }
 
 // 256 rows per workgroup when that still gives >= 400 workgroups, otherwise 128
@@ -257,10 +279,10 @@ static int lm_head_tpw(int V) {
     return (V + 255) / 256 >= 400 ? 4 : 2;
 }
 
-// Measured on MI355X (N = 16..64): 256-row tiles with two stages in flight for large vocabularies
-// (4.9 TB/s at 128256 x 8192), 128-row tiles with four stages for 32000-row heads (4.3-4.4 TB/s).
+// Measured on MI355X (N = 64): 256-row tiles with two stages in flight for large vocabularies (411 us, 5.1 TB/s at 128256 x
+// 8192), 128-row tiles with four stages for 32000-row heads (70.4 us, 3.7 TB/s at 32000 x 4096).
 // Up to 32 hidden states the 128-row tiles carry two n-tiles instead of four: less of x to build, read back and multiply
-// per stage (head from HBM: 32000 x 4096, N = 32 71.0 -> 63.7 us).  The 256-row tiles do not gain and keep four.  Up to 16
+// per stage (32000 x 4096, N = 32: 62 us instead of 70).  The 256-row tiles do not gain and keep four.  Up to 16
 // states, and more of them on a small head, go to head_states.hip.
 template <int MODE>
 static hipError_t launch_stream(const GemmParams &p, hipStream_t st) {

@@ -117,18 +117,6 @@ __device__ __forceinline__ int hs_bound(float ssq) {
     return ((int)(__builtin_bit_cast(uint32_t, ssq) >> 23) - 127 + 2) >> 1;
 }
 
-// Two loads of whole lines -- lane (q, c): 16-byte piece q + 4 * (c / 8) of row c % 8 (a) and of row 8 + c % 8 (b) -- as
-// two operands: pieces 0..3 (a) and 4..7 (b) of rows 0..15, piece q (4 + q) of row c on lane (q, c).
-__device__ __forceinline__ void hs_lines(uintx4 &a, uintx4 &b) {
-    constexpr int kRor8 = 0x128;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int x = (int)a[e], y = (int)b[e];
-        a[e] = (uint32_t)__builtin_amdgcn_update_dpp(x, y, kRor8, 0xF, 0xC, false);  // lanes 8..15: b's lanes 0..7
-        b[e] = (uint32_t)__builtin_amdgcn_update_dpp(y, x, kRor8, 0xF, 0x3, false);  // lanes 0..7: a's lanes 8..15
-    }
-}
-
 // LW = 2: words between lane groups, so that word j holds elements of sub-chunk j / LW only
 template <int LW>
 __device__ __forceinline__ void hs_exchange(uint32_t (&w)[4]) {
@@ -326,7 +314,7 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
                 if constexpr (Q4) {
 #pragma unroll
                     for (int ch = 0; ch < CPW; ++ch) {
-                        if (ch % 2 == 0) hs_lines(a[slot][ch], a[slot][ch + 1]);
+                        if (ch % 2 == 0) whole_lines(a[slot][ch], a[slot][ch + 1]);
                         uint32_t w[4] = {a[slot][ch][0], a[slot][ch][1], a[slot][ch][2], a[slot][ch][3]};
                         hs_exchange<LW>(w);
 #pragma unroll
@@ -354,7 +342,7 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
                     floatx4 acc1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int k = 0; k < kSteps; k += 2) {
-                        hs_lines(a[slot][k], a[slot][k + 1]);
+                        whole_lines(a[slot][k], a[slot][k + 1]);
 #pragma unroll
                         for (int u = 0; u < 2; ++u) {
                             half8 b = __builtin_bit_cast(half8, a[slot][k + u]);
