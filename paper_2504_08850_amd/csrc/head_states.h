@@ -8,7 +8,7 @@
 //     into matrix operands once and stays in registers (128 of them); nothing is shared between the wavefronts while
 //     they stream, so there is neither LDS traffic nor a barrier per stage;
 //   * a tile is 16 rows.  A wavefront's 1024 bytes (fp16) or 256 bytes (codes) of each row come in 16-byte loads, each
-//     instruction whole 128-byte lines of eight rows, with the non-temporal hint; two such loads become the operands
+//     instruction whole 128-byte lines of eight rows, with the non-temporal hint (hs_hint says when); two such loads become the operands
 //     of two matrix steps by exchanging halves of 16 lanes.  Every register of a tile is asked for again, for a later
 //     tile, as soon as it has been used: 128 KB per CU are in flight all the time;
 //   * every eight tiles (four, with sixteen wavefronts) the partial sums meet in LDS and are added in ascending order of elements.
@@ -144,7 +144,8 @@ __device__ __forceinline__ int hs_element(int j, int q) {
 // emit(row, n, y) is called by the lanes of the first wavefronts, all of a wavefront's lanes together and rows ascending
 // for each lane: row may lie past the end (>= V), y[r] is the logit of state n + r, n = 4 * (lane / 16).
 // LW: 0 = fp16 head, else the group is 32 * LW.  RAGGED: rows end before the passes do (d != passes * chunks * 128).
-template <int LW, int CPW, bool RAGGED, class StateRow, class Emit>
+// NT: the rows are read with the non-temporal hint.
+template <int LW, int CPW, bool RAGGED, bool NT, class StateRow, class Emit>
 __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned char *smem, int row_groups, int tile_begin,
                                                  int tile_end, StateRow state_row, Emit emit) {
     constexpr bool Q4 = LW != 0;
@@ -190,7 +191,9 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
             for (int u = 0; u < 2; ++u) {
                 const uint32_t row = (uint32_t)min((ln & 7) + 8 * u, last) * row_bytes;
                 const char *at = RAGGED ? base + (row + min(piece + 128 * i, limit)) : base + (row + piece) + 128 * i;
-                if constexpr (Q4)
+                if constexpr (Q4 && !NT)
+                    a[slot][2 * i + u] = *reinterpret_cast<const uintx4_a4 *>(at);
+                else if constexpr (Q4)
                     a[slot][2 * i + u] = __builtin_nontemporal_load(reinterpret_cast<const uintx4_a4 *>(at));
                 else
                     a[slot][2 * i + u] = __builtin_nontemporal_load(reinterpret_cast<const uintx4 *>(at));
@@ -408,9 +411,19 @@ inline int hs_chunks_per_wave(int d, int lw) {
     return sh.waves % 4 == 0 && d == sh.passes * sh.chunks * kHsChunk ? 4 : 2;
 }
 
-// f(LW, CPW, RAGGED as integral constants, shape) for a head (group 0: fp16)
+// The hint (us, 16 states, without / with it): the fp16 head gains wherever it comes from memory and loses little where not
+// (50280 x 2048 46.9 / 42.0; 16000 x 2048, one head after the other 20.2 / 18.4, few heads that stay in the last-level cache
+// 17.2 / 18.0).  Codes: one layer's weights or so pass through that cache between two verifications, and a small head
+// stays there: groups of 128, from the cache and from memory, 32000 x 4096 22.8 / 25.5 and 25.5 / 24.7, 24001 x 4608 25.6 /
+// 28.0 and 28.6 / 28.2; from 82 MB on it does not pay: 32000 x 5120, groups of 64, 39.6 / 39.1 and 40.8 / 39.0, 32000 x 8192
+// 49.6 / 47.3 and 50 / 47.
+inline bool hs_hint(int d, int V, int lw) {
+    return lw == 0 || (size_t)V * d / 2 > ((size_t)72 << 20);
+}
+
+// f(LW, CPW, RAGGED, NT as integral constants, shape) for a head (group 0: fp16)
 template <class F>
-hipError_t hs_dispatch(int d, int group, F f) {
+hipError_t hs_dispatch(int d, int V, int group, F f) {
     const int lw = hs_words(group);
     if (lw < 0) return hipErrorInvalidValue;
     const int cpw = hs_chunks_per_wave(d, lw);
@@ -419,14 +432,14 @@ hipError_t hs_dispatch(int d, int group, F f) {
     std::integral_constant<int, 0> w0;
     std::integral_constant<int, 2> two;
     std::integral_constant<int, 4> four;
-    if (lw == 0) return ragged ? f(w0, four, std::true_type{}, sh) : f(w0, four, std::false_type{}, sh);
-    if (lw == 4)
-        return cpw == 4 ? f(four, four, std::false_type{}, sh)
-               : ragged ? f(four, two, std::true_type{}, sh)
-                        : f(four, two, std::false_type{}, sh);
-    return cpw == 4 ? f(two, four, std::false_type{}, sh)
-           : ragged ? f(two, two, std::true_type{}, sh)
-                    : f(two, two, std::false_type{}, sh);
+    std::false_type no;
+    std::true_type yes;
+    if (lw == 0) return ragged ? f(w0, four, yes, yes, sh) : f(w0, four, no, yes, sh);
+    auto codes = [&](auto w, auto nt) {
+        return cpw == 4 ? f(w, four, no, nt, sh) : ragged ? f(w, two, yes, nt, sh) : f(w, two, no, nt, sh);
+    };
+    const bool hint = hs_hint(d, V, lw);
+    return lw == 4 ? (hint ? codes(four, yes) : codes(four, no)) : hint ? codes(two, yes) : codes(two, no);
 }
 
 }  // namespace specee

@@ -18,7 +18,7 @@ struct HeadStatesParams {
     const int32_t *gate, *done;
 };
 
-template <int LW, int CPW, bool RAGGED, bool ARGMAX>
+template <int LW, int CPW, bool RAGGED, bool NT, bool ARGMAX>
 __global__ __launch_bounds__(hs_max_waves(CPW) * kWave) void head_states_kernel(HeadStatesParams p) {
     constexpr int kHsBlock = hs_block(CPW);
     extern __shared__ __attribute__((aligned(16))) unsigned char hs_smem[];
@@ -41,7 +41,7 @@ __global__ __launch_bounds__(hs_max_waves(CPW) * kWave) void head_states_kernel(
     // (several passes over the rows: the sums of as many tiles wait in LDS as there is room for)
     const int most = p.hs.passes > 1 ? kHsMaxTiles : t1 - t0;
     for (int t = t0; t < t1; t += most)
-        head_states_rows<LW, CPW, RAGGED>(
+        head_states_rows<LW, CPW, RAGGED, NT>(
             p.hs, hs_smem, 1, t, min(t1, t + most), [&](int n) { return p.hidden + (size_t)min(n0 + n, p.N - 1) * p.hs.d; },
             [&](int row, int n, floatx4 y) {
 #pragma unroll
@@ -91,13 +91,13 @@ int head_states_workgroups(int d, int V, int group, int limit) {
     return std::min({2 * sh.waves <= hs_max_waves(sh.cpw) ? 512 : 256, tiles, limit});
 }
 
-template <int LW, int CPW, bool RAGGED, bool ARGMAX>
+template <int LW, int CPW, bool RAGGED, bool NT, bool ARGMAX>
 static hipError_t launch_hs(HeadStatesParams &p, const HsShape &sh, int wgs, hipStream_t s) {
     const int tiles = (p.hs.V + kHsTile - 1) / kHsTile;
     p.tiles_per_wg = tiles / wgs;
     p.tiles_over = tiles % wgs;
     p.hs.passes = sh.passes; p.hs.chunks = sh.chunks; p.hs.subs = sh.subs; p.hs.buffers = sh.buffers;
-    auto kern = head_states_kernel<LW, CPW, RAGGED, ARGMAX>;
+    auto kern = head_states_kernel<LW, CPW, RAGGED, NT, ARGMAX>;
     // per launch: the library keeps no state; a refusal shows as the launch error
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh.lds);
     hipLaunchKernelGGL(kern, dim3(wgs, (p.N + kHsStates - 1) / kHsStates), dim3(sh.waves * kWave), sh.lds, s, p);
@@ -106,8 +106,8 @@ static hipError_t launch_hs(HeadStatesParams &p, const HsShape &sh, int wgs, hip
 
 template <bool ARGMAX>
 static hipError_t launch_hs_format(HeadStatesParams &p, int wgs, hipStream_t s) {
-    return hs_dispatch(p.hs.d, p.hs.qweight ? p.hs.group : 0, [&](auto lw, auto cpw, auto ragged, const HsShape &sh) {
-        return launch_hs<decltype(lw)::value, decltype(cpw)::value, decltype(ragged)::value, ARGMAX>(p, sh, wgs, s);
+    return hs_dispatch(p.hs.d, p.hs.V, p.hs.qweight ? p.hs.group : 0, [&](auto lw, auto cpw, auto ragged, auto nt, const HsShape &sh) {
+        return launch_hs<decltype(lw)::value, decltype(cpw)::value, decltype(ragged)::value, decltype(nt)::value, ARGMAX>(p, sh, wgs, s);
     });
 }
 

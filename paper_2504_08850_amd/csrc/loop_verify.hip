@@ -50,7 +50,7 @@ __device__ __forceinline__ const LoopParams &loop_args() {
     return ((const LoopVerifyParams *)at)->lp;
 }
 
-template <int LW, int CPW, bool RAGGED>
+template <int LW, int CPW, bool RAGGED, bool NT>
 __global__ __launch_bounds__(hs_max_waves(CPW) * kWave) void loop_verify_kernel(LoopVerifyParams p) {
     constexpr int kBlock = hs_block(CPW);
     extern __shared__ __attribute__((aligned(16))) unsigned char hs_smem[];
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(hs_max_waves(CPW) * kWave) void loop_verify_kernel(
             float bv[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
             int bi[4] = {0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff};
             for (int t = t_begin; t < t_end; t += kHsMaxTiles)
-                head_states_rows<LW, CPW, RAGGED>(
+                head_states_rows<LW, CPW, RAGGED, NT>(
                     p.hs, hs_smem, p.row_groups, t, min(t + kHsMaxTiles, t_end),
                     [&](int n) {
                         const int at = n < ns ? n : 0;
@@ -266,10 +266,10 @@ __global__ __launch_bounds__(hs_max_waves(CPW) * kWave) void loop_verify_kernel(
     }
 }
 
-template <int LW, int CPW, bool RAGGED>
+template <int LW, int CPW, bool RAGGED, bool NT>
 static hipError_t launch_lv(LoopVerifyParams &p, const HsShape &sh, int max_wgs, hipStream_t s) {
     p.hs.passes = sh.passes; p.hs.chunks = sh.chunks; p.hs.subs = sh.subs; p.hs.buffers = sh.buffers;
-    auto kern = loop_verify_kernel<LW, CPW, RAGGED>;
+    auto kern = loop_verify_kernel<LW, CPW, RAGGED, NT>;
     // per launch: the library keeps no state; a refusal shows as the launch error
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh.lds);
     // every workgroup must be resident while the grid meets: sized from what the runtime says fits on the device
@@ -299,8 +299,9 @@ hipError_t launch_loop_verify(const LoopParams &lp, int max_wgs, hipStream_t s) 
     p.lp = lp;
     p.hs.d = lp.d; p.hs.V = lp.V; p.hs.eps = lp.eps; p.hs.gamma = lp.gamma; p.hs.lm_head = lp.lm_head;
     p.hs.qweight = lp.qweight; p.hs.scales = lp.qscales; p.hs.zeros = lp.qzeros; p.hs.group = lp.group;
-    return hs_dispatch(lp.d, lp.qweight ? lp.group : 0, [&](auto lw, auto cpw, auto ragged, const HsShape &sh) {
-        return launch_lv<decltype(lw)::value, decltype(cpw)::value, decltype(ragged)::value>(p, sh, max_wgs, s);
+    return hs_dispatch(lp.d, lp.V, lp.qweight ? lp.group : 0, [&](auto lw, auto cpw, auto ragged, auto nt, const HsShape &sh) {
+        return launch_lv<decltype(lw)::value, decltype(cpw)::value, decltype(ragged)::value, decltype(nt)::value>(
+            p, sh, max_wgs, s);
     });
 }
 

@@ -265,3 +265,20 @@ def test_head_of_many_states_by_whole_lines(sp, d, V, N):
         assert torch.all((got[:, a:b].double() - part.double()).abs() <= bound)
     v = sp.verify(h, g, w, torch.zeros(N, 1, dtype=torch.int32, device="cuda"))
     assert torch.equal(v["token"].long(), got.argmax(dim=1)) and torch.equal(v["max_logit"], got.max(dim=1).values)
+
+
+@pytest.mark.parametrize("d,group", [(4096, 128), (4224, 128), (4608, 128), (4096, 64), (4160, 64), (4608, 64)])
+def test_q4_head_of_several_states_with_and_without_the_hint(sp, d, group):
+    """Codes above 72 MB are read with the non-temporal hint, the first and last rows of the same head without it."""
+    V, n = 2 ** 28 // d + 33, 12001
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    q = torch.randint(-2 ** 31, 2 ** 31 - 1, (V, d // 8), generator=gen, device="cuda", dtype=torch.int32)
+    s, z = (torch.rand(V, d // group, generator=gen, device="cuda").half() for _ in range(2))
+    h, g = torch.randn(2, d, generator=gen, device="cuda").half(), torch.ones(d, device="cuda").half()
+    assert V * d // 2 > 72 << 20 > n * d // 2
+    got = sp.lm_head_gemv_q4(h, g, q, s, 15 * z, group)
+    for a, b in ((0, n), (V - n, V)):
+        part = sp.lm_head_gemv_q4(h, g, q[a:b].contiguous(), s[a:b].contiguous(), 15 * z[a:b].contiguous(), group)
+        assert torch.equal(got[:, a:b], part)
+    v = sp.verify_q4(h, g, q, s, 15 * z, group, torch.zeros(2, 1, dtype=torch.int32, device="cuda"))
+    assert torch.equal(v["token"].long(), got.argmax(dim=1)) and torch.equal(v["max_logit"], got.max(dim=1).values)
