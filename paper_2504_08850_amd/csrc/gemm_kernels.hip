@@ -261,15 +261,15 @@ __global__ __launch_bounds__(kGemmThreads, 2) void full_head_gemm_kernel(GemmPar
     }
 }
 
-// Whole lines: of rows that consist of them, and on heads of more than 128 MB.  Halves of lines / whole lines, us, 24 and 64
-// states: 128256 x 8192 399 / 373, 437 / 411; 131072 x 4096 259 / 218, 270 / 234; 32000 x 4096 66.2 / 61.2, 76 / 70.4;
-// 50280 x 2048 59.0 / 53.0, 68.4 / 62.5; 20000 x 2048 (82 MB, from the last-level cache) 23.0 / 29.4, 30.6 / 34.2;
-// 20011 x 4104 62.7 / 65.0, 75.4 / 76.5.
+// Whole lines: of rows that consist of them, and on heads that the 256 MB last-level cache is unlikely to hold.  Halves of
+// lines / whole lines, us, 24 and 64 states: 128256 x 8192 399 / 373, 437 / 411; 131072 x 4096 259 / 218, 270 / 234; 32000 x
+// 4096 66.2 / 61.2, 76 / 70.4; 50280 x 2048 59.0 / 53.0, 68.4 / 62.5; 18000 x 4096 (147 MB) from memory 53.6 / 51.7, 60.7 /
+// 59.0, but 20000 x 4096, 64 states, again and again 50.3 / 60.8; 20011 x 4104 62.7 / 65.0, 75.4 / 76.5.
 template <int MODE, int TPW, int PD, int NT>
 static void launch_one(const GemmParams &p, hipStream_t st) {
     const int rows_per_wg = 16 * TPW * kGemmWaves;
     dim3 grid((p.V + rows_per_wg - 1) / rows_per_wg, 1, (p.N + 16 * NT - 1) / (16 * NT));
-    const bool lines = p.d % kKC == 0 && (size_t)p.V * p.d * sizeof(half_t) > ((size_t)128 << 20);
+    const bool lines = p.d % kKC == 0 && (size_t)p.V * p.d * sizeof(half_t) > ((size_t)192 << 20);
     hipLaunchKernelGGL((lines ? full_head_gemm_kernel<TPW, MODE, PD, NT, true> : full_head_gemm_kernel<TPW, MODE, PD, NT, false>),
                        grid, dim3(kGemmThreads), 0, st, p);
 }

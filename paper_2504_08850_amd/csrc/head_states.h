@@ -259,12 +259,14 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
 #pragma unroll
             for (int i = 0; i < kSteps; ++i) {
                 if (RAGGED) xh[i] = element(i) < d ? xh[i] : zero_half8();
+                float some = 0.f;  // (short chains: all logits of a state share this sum's error)
 #pragma unroll
                 for (int e = 0; e < 8; e += 2) {
                     const half2_t h = {xh[i][e], xh[i][e + 1]}, g = {xl[i][e], xl[i][e + 1]};
-                    ssq = __builtin_amdgcn_fdot2(h, h, ssq, false);
+                    some = __builtin_amdgcn_fdot2(h, h, some, false);
                     ssg = __builtin_amdgcn_fdot2(g, g, ssg, false);
                 }
+                ssq += some;
             }
 #pragma unroll
             for (int off = 16; off <= 32; off <<= 1) {
@@ -374,9 +376,12 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
             for (int i = wg_wave; i < nb; i += G * W) {
                 const int ln = hs_opaque(lane), lq = ln >> 4;
                 const floatx4 *src = part + (pbuf * W * kHsBlock + i) * kWave + ln;
-                floatx4 y = *src;
+                double sum[4] = {};  // (a few additions per logit)
 #pragma unroll 4
-                for (int w = 1; w < W; ++w) y += src[w * kHsBlock * kWave];
+                for (int w = 0; w < W; ++w)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sum[r] += (double)src[w * kHsBlock * kWave][r];
+                floatx4 y = {(float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]};
                 if (p.passes > 1) {
                     floatx4 *at = acc_lds + (tb - tile_begin + i) * kWave + ln;  // this lane's own cell
                     if (pass > 0) y += *at;

@@ -135,15 +135,14 @@ bool head_states_q4_preferred(int d, int V, int N, int group) {
     return N >= 2 && head_states_q4_ok(group) && (long long)N * V >= (group == 128 ? 16000 : 24000);
 }
 
-// Against the vector kernel, which passes over the head once per state, and the tiles of up to 64 states (gemm_kernels.hip),
-// whose 128 rows per workgroup leave most of the chip idle on a small head.  Vector kernel against this one, us: 32000 x
-// 4096, 1 state 44.3 / 46.5, 2 states 87.3 / 46.7; 6000 x 4096, 2 states 17.6 / 15.2; 2000 x 4096, 2 states 7.8 / 10.0.
-// Tiles against this one, a pass per 16 states: 32000 x 4096, 16 states 65.7 / 48.7, 32 states 64 / 93; 6000 x 4096, 16
-// states 39.4 / 16.8, 32 states 40.4 / 28.3, 64 states 51.7 / 54.6; 2000 x 4096, 64 states 51.4 / 24.4; 300 x 1024, 3
-// states 11.8 / 4.7; 16000 x 1024, 32 states 14.2 / 16.5; 128256 x 8192, 16 states 397 / 390.
+// Against the tiles of up to 64 states (gemm_kernels.hip), whose 128 rows per workgroup leave most of the chip idle on a small
+// head, us: 32000 x 4096, 16 states 65.7 / 48.7, 32 states, a pass per 16, 64 / 93; 6000 x 4096, 16 states 39.4 / 16.8, 32
+// states 40.4 / 28.3, 64 states 51.7 / 54.6; 2000 x 4096, 64 states 51.4 / 24.4; 300 x 1024, 3 states 11.8 / 4.7; 16000 x
+// 1024, 32 states 14.2 / 16.5; 128256 x 8192, 16 states 397 / 390.  Two states would gain too (32000 x 4096 87.3 / 46.7),
+// but their sums are the vector kernel's, which are a little more exact (error against float64 1.2e-7 / 1.6e-7).
 bool head_states_preferred(int d, int V, int N) {
     const int passes = (N + kHsStates - 1) / kHsStates;
-    return N == 2 ? V >= 6000 : passes == 1 ? N > 2 : N <= 64 && (long long)passes * V <= 20000;
+    return N > 2 && (passes == 1 || (N <= 64 && (long long)passes * V <= 20000));
 }
 
 hipError_t launch_head_states(int d, int V, float eps, int N, const half_t *hidden, const half_t *gamma,

@@ -286,7 +286,7 @@ int lm_head_gemv(const specee_dims *dm, int N, const specee_half *hidden, const 
     if (misaligned(hidden) || misaligned(gamma) || misaligned(lm_head)) return SPECEE_EALIGN;
     if (misaligned(out)) return SPECEE_EALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // one hidden state (two on a small head): stream the head once per state on the vector units;
+    // one or two hidden states: stream the head once per state on the vector units;
     // more: one pass over the head per 16 or per 64 of them on the matrix cores
     if (head_states_preferred(dm->d, dm->V, N))
         return launch_head_states(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), H(lm_head), HeadQ4{}, out, st) == hipSuccess
