@@ -18,9 +18,11 @@
 // the passes wait in LDS.
 //
 // Matrix operands of v_mfma_f32_16x16x32_f16 (lane = 16 * q + c):
-//   A = x of state c, cut exactly into two halves, hi = round(h * gamma) and lo = fma(h, gamma, -hi), after the
-//       wavefront's h and gamma have been scaled by powers of two, by their norms, so that no product reaches 2^15.
-//       What the cut can lose lies 2^-25 below 1, 2^-30 or so below the largest of the wavefront's products;
+//   A = x of state c, cut into two halves, hi = round(h * gamma) and lo = fma(h, gamma, -hi).  First gamma, as far as it
+//       stays below 2^15, and then h are scaled up by powers of two (exactly) so that the norm of the wavefront's x comes
+//       to between 2^13 and 2^15: the cut loses what lies below 2^-25, 2^-35 of it.  (Each scaled by its own norm, before
+//       the product, lost 1e-5 of the logits where large hidden elements meet weights near zero: |h| 3e4 and 0.1, gamma
+//       1e-6 and 1; products in 32 bits cost twice the instructions, on codes 1.6 us.);
 //   B = 8 elements of row c of the tile.  fp16 head: as loaded.  Quantised head: a byte that holds a code is the fp8
 //       (E4M3) number code * 2^-9, so one conversion with scale 2^9 makes two exact halves of two codes: seven
 //       instructions per word of eight, in the order 0,2,4,6,1,3,5,7, in which x is built too.  (Codes as subnormal
@@ -244,6 +246,7 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
         };
         // the hidden states and the weight are asked for before the rows: loads come back in order, and the operands are made
         // of them while the first rows are on their way
+        const half8 gamma8 = load_half8(p.gamma + min(e0 + (lane * 8) % (CPW * kHsChunk), d - 8));  // the share's, once
         load_x();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -255,26 +258,46 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
         }
         __builtin_amdgcn_sched_barrier(0);
         {
-            float ssq = 0.f, ssg = 0.f;
+            float ssq = 0.f, ssx = 0.f, ssg = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) {
+                const half2_t g = {gamma8[e], gamma8[e + 1]};
+                ssg = __builtin_amdgcn_fdot2(g, g, ssg, false);
+            }
 #pragma unroll
             for (int i = 0; i < kSteps; ++i) {
                 if (RAGGED) xh[i] = element(i) < d ? xh[i] : zero_half8();
                 float some = 0.f;  // (short chains: all logits of a state share this sum's error)
 #pragma unroll
                 for (int e = 0; e < 8; e += 2) {
-                    const half2_t h = {xh[i][e], xh[i][e + 1]}, g = {xl[i][e], xl[i][e + 1]};
+                    const half2_t h = {xh[i][e], xh[i][e + 1]}, x = h * half2_t{xl[i][e], xl[i][e + 1]};
                     some = __builtin_amdgcn_fdot2(h, h, some, false);
-                    ssg = __builtin_amdgcn_fdot2(g, g, ssg, false);
+                    ssx = __builtin_amdgcn_fdot2(x, x, ssx, false);
                 }
                 ssq += some;
             }
+            auto over_q = [](float v) {
+                v += __shfl_xor(v, 16, kWave);
+                return v + __shfl_xor(v, 32, kWave);
+            };
+            ssq = over_q(ssq);
+            ssx = over_q(ssx);
+            if (__any(!(ssx < INFINITY))) {  // a product that is no half
+                ssx = 0.f;
 #pragma unroll
-            for (int off = 16; off <= 32; off <<= 1) {
-                ssq += __shfl_xor(ssq, off, kWave);
-                ssg += __shfl_xor(ssg, off, kWave);
+                for (int i = 0; i < kSteps; ++i)
+#pragma unroll
+                    for (int e = 0; e < 8; e += 2) {
+                        constexpr half2_t down = {0x1p-9, 0x1p-9};
+                        const half2_t x = half2_t{xh[i][e], xh[i][e + 1]} * down * (half2_t{xl[i][e], xl[i][e + 1]} * down);
+                        ssx = __builtin_amdgcn_fdot2(x, x, ssx, false);
+                    }
+                ssx = 0x1p36f * over_q(ssx);
             }
-            // |h * 2^uh| < 2^7 and |gamma * 2^ug| < 2^8, by the norms: no product reaches 2^15
-            const int uh = max(-14, min(15, 7 - hs_bound(ssq))), ug = max(-14, min(15, 8 - hs_bound(ssg)));
+            ssg = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wave_sum_to_last_row(ssg)), kWave - 1));
+            // |x * 2^u| < 2^15 by the norm; of it as much through gamma as leaves that below 2^15 too, the rest through h
+            const int u = max(-18, 15 - hs_bound(ssx));
+            const int ug = max(0, min(min(u, 15), 15 - hs_bound(ssg))), uh = min(u - ug, max(0, min(15, 15 - hs_bound(ssq))));
             if (q == 0) {
                 ssq_lds[wave * kHsStates + c] = ssq;
                 unscale_lds[wave * kHsStates + c] = __builtin_bit_cast(float, (uint32_t)(127 - uh - ug) << 23);

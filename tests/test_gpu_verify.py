@@ -210,8 +210,8 @@ def head_rows(rng, V, d, group):
 def test_head_of_several_states_by_shares_of_the_row(sp, d, V, N, group, hscale):
     """fp32 sums of exact products: a term passes at most 512 additions in a wavefront's share of the row (32 per matrix
     instruction, 16 of them), 16 shares, four passes and a handful of folds and factors, each off by 2^-24 of what it has
-    summed.  h and gamma are scaled by their shares' norms to between 2^5 and 2^8 before x is cut, so that what lies below
-    the normal halves is off by 2^-25 of that, at most 2^-28 of the product of the norms."""
+    summed.  x is scaled by its share's largest element to between 2^14 and 2^15 before it is cut into two halves, so that
+    what lies below the normal halves is off by 2^-25 of that, at most 2^-39 of the largest."""
     rng = np.random.default_rng(d + V + N)
     h = (rng.standard_normal((N, d)).clip(-4, 4) * hscale).astype(np.float16)
     g = (1 + 0.05 * rng.standard_normal(d)).astype(np.float16)
@@ -220,8 +220,8 @@ def test_head_of_several_states_by_shares_of_the_row(sp, d, V, N, group, hscale)
     h64, g64 = h.astype(np.float64), g.astype(np.float64)
     r = 1.0 / np.sqrt((h64 ** 2).mean(axis=1, keepdims=True) + 1e-5)
     ref = r * ((h64 * g64) @ w.T)
-    norms = np.sqrt((h64 ** 2).sum(axis=1, keepdims=True) * (g64 ** 2).sum())
-    bound = r * ((512 + 16 + 4 + 16) * 2.0 ** -24 * (np.abs(h64 * g64) @ absw.T) + 2.0 ** -28 * norms * absw.sum(axis=1))
+    x = np.abs(h64 * g64)
+    bound = r * ((512 + 16 + 4 + 16) * 2.0 ** -24 * (x @ absw.T) + 2.0 ** -39 * x.max(axis=1, keepdims=True) * absw.sum(axis=1))
     got = host(logits(dev(h), dev(g), *head, out=torch.full((N, V), float("nan"), device="cuda")))
     assert np.all(np.abs(got - ref) <= bound)
     ids = np.stack([rng.choice(V, min(V, 3), replace=False) for _ in range(N)]).astype(np.int32)
@@ -233,6 +233,29 @@ def test_head_of_several_states_by_shares_of_the_row(sp, d, V, N, group, hscale)
     b = host(logits(dev(bad), dev(g), *head))
     rest = np.setdiff1d(np.arange(N), [0, N // 2])
     assert np.isnan(b[[0, N // 2]]).all() and np.array_equal(b[rest], got[rest])
+
+
+@pytest.mark.parametrize("d,V,N,group", [(72, 4000, 5, 0), (1024, 4001, 8, 0), (4096, 4111, 16, 0), (4104, 2003, 16, 0),
+                                         (192, 4001, 16, 64), (2048, 1603, 16, 128), (3072, 1009, 16, 128),
+                                         (4096, 1103, 16, 64), (4608, 1601, 16, 64), (8192, 1503, 16, 128)])
+@pytest.mark.parametrize("large,gamma", [(30000.0, 2.0 ** -20), (1500.0, 2.0 ** -14), (30000.0, 0.0), (30000.0, 8.0),
+                                         (2.0 ** -18, 1.0)])
+def test_head_keeps_the_small_elements_beside_a_large_one(sp, d, V, N, group, large, gamma):
+    """Hidden elements of very different size, the large ones where the RMSNorm weight is near zero: the small ones make the
+    logits and must keep their 22 bits.  Also products that no half holds, and hidden states of subnormal halves.  548 additions, each off by at most 2^-24 of what it has
+    summed and independent of the others, are off by sqrt(548 / 3) * 2^-24 = 8.1e-7 together; on codes scale * (sum of
+    codes - zero * sum), whose parts have 2.5 times the root mean square of the difference."""
+    rng = np.random.default_rng(d + V + N)
+    h = rng.standard_normal((N, d)) * min(0.1, large)
+    g = 1 + 0.05 * rng.standard_normal(d)
+    if large > 1:
+        h[:, [d // 7, d // 3]], g[[d // 7, d // 3]] = large, gamma
+    h, g = h.astype(np.float16), g.astype(np.float16)
+    head, w, _ = head_rows(rng, V, d, group)
+    got = host((sp.lm_head_gemv_q4 if group else sp.lm_head_gemv)(dev(h), dev(g), *head, eps=0.0))
+    h64 = h.astype(np.float64)
+    ref = ((h64 * g.astype(np.float64)) @ w.T) / np.sqrt((h64 ** 2).mean(axis=1, keepdims=True))
+    assert np.linalg.norm(got - ref) <= 8.1e-7 * (2.5 if group else 1.0) * np.linalg.norm(ref)
 
 
 def test_head_of_several_states_more_tiles_than_sums_wait_in_lds(sp):
