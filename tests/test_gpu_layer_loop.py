@@ -392,3 +392,17 @@ def test_layer_loop_verifies_what_fired_sixteen_at_a_time(sp, d, V, L, B, group,
         assert np.array_equal(np.flatnonzero(out["exit"][:, b]), seen)
         off = np.setdiff1d(np.arange(L), seen)
         assert (out["scores"][seen, b] > 0).all() and not out["scores"][off, b].any() and not out["probs"][off, b].any()
+
+
+def test_layer_loop_finds_a_row_with_an_infinite_logit(sp):
+    """An infinite weight makes its row the winner of a verification, as in specee_verify."""
+    rng = np.random.default_rng(6)
+    L, B, d, V, K, H = 2, 1, 512, 200, 2, 16
+    h = (1 + rng.random((L, B, d))).astype(np.float16)
+    w = (0.05 * rng.standard_normal((V, d))).astype(np.float16)
+    w[123, 7] = np.inf
+    g, ids = np.ones(d, np.float16), np.array([[5, 122]], np.int32)
+    W1, w2 = (dev((0.1 * rng.standard_normal(s)).astype(np.float16)) for s in ((L, H, 3 * K), (L, H)))
+    assert int(sp.verify(dev(h[0]), dev(g), dev(w), dev(ids))["token"][0]) == 123
+    out = sp.layer_loop(dev(h), dev(g), dev(w), dev(ids), W1, w2, threshold=-1.0)
+    assert (host(out["ver_token"]) == 123).all() and int(out["exit_layer"][0]) == -1 and int(out["status"][0]) == 0

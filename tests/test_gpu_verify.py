@@ -258,6 +258,40 @@ def test_head_keeps_the_small_elements_beside_a_large_one(sp, d, V, N, group, la
     assert np.linalg.norm(got - ref) <= 8.1e-7 * (2.5 if group else 1.0) * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("d,large", [(2048, 0), (3072, 0), (4096, 0), (4608, 0), (5120, 0), (4096, 1500.0), (5120, 900.0)])
+def test_fp16_head_of_several_states_sums_as_exactly_as_of_one(sp, d, large):
+    """Both sum in 32 bits.  Of one state a lane adds d / 64 products in a row; of several, a chain of four matrix
+    instructions makes 16 such additions at most, then four chains and the shares meet.  Errors against float64 as norms
+    over 32000 logits each, a random quantity: a fifth more is allowed."""
+    rng = np.random.default_rng(d)
+    h, g = 0.3 * rng.standard_normal((4, d)) if large else rng.standard_normal((4, d)), 1 + 0.05 * rng.standard_normal(d)
+    if large:
+        h[:, [d // 7, d // 3]], g[[d // 7, d // 3]] = large, 0.02
+    h, g = h.astype(np.float16), g.astype(np.float16)
+    (w_d,), w, _ = head_rows(rng, 8000, d, 0)
+    h64 = h.astype(np.float64)
+    ref = ((h64 * g.astype(np.float64)) @ w.T) / np.sqrt((h64 ** 2).mean(axis=1, keepdims=True) + 1e-5)
+    one = np.concatenate([host(sp.lm_head_gemv(dev(s[None]), dev(g), w_d)) for s in h])
+    four = host(sp.lm_head_gemv(dev(h), dev(g), w_d))
+    assert np.linalg.norm(four - ref) <= 1.2 * np.linalg.norm(one - ref)
+
+
+def test_fp16_head_of_several_states_keeps_infinite_logits(sp):
+    """A row with an infinite weight has an infinite logit, as in the sums for one state; both signs in it: NaN."""
+    rng = np.random.default_rng(5)
+    d, V = 1032, 300
+    h = (1 + rng.random((4, d))).astype(np.float16)   # (x > 0 everywhere: the weight's sign is the logit's)
+    w = (0.05 * rng.standard_normal((V, d))).astype(np.float16)
+    w[17, 3], w[40, 1031], w[41, 600], w[41, 8] = np.inf, -np.inf, np.inf, -np.inf
+    g = np.ones(d, np.float16)
+    one = np.concatenate([host(sp.lm_head_gemv(dev(s[None]), dev(g), dev(w))) for s in h])
+    four = host(sp.lm_head_gemv(dev(h), dev(g), dev(w)))
+    for y in (one, four):
+        assert (y[:, 17] == np.inf).all() and (y[:, 40] == -np.inf).all() and np.isnan(y[:, 41]).all()
+        assert np.isfinite(np.delete(y, [17, 40, 41], axis=1)).all()
+    assert (host(sp.verify(dev(h), dev(g), dev(w), dev(np.zeros((4, 1), np.int32)))["token"]) == 17).all()
+
+
 def test_head_of_several_states_more_tiles_than_sums_wait_in_lds(sp):
     """Two passes over the rows and 33 tiles for the first workgroups: the sums of a row do not depend on the split."""
     d, V, N = 4104, 131100, 3
