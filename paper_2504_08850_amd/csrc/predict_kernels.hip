@@ -520,13 +520,25 @@ __global__ __launch_bounds__(T) void predict_q4_kernel(PredictParams p) {
 #pragma unroll
         for (int k = 0; k < KC; ++k) {
             const uint32_t even = w[k] & 0x0f0f0f0fu, odd = (w[k] >> 4) & 0x0f0f0f0fu;  // elements 0,2,4,6 / 1,3,5,7
-            float pd = 0.f;
+            if constexpr (SWEEP) {
+                // weight by weight, as in the layer loop's other kernel: the difference of two sums below is off by half
+                // as much again (error of the loop's logits against float64 1.6e-7 / 1.1e-7), and few workgroups wait for
+                // memory here, not for arithmetic
+                const float s = (float)sc[k], z = (float)zp[k];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                pd += x[2 * j] * (float)((even >> (8 * j)) & 0xffu);
-                pd += x[2 * j + 1] * (float)((odd >> (8 * j)) & 0xffu);
+                for (int j = 0; j < 4; ++j) {
+                    acc[k] += x[2 * j] * (s * ((float)((even >> (8 * j)) & 0xffu) - z));
+                    acc[k] += x[2 * j + 1] * (s * ((float)((odd >> (8 * j)) & 0xffu) - z));
+                }
+            } else {
+                float pd = 0.f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    pd += x[2 * j] * (float)((even >> (8 * j)) & 0xffu);
+                    pd += x[2 * j + 1] * (float)((odd >> (8 * j)) & 0xffu);
+                }
+                acc[k] += (float)sc[k] * (pd - (float)zp[k] * xs);
             }
-            acc[k] += (float)sc[k] * (pd - (float)zp[k] * xs);
         }
     };
 #pragma unroll

@@ -186,3 +186,30 @@ def test_layer_loop_q4_other_widths(sp, oracle, seed, K, d, group):
     oracle.set_threads(8)
     check_loop(oracle, sp, t, 0.45, what=f"q4 loop K={K} d={d}")
     oracle.set_threads(1)
+
+
+@pytest.mark.parametrize("d,group", [(2048, 128), (4096, 64), (4096, 128), (8192, 128)])
+def test_layer_loop_q4_predictors_are_as_exact_in_every_group(sp, d, group):
+    """The same weights in groups of `group` and, scales and zero-points repeated, of 32, which the loop walks layer by
+    layer: both add x * (scale * (code - zero)) weight by weight, so their logits are off by as much (norms over 2048
+    logits; half as much again where sums of codes are scaled and the zero-point's share taken off)."""
+    rng = np.random.default_rng(d + group)
+    V, L, B, K, H = 3000, 32, 16, 4, 16
+    codes = rng.integers(0, 16, (V, d), dtype=np.uint32)
+    q = dev((codes.reshape(V, d // 8, 8) << (4 * np.arange(8, dtype=np.uint32))).sum(axis=2, dtype=np.uint32).view(np.int32))
+    s = rng.uniform(0.004, 0.02, (V, d // group)).astype(np.float16)
+    z = rng.uniform(5, 10, (V, d // group)).astype(np.float16)
+    h = rng.standard_normal((L, B, d)).astype(np.float16)
+    g = (1 + 0.05 * rng.standard_normal(d)).astype(np.float16)
+    ids = np.stack([rng.choice(V, K, replace=False) for _ in range(B)]).astype(np.int32)
+    W1, w2 = (dev((0.1 * rng.standard_normal(x)).astype(np.float16)) for x in ((L, H, 3 * K), (L, H)))
+    s64, z64 = (np.repeat(a.astype(np.float64), group, axis=1) for a in (s, z))
+    w = (s64 * (codes - z64))[ids] * g.astype(np.float64)
+    h64 = h.astype(np.float64)
+    ref = np.einsum("lbd,bkd->lbk", h64, w) / np.sqrt((h64 ** 2).mean(axis=2) + 1e-5)[:, :, None]
+
+    def error(grp):
+        a, b = (dev(np.repeat(x, group // grp, axis=1)) for x in (s, z))
+        out = sp.layer_loop_q4(dev(h), dev(g), q, a, b, grp, dev(ids), W1, w2, threshold=2.0)
+        return np.linalg.norm(host(out["logits"]) - ref)
+    assert error(group) <= 1.15 * error(32)
