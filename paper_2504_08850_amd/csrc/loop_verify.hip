@@ -107,9 +107,11 @@ __global__ __launch_bounds__(hs_max_waves(CPW) * kWave) void loop_verify_kernel(
             // ---- one pass over this workgroup's rows
             float bv[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
             int bi[4] = {0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff};
-            for (int t = t_begin; t < t_end; t += kHsMaxTiles)
+            // (several passes over the rows: the sums of as many tiles wait in LDS as there is room for)
+            const int most = p.hs.passes > 1 ? kHsMaxTiles : t_end - t_begin;
+            for (int t = t_begin; t < t_end; t += most)
                 head_states_rows<LW, CPW, RAGGED, NT>(
-                    p.hs, hs_smem, p.row_groups, t, min(t + kHsMaxTiles, t_end),
+                    p.hs, hs_smem, p.row_groups, t, min(t + most, t_end),
                     [&](int n) {
                         const int at = n < ns ? n : 0;
                         return p.lp.hidden + ((size_t)sel_l[at] * B + sel_b[at]) * p.hs.d;

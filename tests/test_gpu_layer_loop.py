@@ -354,6 +354,8 @@ def test_layer_loop_other_widths(sp, oracle, seed, K, d, H):
     (4608, 16, 3, 1, 0, [None]), (8192, 1, 2, 1, 0, [0]),                      # two passes over the rows, one tile
     (192, 9000, 3, 9, 64, [2] * 9), (4096, 1601, 17, 2, 64, [16, 3]),
     (512, 20011, 4, 1, 128, [2]), (3072, 1500, 6, 4, 128, [5, 0, None, 5]), (8192, 1203, 2, 9, 128, [1] * 9),
+    (128, 131200, 3, 2, 0, [None, 2]), (4104, 131100, 2, 1, 0, [1]),           # 33 tiles of rows, in one pass and in two
+    (256, 140000, 2, 2, 64, [1, None]),
 ])
 def test_layer_loop_verifies_what_fired_sixteen_at_a_time(sp, d, V, L, B, group, plant):
     """Every active layer fires.  A verification's sums do not depend on which others share the pass, so tokens, hits and
