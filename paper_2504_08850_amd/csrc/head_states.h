@@ -197,12 +197,11 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
             for (int u = 0; u < 2; ++u) {
                 const uint32_t row = (uint32_t)min((ln & 7) + 8 * u, last) * row_bytes;
                 const char *at = RAGGED ? base + (row + min(piece + 128 * i, limit)) : base + (row + piece) + 128 * i;
-                if constexpr (Q4 && !NT)
-                    a[slot][2 * i + u] = *reinterpret_cast<const uintx4_a4 *>(at);
-                else if constexpr (Q4)
-                    a[slot][2 * i + u] = __builtin_nontemporal_load(reinterpret_cast<const uintx4_a4 *>(at));
+                typedef std::conditional_t<Q4, uintx4_a4, uintx4> piece_t;
+                if constexpr (NT)
+                    a[slot][2 * i + u] = __builtin_nontemporal_load(reinterpret_cast<const piece_t *>(at));
                 else
-                    a[slot][2 * i + u] = __builtin_nontemporal_load(reinterpret_cast<const uintx4 *>(at));
+                    a[slot][2 * i + u] = *reinterpret_cast<const piece_t *>(at);
             }
         };
         // scales and zero-points of this wavefront's groups of row c of a tile: side by side in memory, one load each (of any
@@ -452,14 +451,18 @@ inline int hs_chunks_per_wave(int d, int lw) {
     return sh.waves % 4 == 0 && d == sh.passes * sh.chunks * kHsChunk ? 4 : 2;
 }
 
-// The hint (us, 16 states, without / with it): the fp16 head gains wherever it comes from memory and loses little where not
-// (50280 x 2048 46.9 / 42.0; 16000 x 2048, one head after the other 20.2 / 18.4, few heads that stay in the last-level cache
-// 17.2 / 18.0).  Codes: one layer's weights or so pass through that cache between two verifications, and a small head
-// stays there: groups of 128, from the cache and from memory, 32000 x 4096 22.8 / 25.5 and 25.5 / 24.7, 24001 x 4608 25.6 /
-// 28.0 and 28.6 / 28.2; from 82 MB on it does not pay: 32000 x 5120, groups of 64, 39.6 / 39.1 and 40.8 / 39.0, 32000 x 8192
-// 49.6 / 47.3 and 50 / 47.
+// The hint (us, without / with it).  Only rows of whole 128-byte lines: where a line holds the end of one row and the start
+// of the next, the second load that needs it asks memory for it again (fp16, 20011 x 4104, verification of 16 states 62.1
+// / 70.3 from memory, 51.0 / 66.6 from the cache, layer loop of one token 56.1 / 61.1, 32001 x 3080 54.3 / 65.0; codes,
+// 40000 x 4160, groups of 64, 50.6 / 51.9 and 46.0 / 51.2, 40000 x 4224, groups of 128, 43.7 / 45.2 and 37.8 / 42.0).
+// fp16 heads gain wherever they come from memory and lose little where not (16 states, 50280 x 2048 46.9 / 42.0; 16000 x
+// 2048, one head after the other 20.2 / 18.4, few heads that stay in the last-level cache 17.2 / 18.0).  Codes: a head is a
+// quarter of that, and how much of it that cache still holds at the next verification depends on what the program does in
+// between.  The line is where neither side loses much: groups of 128, from the cache and from memory, 32000 x 4096 22.8 /
+// 25.5 and 25.5 / 24.7, 24001 x 4608 25.6 / 28.0 and 28.6 / 28.2, 40000 x 4096 24.2 / 27.1 and 29.4 / 28.4, 32000 x 8192
+// 49.6 / 47.3 and 50 / 47; groups of 64, 32000 x 5120 39.6 / 39.1 and 40.8 / 39.0.
 inline bool hs_hint(int d, int V, int lw) {
-    return lw == 0 || (size_t)V * d / 2 > ((size_t)72 << 20);
+    return lw == 0 ? d % 64 == 0 : d % 256 == 0 && (size_t)V * d / 2 > ((size_t)72 << 20);
 }
 
 // f(LW, CPW, RAGGED, NT as integral constants, shape) for a head (group 0: fp16)
@@ -475,11 +478,11 @@ hipError_t hs_dispatch(int d, int V, int group, F f) {
     std::integral_constant<int, 4> four;
     std::false_type no;
     std::true_type yes;
-    if (lw == 0) return ragged ? f(w0, four, yes, yes, sh) : f(w0, four, no, yes, sh);
+    const bool hint = hs_hint(d, V, lw);
+    if (lw == 0) return !ragged ? f(w0, four, no, yes, sh) : hint ? f(w0, four, yes, yes, sh) : f(w0, four, yes, no, sh);
     auto codes = [&](auto w, auto nt) {
         return cpw == 4 ? f(w, four, no, nt, sh) : ragged ? f(w, two, yes, nt, sh) : f(w, two, no, nt, sh);
     };
-    const bool hint = hs_hint(d, V, lw);
     return lw == 4 ? (hint ? codes(four, yes) : codes(four, no)) : hint ? codes(two, yes) : codes(two, no);
 }
 

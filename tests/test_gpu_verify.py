@@ -198,6 +198,7 @@ def head_rows(rng, V, d, group):
 
 @pytest.mark.parametrize("d,V,N,group,hscale", [
     (8, 1, 3, 0, 1.0), (72, 17, 16, 0, 1.0), (512, 16, 15, 0, 1.0), (520, 33, 17, 0, 1.0),  # rows end in a wavefront
+    (576, 33, 17, 0, 1.0), (4608, 515, 16, 0, 1.0),                                         # the same, rows of whole lines
     (1032, 6007, 2, 0, 1.0), (2048, 4099, 64, 0, 1.0), (4096, 4111, 16, 0, 1.0),            # several tiles, passes of states
     (4104, 47, 15, 0, 1.0), (8192, 515, 16, 0, 1.0), (16384, 40, 3, 0, 1.0),                # two, two and four passes over rows
     (1024, 129, 8, 0, 2.0 ** -13), (1024, 129, 8, 0, 16000.0),
