@@ -83,12 +83,17 @@ __global__ __launch_bounds__(hs_max_waves(CPW) * kWave) void head_states_kernel(
     }
 }
 
-// Workgroups of a pass: one per CU (two where both fit), each with its share of the tiles; never more than `limit` (the
-// arg-max candidates that the caller's workspace holds).
+// Workgroups of a pass, each with its share of the tiles; never more than `limit` (the arg-max candidates that the caller's
+// workspace holds).  One per CU; where two fit, two of them if the tiles go round: with one or two each, the second one's
+// operands cost more than it brings (16 states, 512 / 256 workgroups, us, 2048 columns: fp16 8000 rows 13.0 / 10.1, 20011 20.0
+// / 18.3, 32000 27.4 / 26.2, 50280 39.5 / 39.1; codes in groups of 128 11.0 / 8.6, 13.3 / 11.7, 15.8 / 15.0, 19.4 / 20.6;
+// 1024 columns, codes, 24000 rows 8.9 / 8.6, 32000 9.7 / 10.6), but not fp16 rows of a single wavefront (512 columns,
+// 8000 rows 5.7 / 6.2, 32000 9.9 / 13.2).
 int head_states_workgroups(int d, int V, int group, int limit) {
     const int tiles = (V + kHsTile - 1) / kHsTile, lw = hs_words(group);
     const HsShape sh = hs_shape(d, lw, hs_chunks_per_wave(d, lw));
-    return std::min({2 * sh.waves <= hs_max_waves(sh.cpw) ? 512 : 256, tiles, limit});
+    const bool two = 2 * sh.waves <= hs_max_waves(sh.cpw) && (tiles >= 1800 || (lw == 0 && sh.waves == 1));
+    return std::min({two ? 512 : 256, tiles, limit});
 }
 
 template <int LW, int CPW, bool RAGGED, bool NT, bool ARGMAX>
@@ -136,10 +141,14 @@ bool head_states_q4_preferred(int d, int V, int N, int group) {
 }
 
 // Against the tiles of up to 64 states (gemm_kernels.hip), whose 128 rows per workgroup leave most of the chip idle on a small
-// head, us: 32000 x 4096, 16 states 65.7 / 48.7, 32 states, a pass per 16, 64 / 93; 6000 x 4096, 16 states 39.4 / 16.8, 32
-// states 40.4 / 28.3, 64 states 51.7 / 54.6; 2000 x 4096, 64 states 51.4 / 24.4; 300 x 1024, 3 states 11.8 / 4.7; 16000 x
-// 1024, 32 states 14.2 / 16.5; 128256 x 8192, 16 states 397 / 390.  Two states would gain too (32000 x 4096 87.3 / 46.7),
-// but their sums are the vector kernel's, which are a little more exact (error against float64 1.2e-7 / 1.6e-7).
+// head, us: 32000 x 4096, 16 states 65.7 / 49.0, 32 states, a pass per 16, 64 / 93; 6000 x 4096, 16 states 39.4 / 16.8, 32
+// states 38.5 / 27.7, 64 states, 4000 rows 49.0 / 48.2; 2000 x 4096, 64 states 48.6 / 24.6; 300 x 1024, 3 states 11.8 / 4.7;
+// 16000 x 1024, 32 states 14.2 / 16.5; 128256 x 8192, 16 states 397 / 390; verification of 16 states, 8000 x 4096 41.9 /
+// 22.6, 20011 x 4104 42.6 / 43.8 (from memory 72 / 62).
+// Rows that leave wavefronts idle are not faster everywhere (16 states, 32000 x 256 6.5 / 11.8, 32000 x 768 12.1 / 16.5, from
+// memory 15.7 / 18.4; 32 states, 10000 x 768 10.3 / 15.7; 64 states, 4000 x 4104 54.5 / 71.8); they are here for the sums,
+// 1.0e-7 to 1.35e-7 off float64 instead of 4e-7 to 9e-7.  Two states would gain too (32000 x 4096 87.3 / 47), but have those
+// of the vector kernel, which are as exact.
 bool head_states_preferred(int d, int V, int N) {
     const int passes = (N + kHsStates - 1) / kHsStates;
     return N > 2 && (passes == 1 || (N <= 64 && (long long)passes * V <= 20000));

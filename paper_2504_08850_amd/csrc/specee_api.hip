@@ -2,6 +2,8 @@
 // kernel launches.  See include/specee.h for the contract of every entry point.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <climits>
 #include <mutex>
 
 #include "../../include/specee.h"
@@ -80,6 +82,19 @@ TreeLayout tree_layout(int S, int n_total, int Mcap) {
     L.ssq_off = align256((size_t)S * n_total * L.Mpad * sizeof(float));
     L.total = L.ssq_off + align256((size_t)S * n_total * sizeof(float));
     return L;
+}
+
+// Workspace of a verification: the arg-max candidates of N states, P each, values and then rows.  A caller needs room for as
+// many as the kernels of the first kind leave (verify_workgroups, lm_head_q4_workgroups); the kernels for several states
+// can use more workgroups on a small head, as many as the room that there is allows.
+size_t verify_bytes(int N, int P) {
+    return 2 * align256((size_t)N * P * sizeof(float));
+}
+int verify_workgroups(int V, int N) {
+    return N <= 2 ? lm_head_gemv_workgroups(V) : lm_head_gemm_workgroups(V);
+}
+int verify_fits(int N, size_t bytes) {
+    return (int)std::min<size_t>(INT_MAX, (bytes / 2 & ~(size_t)255) / ((size_t)N * sizeof(float)));
 }
 
 // Workspace of the layer loop: arrival counters [B] and the abort flag (cleared at every call), then the arg-max slots and
@@ -170,14 +185,19 @@ size_t specee_workspace_bytes(int op, const specee_dims *dm, int n, int Mcap) {
             return check_dims(dm, false) ? (size_t)-1 : 0;
         case SPECEE_OP_VERIFY: {
             if (check_dims(dm, false)) return (size_t)-1;
-            int P = n <= 2 ? lm_head_gemv_workgroups(dm->V) : lm_head_gemm_workgroups(dm->V);
-            return 2 * align256((size_t)n * P * sizeof(float));
+            return verify_bytes(n, std::max(verify_workgroups(dm->V, n), head_states_preferred(dm->d, dm->V, n)
+                                                                             ? head_states_workgroups(dm->d, dm->V, 0, INT_MAX)
+                                                                             : 0));
         }
         case SPECEE_OP_PREDICT_TREE_Q4:
             return check_dims(dm, true) ? (size_t)-1 : 0;
         case SPECEE_OP_VERIFY_Q4:
+            // (the group is not known here: room for the kernel that most of them take, if d can have such a group)
             if (check_dims(dm, false)) return (size_t)-1;
-            return 2 * align256((size_t)n * lm_head_q4_workgroups(dm->V) * sizeof(float));
+            return verify_bytes(n, std::max(lm_head_q4_workgroups(dm->V),
+                                            n >= 2 && dm->d % 64 == 0
+                                                ? head_states_workgroups(dm->d, dm->V, dm->d % 128 == 0 ? 128 : 64, INT_MAX)
+                                                : 0));
         case SPECEE_OP_LAYER_LOOP:
             if (check_dims(dm, true) || n > kLoopMaxTokens) return (size_t)-1;
             return loop_layout(n).total;
@@ -496,17 +516,17 @@ int specee_verify_q4(const specee_dims *dm, int N, const specee_half *hidden, co
     if ((rc = check_q4(dm, qweight, scales, zeros, group))) return rc;
     if (!hidden || !gamma || !ids || !token || !max_logit || !hit) return SPECEE_EINVAL;
     if (misaligned(hidden) || misaligned(gamma) || misaligned(workspace)) return SPECEE_EALIGN;
-    // the workspace is sized for the vector kernel's candidates; the kernels for several states leave at most as many
-    const size_t half_ws = align256((size_t)N * lm_head_q4_workgroups(dm->V) * sizeof(float));
-    if (!workspace || workspace_bytes < 2 * half_ws) return SPECEE_EWORKSPACE;
+    // (the vector kernel's candidates; lm_head_q4_mfma.hip leaves at most as many)
+    int P = lm_head_q4_workgroups(dm->V);
+    if (!workspace || workspace_bytes < verify_bytes(N, P)) return SPECEE_EWORKSPACE;
+    const bool states = head_states_q4_preferred(dm->d, dm->V, N, group);
+    if (states) P = head_states_workgroups(dm->d, dm->V, group, verify_fits(N, workspace_bytes));
     float *best_val = static_cast<float *>(workspace);
-    int32_t *best_idx = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + half_ws);
+    int32_t *best_idx = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + verify_bytes(N, P) / 2);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const HeadQ4 q4{qweight, H(scales), H(zeros), group};
-    int P = lm_head_q4_workgroups(dm->V);
     hipError_t e;
-    if (head_states_q4_preferred(dm->d, dm->V, N, group)) {
-        P = head_states_workgroups(dm->d, dm->V, group, P);
+    if (states) {
         e = launch_head_states_argmax(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), nullptr, q4, P, best_val, best_idx,
                                       gate, done, st);
     } else {
@@ -646,14 +666,13 @@ int specee_verify(const specee_dims *dm, int N, const specee_half *hidden, const
     if (!hidden || !gamma || !lm_head || !ids || !token || !max_logit || !hit) return SPECEE_EINVAL;
     if (misaligned(hidden) || misaligned(gamma) || misaligned(lm_head) || misaligned(workspace)) return SPECEE_EALIGN;
     const bool vec = N <= 2;
-    int P = vec ? lm_head_gemv_workgroups(dm->V) : lm_head_gemm_workgroups(dm->V);
-    const size_t half_ws = align256((size_t)N * P * sizeof(float));
-    if (!workspace || workspace_bytes < 2 * half_ws) return SPECEE_EWORKSPACE;
-    float *best_val = static_cast<float *>(workspace);
-    int32_t *best_idx = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + half_ws);
-    hipStream_t st = static_cast<hipStream_t>(stream);
+    int P = verify_workgroups(dm->V, N);
+    if (!workspace || workspace_bytes < verify_bytes(N, P)) return SPECEE_EWORKSPACE;
     const bool states = head_states_preferred(dm->d, dm->V, N);
-    if (states) P = head_states_workgroups(dm->d, dm->V, 0, P);
+    if (states) P = head_states_workgroups(dm->d, dm->V, 0, verify_fits(N, workspace_bytes));
+    float *best_val = static_cast<float *>(workspace);
+    int32_t *best_idx = reinterpret_cast<int32_t *>(static_cast<char *>(workspace) + verify_bytes(N, P) / 2);
+    hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
     if (states)
         e = launch_head_states_argmax(dm->d, dm->V, dm->eps, N, H(hidden), H(gamma), H(lm_head), HeadQ4{}, P, best_val,

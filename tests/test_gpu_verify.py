@@ -259,6 +259,25 @@ def test_head_keeps_the_small_elements_beside_a_large_one(sp, d, V, N, group, la
     assert np.linalg.norm(got - ref) <= 8.1e-7 * (2.5 if group else 1.0) * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("d,V,N,group", [(4096, 6007, 16, 0), (1024, 300, 3, 0), (512, 20011, 5, 0), (4096, 8003, 16, 128),
+                                         (512, 5003, 7, 64)])
+def test_verify_of_several_states_on_as_many_workgroups_as_the_workspace_has_room_for(sp, d, V, N, group):
+    """The queried workspace holds an arg-max candidate per tile of 16 rows or per CU, whichever is less (the kernels for
+    other shapes leave one per 32 or 128 rows); what they leave is enough too, with the same outputs."""
+    rng = np.random.default_rng(V)
+    head, _, _ = head_rows(rng, V, d, group)
+    verify, op = (sp.verify_q4, sp.OP_VERIFY_Q4) if group else (sp.verify, sp.OP_VERIFY)
+    room = sp.workspace_bytes(op, sp.Dims(d, V, 2, 1, 1e-5, 0.5), N)
+    assert room >= 2 * N * 4 * min(256, -(-V // 16))
+    h, g = dev(rng.standard_normal((N, d)).astype(np.float16)), dev(np.ones(d, np.float16))
+    ids = dev(rng.integers(0, V, (N, 2)).astype(np.int32))
+    least = 2 * 256 * -(-N * 4 * -(-V // (32 if group else 128)) // 256)
+    a, b = (verify(h, g, *head, ids, workspace=torch.full((n // 4,), 1e30, device="cuda")) for n in (room, least))
+    assert all(torch.equal(a[k], b[k]) for k in ("token", "max_logit", "hit"))
+    full = (sp.lm_head_gemv_q4 if group else sp.lm_head_gemv)(h, g, *head)
+    assert torch.equal(a["token"].long(), full.argmax(dim=1)) and torch.equal(a["max_logit"], full.max(dim=1).values)
+
+
 @pytest.mark.parametrize("d,large", [(2048, 0), (3072, 0), (4096, 0), (4608, 0), (5120, 0), (4096, 1500.0), (5120, 900.0)])
 def test_fp16_head_of_several_states_sums_as_exactly_as_of_one(sp, d, large):
     """Both sum in 32 bits.  Of one state a lane adds d / 64 products in a row; of several, a chain of four matrix
