@@ -1,4 +1,4 @@
-"""GPU: the early-exit decode loop in one persistent launch on the 4-bit group-quantised LM head
+"""GPU: the early-exit decode loop in one call on the 4-bit group-quantised LM head
 (specee_layer_loop_q4; paper Sec. 4.3.3 and 5.3 in the weight-quantised setting of Sec. 7.1 / 7.3) against the
 oracle's loop on the same codes, scales and zero-points."""
 import numpy as np
@@ -213,3 +213,59 @@ def test_layer_loop_q4_predictors_are_as_exact_in_every_group(sp, d, group):
         out = sp.layer_loop_q4(dev(h), dev(g), q, a, b, grp, dev(ids), W1, w2, threshold=2.0)
         return np.linalg.norm(host(out["logits"]) - ref)
     assert error(group) <= 1.15 * error(32)
+
+
+# ---- groups other than 128 and 64: the kernel that walks the layers
+WALKED = [
+    # seed, d, V, K, H, L, B, group, plant, threshold
+    (2, 520, 777, 3, 100, 7, 5, 8, [6, 1, None, 3, 3], 0.48),     # words of codes
+    (2, 1024, 301, 4, 512, 6, 7, 32, [0, 3, None, 5, 1, 2, 4], 0.45),
+    (3, 8192, 600, 4, 1024, 5, 2, 256, [4, 1], 0.45),             # two vectors per thread
+]
+
+
+@pytest.mark.parametrize("seed,d,V,K,H,L,B,group,plant,thr", WALKED)
+def test_layer_loop_q4_walked_with_an_active_mask_never_and_always_firing(sp, oracle, seed, d, V, K, H, L, B, group, plant, thr):
+    t = plant_hits(oracle, loop_inputs_q4(seed, d, V, K, H, L, B, group), plant)
+    active = np.ones(L, np.int32)
+    active[[0, 3]] = 0
+    oracle.set_threads(8)
+    ref = check_loop(oracle, sp, t, thr, active=active, what="walked, active mask", graph=True)
+    assert not ref["scores"][0].any() and not ref["scores"][3].any() and ref["exit"].any()
+    ref = check_loop(oracle, sp, t, 2.0, what="walked, never fires")
+    assert np.all(ref["exit_layer"] == -1) and not ref["exit"].any()
+    ref = check_loop(oracle, sp, t, -1.0, what="walked, always fires", graph=True)
+    oracle.set_threads(1)
+    assert ref["exit"].sum() > ref["hit"].sum() >= 1
+
+
+@pytest.mark.parametrize("seed,L,group,thr", [(3, 70, 32, 2.0), (7, 70, 32, -1.0), (3, 150, 8, 2.0), (3, 150, 32, -1.0),
+                                              (3, 1100, 32, 2.0)])
+def test_layer_loop_q4_walked_down_a_deep_stack_with_a_sparse_active_mask(sp, oracle, seed, L, group, thr):
+    """Both words of the mask, the mask in LDS beyond 128 layers and in place beyond 1024."""
+    t = plant_hits(oracle, loop_inputs_q4(seed, 64, 40, 4, 8, L, 3, group), [None, L - 1, 64])
+    rng = np.random.default_rng(5)
+    active = (rng.random(L) < 0.1).astype(np.int32)
+    active[[0, 63, 64, L - 1]] = [1, 1, 0 if thr > 1 else 1, 1]
+    if L > 128:
+        active[[127, 128]] = 1
+    ref = check_loop(oracle, sp, t, thr, active=active, what=f"walked, {L} layers")
+    assert (ref["exit"].sum() > 10) == (thr < 0) and not ref["scores"][active == 0].any()
+
+
+def test_layer_loop_q4_walked_bounded_wait_gives_up_instead_of_hanging(sp, oracle):
+    """One poll: a token's workgroups almost never meet; status 1 then, and the next call on the same workspace is clean."""
+    t = plant_hits(oracle, loop_inputs_q4(12, 1024, 3001, 4, 512, 4, 2, 32), [1, 2])
+    args = [dev(t["hidden"]), dev(t["gamma"]), dev(t["q"].view(np.int32)), dev(t["scales"]), dev(t["zeros"]), t["group"],
+            dev(t["ids"]), dev(t["W1"]), dev(t["w2"]), dev(t["b1"]), dev(t["b2"])]
+    out = sp.layer_loop_q4(*args, threshold=-1.0, spin_limit=1)
+    torch.cuda.synchronize()
+    ref = reference(oracle, t, -1.0)
+    st = host(out["status"])
+    assert set(st.tolist()) <= {0, 1}
+    ok = st == 0
+    assert np.array_equal(host(out["exit_layer"])[ok], ref["exit_layer"][ok])
+    assert np.all(host(out["exit_layer"])[~ok] == -1) and np.all(host(out["token"])[~ok] == -1)
+    again = sp.layer_loop_q4(*args, threshold=-1.0, workspace=out["_workspace"])
+    torch.cuda.synchronize()
+    assert np.all(host(again["status"]) == 0) and np.array_equal(host(again["exit_layer"]), ref["exit_layer"])
