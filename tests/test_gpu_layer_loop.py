@@ -134,7 +134,7 @@ def test_layer_loop_device_side_control(sp, oracle):
         check(state, exp, done_ref, c, f"graph replay {rep}")
 
 
-# ------------------------------------------------------------------ the same loop as ONE launch (specee_layer_loop)
+# ------------------------------------------------------------------ the same loop as one call (specee_layer_loop)
 def loop_inputs(seed, d, V, K, H, L, B, plant, bias=True):
     """Random model and tokens; token b's first id is the full head's arg-max at layer plant[b] (None: never)."""
     rng = np.random.default_rng(seed)
@@ -215,7 +215,7 @@ def check_loop(oracle, sp, t, threshold, active=None, what="", graph=False):
     (1, 520, 777, 3, 100, 7, 5, [6, 1, None, 3, 3], 0.48, True),            # K odd: generic MLP path
     (1, 8192, 2000, 4, 1024, 4, 2, [3, 1], 0.45, True),                     # two vectors per thread, H > 512
     (4, 64, 40, 16, 8, 5, 4, [2, 2, None, 0], 0.5, True),                   # K = KMAX, tiny d
-    (14, 1024, 1000, 4, 512, 6, 64, [i % 6 if i % 5 else None for i in range(64)], 0.6, False),  # 64 tokens: groups of 4
+    (14, 1024, 1000, 4, 512, 6, 64, [i % 6 if i % 5 else None for i in range(64)], 0.6, False),  # 64 tokens: rounds over them
 ])
 def test_layer_loop_one_launch_matches_oracle(sp, oracle, seed, d, V, K, H, L, B, plant, threshold, bias):
     t, plant = loop_inputs(seed, d, V, K, H, L, B, plant, bias)
@@ -255,7 +255,7 @@ def test_layer_loop_one_launch_llama7b_shape(sp, oracle):
 
 
 def test_layer_loop_bounded_wait_gives_up_instead_of_hanging(sp, oracle):
-    """With a spin limit of one poll a group almost never meets: the call must still return, with status 1 for
+    """With a spin limit of one poll the workgroups almost never meet: the call must still return, with status 1 for
     the tokens it gave up on (or 0 with correct results if the workgroups did arrive together)."""
     t, plant = loop_inputs(12, 1032, 3001, 4, 512, 4, 2, [1, 2])
     t = plant_hits(oracle, t, plant)
@@ -276,7 +276,7 @@ def test_layer_loop_bounded_wait_gives_up_instead_of_hanging(sp, oracle):
 
 
 def test_layer_loop_deep_stack_with_a_sparse_active_mask(sp, oracle):
-    """More than 128 layers (the mask no longer fits the two scalar words) with most predictors switched off."""
+    """Several windows of 64 layers, previous active layers more than one of them away, most predictors switched off."""
     L = 150
     t, _ = loop_inputs(3, 64, 40, 4, 8, L, 3, [None, None, None])
     rng = np.random.default_rng(5)
@@ -284,7 +284,7 @@ def test_layer_loop_deep_stack_with_a_sparse_active_mask(sp, oracle):
     active[[0, 63, 64, 127, 128, 149]] = [1, 1, 0, 1, 1, 1]
     ref = check_loop(oracle, sp, t, 2.0, active=active, what="deep stack, never fires")
     assert np.all(ref["scores"][active == 0] == 0) and np.all(ref["scores"][active == 1] != 0)
-    t2, _ = loop_inputs(3, 64, 40, 4, 8, 100, 3, [None, None, None])      # 65..128 layers: both mask words
+    t2, _ = loop_inputs(3, 64, 40, 4, 8, 100, 3, [None, None, None])      # two windows
     a2 = (rng.random(100) < 0.4).astype(np.int32)
     a2[[0, 63, 64, 99]] = [0, 1, 1, 1]
     check_loop(oracle, sp, t2, 2.0, active=a2, what="100 layers, never fires")
@@ -327,13 +327,14 @@ def test_layer_loop_compiled_in_widths(sp, oracle, seed, K, d, H):
 
 
 def test_layer_loop_rereads_a_head_of_134_mb(sp, oracle):
-    """One token, six verifications of a head above the line of the non-temporal hint: four with it, two without."""
-    t, plant = loop_inputs(2, 8192, 8200, 4, 512, 6, 1, [5], False)
+    """One token, twenty verifications, sixteen to a pass: the head, more than half of the last-level cache, is read twice,
+    and the token leaves in the second pass."""
+    t, plant = loop_inputs(2, 8192, 8200, 4, 512, 20, 1, [19], False)
     t = plant_hits(oracle, t, plant)
     oracle.set_threads(8)
     ref = check_loop(oracle, sp, t, -1.0, what="134 MB head")
     oracle.set_threads(1)
-    assert ref["exit"].sum() == 6 and ref["exit_layer"][0] == 5
+    assert ref["exit"].sum() == 20 and ref["exit_layer"][0] == 19
 
 
 @pytest.mark.parametrize("seed,K,d,H", [(0, 1, 520, 9), (0, 2, 4104, 513), (0, 6, 520, 515), (0, 7, 4104, 40)])
@@ -359,7 +360,8 @@ def test_layer_loop_other_widths(sp, oracle, seed, K, d, H):
 ])
 def test_layer_loop_verifies_what_fired_sixteen_at_a_time(sp, d, V, L, B, group, plant):
     """Every active layer fires.  A verification's sums do not depend on which others share the pass, so tokens, hits and
-    exits are those of specee_verify on the same hidden states, to the bit."""
+    exits are, to the bit, those of specee_verify on the same hidden states, sixteen at a time (for one state it sums in
+    another order)."""
     from test_gpu_verify import head_rows
     rng = np.random.default_rng(d + V + L)
     K, H = 3, 40
