@@ -287,6 +287,12 @@ int specee_predict_tree_q4(const specee_dims *dims, int G, int N, int Mcap, cons
  * token's previous active layer; if the exit flag is set, specee_verify on the
  * same hidden state; on a hit the loop ends for that token.  What lies after a
  * token's exit counts as not evaluated, and the host takes no part in any decision.
+ * (A verification's sums are those of specee_verify for 3 to 16 states, on a
+ * quantised head in groups of 128 and 64 of specee_verify_q4 for as many as make it
+ * take them 16 at a time; for fewer it adds in another order, so that two logits
+ * closer to each other than the rounding of their sums, 1e-7 of a typical logit, may
+ * change places.  An infinite weight of the head makes its logit infinite in either;
+ * with an infinite gamma, logits that are infinite for one state may be NaN.)
  *   hidden [L][B][d] (every layer's hidden state exists before the call),
  *   ids [B][K], prev0 [B][K] or NULL (zeros), mlp with leading L (as for
  *   specee_predict_sweep), active [L] int32 or NULL (all layers active).

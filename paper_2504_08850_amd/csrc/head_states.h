@@ -3,15 +3,16 @@
 //     Y[n][v] = r_n * sum_i x[n][i] * W[v][i],   x = h * gamma,
 //     quantised  W[v][i] = scale[v][g] * (code[v][i] - zero[v][g]),  g = i / group.
 // One pass over the head is all the memory traffic there is, so the kernel is built around the stream:
-//   * the hidden dimension is cut over the wavefronts of a workgroup: wavefront w owns 512 consecutive elements of it
-//     (four chunks of 128) for all rows of the workgroup.  The x of its elements -- the same for every row -- is turned
-//     into matrix operands once and stays in registers (128 of them); nothing is shared between the wavefronts while
-//     they stream, so there is neither LDS traffic nor a barrier per stage;
-//   * a tile is 16 rows.  A wavefront's 1024 bytes (fp16) or 256 bytes (codes) of each row come in 16-byte loads, each
-//     instruction whole 128-byte lines of eight rows, with the non-temporal hint (hs_hint says when); two such loads become the operands
-//     of two matrix steps by exchanging halves of 16 lanes.  Every register of a tile is asked for again, for a later
-//     tile, as soon as it has been used: 128 KB per CU are in flight all the time;
-//   * every eight tiles (four, with sixteen wavefronts) the partial sums meet in LDS and are added in ascending order of elements.
+//   * the hidden dimension is cut over the wavefronts of a workgroup: wavefront w owns CPW chunks of 128 consecutive
+//     elements of it (512, or 256 of some quantised heads: hs_chunks_per_wave) for all rows of the workgroup.  The x of its
+//     elements -- the same for every row -- is turned into matrix operands once and stays in registers (32 per chunk);
+//     nothing is shared between the wavefronts while they stream, so there is neither LDS traffic nor a barrier per stage;
+//   * a tile is 16 rows.  A wavefront's 256 bytes per chunk (fp16) or 64 (codes) of each row come in 16-byte loads, each
+//     instruction whole 128-byte lines of eight rows, with the non-temporal hint (hs_hint says when); two such loads become
+//     the operands of two matrix steps by exchanging halves of 16 lanes.  Every register of a tile is asked for again, for
+//     the next tile, as soon as it has been used: a tile per wavefront is in flight all the time, 128 KB per CU of an fp16
+//     row of 4096 (eight wavefronts), 80 KB where a row makes five wavefronts (4608, in two passes), 32 KB of codes;
+//   * every 2 * CPW tiles (eight or four) the partial sums meet in LDS and are added in ascending order of elements.
 // Shorter rows (d <= 2048) leave room for several workgroups on a CU, or for several groups of wavefronts in one workgroup,
 // which take the tiles in turn and meet together.
 // Longer rows (d > 4096) are done in passes over the workgroup's rows, 4096 elements or less at a time; the sums of

@@ -130,12 +130,17 @@ bool head_states_q4_ok(int group) {
 }
 
 // A pass here costs the same for one state as for sixteen, and at least some 5 us + 1.2 us per 1024 columns; the vector
-// kernel's time is that of all its rows, N * V.  Vector kernel against this one, us, 4096 columns: groups of 128: 32000
-// rows, 2 states 32.5 / 21.2, 16 states 201 / 23.8; 8000 rows, 2 states 12.5 / 10.7; 2000 rows, 8 states 12.6 / 9.1;
+// kernel's time is that of all its rows, N * V.  Vector kernel against this one, logits, us, 4096 columns: groups of 128:
+// 32000 rows, 2 states 32.5 / 21.2, 16 states 201 / 23.8; 8000 rows, 2 states 12.5 / 10.7; 2000 rows, 8 states 12.6 / 9.1;
 // 500 rows, 16 states 7.8 / 10.5; groups of 64: 32000 rows, 2 states 32.5 / 22.8; 8000 rows, 2 states 12.0 / 12.0, 4
 // states 20.1 / 12.0; 4096 rows, 4 states 9.8 / 10.5.  4608 and 5120 columns, whose last wavefronts are idle in part, are
 // the latest to gain (8000 rows, 2 states, groups of 128: 14.9 / 15.7, of 64: 15.2 / 18.4).  One state stays on the
 // vector units (32000 rows 18.2 / 21.2).
+// Which states a gate lets through is known on the device only, and a state's logits are the same whoever else is let
+// through, so the line is that of all N.  The vector kernel skips the others one by one and is the faster one, on small
+// heads, while few are let through (verification, 8000 rows, groups of 128, 1 of 4 states 11.1 / 16.1, 2 of 4 14.0 / 16.3,
+// all 23.4 / 16.3; 2000 rows, 1 of 16 10.2 / 15.7, all 22.4 / 15.8; 32000 rows, groups of 64, 1 of 2 20.0 / 27.2, both 33.5 /
+// 27.2), and none at all costs 4 us with both.
 bool head_states_q4_preferred(int d, int V, int N, int group) {
     return N >= 2 && head_states_q4_ok(group) && (long long)N * V >= (group == 128 ? 16000 : 24000);
 }

@@ -25,13 +25,13 @@
 // wavefront would make the LDS reads the bound.  B sits in LDS in fragment order, double-buffered: a wavefront's
 // read is 64 consecutive 16-byte pieces, without bank conflicts.
 //
-// Groups of exactly 128 and 64 go to head_states.hip where they gain from the matrix cores (same shapes: 23.8 us, groups of
-// 64 25.0 us); this kernel does the other multiples of 32.
+// Groups of exactly 128 and 64 go to head_states.hip where they gain from the matrix cores; this kernel does the other
+// multiples of 32.
 //
-// Measured against the vector kernel, 32000 x 4096, groups of 128 (70 MB): 16 states 193 -> 27.2 us, 8 states
-// 106 -> 25.6 us, 2 states 32.1 -> 25.8 us; with arg-max, 16 states 195 -> 29.9 us.  Groups of 64 (twice the folds):
-// 191 -> 34.3 us.  50280 x 2048, 16 states: 171 -> 28.8 us.  The time hardly depends on the number of states: the
-// instruction streams (unpacking, building B, folding), the matrix cores and the 70 MB (11 us) overlap in part only.
+// Measured against the vector kernel: 32000 x 4096, groups of 256, 2 states 32.1 -> 24.4 us, 16 states 202 -> 26.5;
+// 32000 x 3072, groups of 192, 16 states 184 -> 25.8, groups of 96 174 -> 36.5; 50280 x 2048, groups of 32, 172 -> 52.9.
+// The time hardly depends on the number of states: the instruction streams (unpacking, building B, folding), the matrix
+// cores and the codes (32000 x 4096: 11 us) overlap in part only.
 #include "device_utils.h"
 #include "kernels.h"
 
@@ -374,10 +374,13 @@ int lm_head_q4_mfma_workgroups(int V) {
 //   folding, the folds of small groups costing more -- however few rows there are;
 //   vector kernel, rounds of 512 workgroups (the last one partly filled) of one state's rows each, whose time is a
 //   prologue plus the rows; above 64 rows per workgroup the re-reads of the larger head show.
-// Vector kernel against this one, 4096 columns in groups of 128: 32000 rows, 2 states 31 / 24 us, 16 states 193 / 27 us;
-// 8000 rows, 2 states 11 / 20 us, 4 states 20 / 21, 6 states 27 / 21; 2000 rows, 16 states 19 / 22, 32 states 33 / 22.
-// Groups of 64: 32000 rows, 2 states 31 / 31, 3 states 44 / 31; 8000 rows, 4 states 19 / 28, 8 states 33 / 29.  Groups
-// of 32, 2048 columns: 50280 rows, 3 states 40 / 50, 4 states 52 / 50.
+// Groups of 128 and 64 were part of that and hardly come here any more (head_states.hip).  Of those that do, 455 pairs (256,
+// 512, 192, 320, 160, 96 and 32; d = 1024 ... 8192, V = 1000 ... 50280, 2 to 16 states): the slower kernel by more than 6 %
+// in 23, by 28 % at most (groups of 256, 8000 x 2048, 4 states 16.2 / 12.7 us), by 1.6 % on average.
+// Vector kernel against this one, us: groups of 256, 4096 columns, 32000 rows, 2 states 32.1 / 24.3, 8000 rows, 2 states 12.0
+// / 20.4, 4 states 21.1 / 20.3, 2000 rows, 16 states 20.2 / 21.6; groups of 192, 3072 columns, 32000 rows, 2 states 29.1 /
+// 23.5, 8000 rows, 4 states 18.9 / 21.2, 8 states 33.2 / 21.6; groups of 32, 2048 columns, 50280 rows, 3 states 39.7 / 50.2,
+// 4 states 51.6 / 50.4.
 bool lm_head_q4_mfma_preferred(int d, int V, int N, int group, const uint32_t *qweight) {
     const int lw = qm_words(d, group, qweight);
     if (N < 2 || lw == 0 || qm_lds_bytes(d, group) > kQmLdsBudget) return false;
