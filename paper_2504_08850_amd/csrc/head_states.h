@@ -120,6 +120,17 @@ __device__ __forceinline__ int hs_bound(float ssq) {
     return ((int)(__builtin_bit_cast(uint32_t, ssq) >> 23) - 127 + 2) >> 1;
 }
 
+// Sum over the four lane groups: lanes (0, c) ... (3, c), in all of them, on the vector units.
+__device__ __forceinline__ float hs_over_q(float v) {
+    const uint32_t a = __builtin_bit_cast(uint32_t, v);
+    const auto s = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    const uint32_t s0 = s[0], s1 = s[1];  // (a bit cast of an element of a vector reads its first one)
+    const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, s0) + __builtin_bit_cast(float, s1));
+    const auto t = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    const uint32_t t0 = t[0], t1 = t[1];
+    return __builtin_bit_cast(float, t0) + __builtin_bit_cast(float, t1);
+}
+
 // LW = 2: words between lane groups, so that word j holds elements of sub-chunk j / LW only
 template <int LW>
 __device__ __forceinline__ void hs_exchange(uint32_t (&w)[4]) {
@@ -244,8 +255,7 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
             }
         };
         auto store_tx = [&](int i, float sum) {  // a sub-chunk's sum of x is complete; only this wavefront reads it
-            sum += __shfl_xor(sum, 16, kWave);
-            sum += __shfl_xor(sum, 32, kWave);
+            sum = hs_over_q(sum);
             if (q == 0) tx[(wave * kSpw + i / (Q4 ? LW : 1)) * kHsStates + c] = sum;
         };
         // the hidden states and the weight are asked for before the rows: loads come back in order, and the operands are made
@@ -280,13 +290,9 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
                 }
                 ssq += some;
             }
-            auto over_q = [](float v) {
-                v += __shfl_xor(v, 16, kWave);
-                return v + __shfl_xor(v, 32, kWave);
-            };
-            ssq = over_q(ssq);
-            ssx = over_q(ssx);
-            if (__any(!(ssx < INFINITY))) {  // a product that is no half
+            ssq = hs_over_q(ssq);
+            ssx = hs_over_q(ssx);
+            if (__builtin_expect(__any(!(ssx < INFINITY)), 0)) {  // a product that is no half
                 ssx = 0.f;
 #pragma unroll
                 for (int i = 0; i < kSteps; ++i)
@@ -296,7 +302,7 @@ __device__ __forceinline__ void head_states_rows(const HsParams &p, unsigned cha
                         const half2_t x = half2_t{xh[i][e], xh[i][e + 1]} * down * (half2_t{xl[i][e], xl[i][e + 1]} * down);
                         ssx = __builtin_amdgcn_fdot2(x, x, ssx, false);
                     }
-                ssx = 0x1p36f * over_q(ssx);
+                ssx = 0x1p36f * hs_over_q(ssx);
             }
             ssg = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wave_sum_to_last_row(ssg)), kWave - 1));
             // |x * 2^u| < 2^15 by the norm; of it as much through gamma as leaves that below 2^15 too, the rest through h
