@@ -465,9 +465,12 @@ hipError_t launch_layer_loop(const LoopParams &p, int max_wgs, hipStream_t s) {
         return hipGetLastError();
     }
     // All predictors, then passes over the head for 16 verifications, wherever head_states.h has such a pass.  Layer by layer
-    // against that, us, one token, 32 layers: 32000 x 4096 fp16, one of them active and firing 54.7 / 54.7, eleven firing
-    // 511 / 58 (50280 x 2048 49.2 / 46.3 and 434 / 50; 16500 x 4096, whose 1032 tiles are one round and eight more than 256
-    // CUs have, 39.8 / 43.3 and 328 / 48); every active layer that does not fire costs layer by layer 1.75 more.
+    // against that, us, fp16, one token, 32 layers, two heads in turn, one of the layers active and firing / eleven firing:
+    // 32000 x 4096 56.8 against 58.2 / 516 against 62; 50280 x 2048 50.7 against 48.4 / 434 against 52; 16500 x 4096, whose
+    // 1032 tiles are four rounds and eight more than 256 CUs have, 40.3 against 44.2 / 332 against 48; rows that leave
+    // wavefronts idle 20011 x 4104 47.9 against 56.5 / 415 against 61, 32001 x 3080 50.8 against 61.3 / 435 against 65.  Every
+    // active layer that does not fire costs layer by layer 1.75 more: with the nine or so that a scheduler leaves of 32
+    // before the one that fires all of these gain or come out even.
     if (!p.qweight || head_states_q4_ok(p.group)) {
         const hipError_t e = launch_loop_scores(p, s);
         return e == hipSuccess ? launch_loop_verify(p, max_wgs, s) : e;

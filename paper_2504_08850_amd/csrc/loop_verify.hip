@@ -16,8 +16,8 @@
 //     The notes lie 128 bytes apart, one per four or eight workgroups: with all of them polling the counter itself, the
 //     memory channel that holds it was slow for the others' rows too, and the meeting took 6 us (512 workgroups: 9 us).
 // Most tokens are decided in the first pass, where verifying layer by layer took one pass per fired layer and token
-// (32000 x 4096, one token, 32 layers, exit at the one that fires: 64.7 -> 57.6 us; eleven that fire 511 -> 58 us).
-// Bound by the pass over the head: 45 us of it are the stream (5.8 TB/s), 5 the scores, 2 go by until the first states are
+// (32000 x 4096, one token, 32 layers, exit at the one that fires: 64.7 -> 58.7 us; eleven that fire 511 -> 59 us).
+// Bound by the pass over the head: 46 us of it are the stream (5.7 TB/s), 5 the scores, 2 go by until the first states are
 // known and 5 from the last row to the end of the kernel (arrival, winners, note, outputs).
 // The meeting needs every workgroup to be resident: the host sizes the grid from the occupancy that the runtime reports,
 // and every wait is bounded (spin limit), so a grid that cannot meet (another kernel holds the CUs) ends with status 1
